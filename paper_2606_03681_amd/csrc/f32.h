@@ -1,0 +1,59 @@
+// Kernels of the float32 mode (and of bfloat16 shapes outside the bf16 matrix-core envelope):
+// float32 arithmetic throughout, storage type T (float or bf16), products on the fp32 matrix
+// cores (v_mfma_f32_16x16x4_f32).
+#pragma once
+
+#include "common.h"
+#include "fast.h"
+
+namespace tfm {
+
+// Chunks of cells that the weight gradients of one backward pass are split into: Z chunks of
+// `chunk` cells (a multiple of 32).  Z never falls as N grows, so the buffers sized for Nmax
+// cells hold the partials of any N <= Nmax.
+struct F32Split {
+  int Z;
+  int64_t chunk;
+};
+F32Split f32_split(int64_t N, int E, int H);
+// Partial rows of one LayerNorm backward.
+int f32_ln_rows(int64_t N);
+// Floats of the weight and bias partials (all six products) and of the norm partials.
+size_t f32_wpart_floats(int64_t Nmax, int E, int H);
+size_t f32_lnpart_floats(int64_t Nmax, int E);
+
+// One weight gradient: part[z][n][k] = sum over the cells m of chunk z of Y[m][n] X[m][k] and
+// bpart[z][n] = sum of Y[m][n].  Y: compact rows, or ROWS_ITEM_HM (Y, Y2, Y3 the head-major item
+// dQ, dK, dV); X: compact or native rows.
+template <class T>
+struct F32WgradJob {
+  const T *Y, *Y2, *Y3, *X;
+  float *part, *bpart;
+  int32_t N, K, ymode, xmode;
+  int32_t tile0, ntn;  // first tile of the job, tiles along N (set by the launch)
+};
+constexpr int F32_WGRADS = 6;
+template <class T>
+struct F32WgradArgs {
+  F32WgradJob<T> j[F32_WGRADS];
+  int32_t n, tiles, Z;
+  int64_t M, chunk;
+  Geo g;
+};
+// All weight gradients of one backward pass in one launch (a.j[0..n) filled in).
+template <class T>
+hipError_t launch_f32_wgrads(F32WgradArgs<T>& a, const F32Split& sp, hipStream_t s);
+
+// h = LN(a + b), a in amode rows (compact or native), h in hmode rows; xhat, rstd compact.
+template <class T>
+hipError_t launch_f32_add_ln(const Geo& g, const T* a, int amode, const T* b, const float* gamma,
+                             const float* beta, T* h, int hmode, T* xhat, float* rstd,
+                             hipStream_t s);
+// du = LN'(dy), dy = dya (amode rows) + dyb (compact, may be null); part [f32_ln_rows(N)][2E]
+// receives per-workgroup column sums of dy xhat and dy.
+template <class T>
+hipError_t launch_f32_ln_bwd(const Geo& g, const T* dya, int amode, const T* dyb, const T* xhat,
+                             const float* rstd, const float* gamma, T* du, float* part,
+                             hipStream_t s);
+
+}  // namespace tfm

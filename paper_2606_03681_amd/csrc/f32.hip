@@ -1,0 +1,339 @@
+// Kernels of the float32 mode (declarations in f32.h).
+//
+// Every product runs on v_mfma_f32_16x16x4_f32 (float32 operands and accumulators; 157 TFLOP/s,
+// as much as the vector unit's FMAs could reach with every slot filled).  Lane layout, with
+// g = lane / 16 and c = lane % 16:
+//   A (16 x 4): lane holds A[c][g];  B (4 x 16): lane holds B[g][c];
+//   D (16 x 16): lane holds D[4g .. 4g+3][c].
+// Any bijection between the contraction index and (instruction, g) that A and B share gives the
+// same product, which the kernels use to read operands 16 bytes per lane and, in the attention
+// kernels, to feed a D tile straight back in as a B operand.
+#include "f32.h"
+
+#include <algorithm>
+
+#include "mfma.h"
+
+namespace tfm {
+
+namespace {
+
+__device__ __forceinline__ f32x4 mfma32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ float4 ld4(const float* p) {
+  return *reinterpret_cast<const float4*>(p);
+}
+__device__ __forceinline__ float4 ld4(const bf16* p) {
+  const uint2 u = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
+                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+}
+__device__ __forceinline__ void st4(float* p, const float4& v) {
+  *reinterpret_cast<float4*>(p) = v;
+}
+__device__ __forceinline__ void st4(bf16* p, const float4& v) {
+  *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16),
+                                            (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16));
+}
+__device__ __forceinline__ float4 zf4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
+
+// Native cell of active cell p (p < 2^26, so 32-bit division).
+__device__ __forceinline__ int64_t native32(const Geo& g, int64_t p) {
+  const uint32_t col = (uint32_t)p / (uint32_t)g.R;
+  const uint32_t r = (uint32_t)p - col * (uint32_t)g.R;
+  return g.col_cell0[col] + (int64_t)r * g.S;
+}
+
+// ---- weight gradients -------------------------------------------------------------------------
+// Contraction over cells: a workgroup sums one chunk of cells into a 64 x 64 tile of one weight
+// gradient, four waves of 32 x 32, 32 cells per step through two LDS buffers with the next
+// step's rows already in flight.  Both operands are read as rows of features (the contraction
+// index is the slow one), row stride 68 floats: the four lane groups of a fragment read take
+// cells 4 apart, 16 banks apart.  All products of a backward pass are one launch: on a table of
+// a few thousand cells no single one of them has enough tiles to fill the chip.
+constexpr int WM = 32;   // cells per step
+constexpr int WLS = 68;  // LDS row stride (floats)
+
+template <class T>
+__device__ __forceinline__ float4 wg_load(const Geo& g, const T* p0, const T* p1, const T* p2,
+                                          int mode, int64_t m, int64_t me, int f, int width) {
+  if (m >= me || f >= width) return zf4();
+  if (mode == ROWS_COMPACT) return ld4(p0 + m * width + f);
+  if (mode == ROWS_NATIVE) return ld4(p0 + native32(g, m) * width + f);
+  const uint32_t col = (uint32_t)m / (uint32_t)g.R;
+  const int r = (int)((uint32_t)m - col * (uint32_t)g.R);
+  int part;
+  const int64_t off = item_hm_offset(g, col, r, f, &part);
+  if (off < 0) return zf4();
+  return ld4((part == 0 ? p0 : (part == 1 ? p1 : p2)) + off);
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) float Ys[2][WM * WLS];
+  __shared__ __attribute__((aligned(16))) float Xs[2][WM * WLS];
+  // the tiles of one chunk sit on one XCD next to each other: its rows come from memory once
+  const int idx = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
+  const int z = (idx / a.tiles) * 8 + xcd, tl = idx % a.tiles;
+  const int64_t mb = (int64_t)z * a.chunk;
+  if (z >= a.Z || mb >= a.M) return;
+  const int64_t me = mb + a.chunk < a.M ? mb + a.chunk : a.M;
+  int ji = 0;
+  while (ji + 1 < a.n && tl >= a.j[ji + 1].tile0) ++ji;
+  const F32WgradJob<T>& J = a.j[ji];
+  const int t = tl - J.tile0;
+  const int n0 = (t % J.ntn) * 64, k0 = (t / J.ntn) * 64;
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+  const int lg = lane >> 4, c = lane & 15;
+  const int wn = (w >> 1) * 32, wk = (w & 1) * 32;
+  const int sc = tid & 15, sr = tid >> 4;  // staging: 4 features from 4 sc of cells sr, sr + 16
+  float4 y[2], x[2];
+  auto gload = [&](int64_t m0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int64_t m = m0 + sr + 16 * i;
+      y[i] = wg_load<T>(a.g, J.Y, J.Y2, J.Y3, J.ymode, m, me, n0 + 4 * sc, J.N);
+      x[i] = wg_load<T>(a.g, J.X, nullptr, nullptr, J.xmode, m, me, k0 + 4 * sc, J.K);
+    }
+  };
+  auto sstore = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      st4(&Ys[b][(sr + 16 * i) * WLS + 4 * sc], y[i]);
+      st4(&Xs[b][(sr + 16 * i) * WLS + 4 * sc], x[i]);
+    }
+  };
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = zero4();
+  const bool bias = k0 == 0;  // this tile also sums its columns of Y, 8 cells a wave and step
+  float bs = 0.f;
+  gload(mb);
+  sstore(0);
+  __syncthreads();
+  int b = 0;
+  for (int64_t m0 = mb; m0 < me; m0 += WM, b ^= 1) {
+    const bool more = m0 + WM < me;
+    if (more) gload(m0 + WM);
+#pragma unroll
+    for (int s = 0; s < WM / 4; ++s) {
+      const int row = 4 * lg + (s & 3) + 16 * (s >> 2);
+      float av[2], bv[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        av[i] = Ys[b][row * WLS + wn + 16 * i + c];
+        bv[i] = Xs[b][row * WLS + wk + 16 * i + c];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(av[i], bv[j], acc[i][j]);
+    }
+    if (bias) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) bs += Ys[b][(8 * w + r) * WLS + lane];
+    }
+    if (more) sstore(b ^ 1);
+    __syncthreads();
+  }
+  float* out = J.part + (int64_t)z * J.N * J.K;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int n = n0 + wn + 16 * i + 4 * lg;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int k = k0 + wk + 16 * j;
+      if (n >= J.N || k >= J.K) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(int64_t)(n + r) * J.K + k + c] = acc[i][j][r];
+    }
+  }
+  if (bias) {
+    Ys[0][tid] = bs;
+    __syncthreads();
+    if (tid < 64 && n0 + tid < J.N)
+      J.bpart[(int64_t)z * J.N + n0 + tid] =
+          (Ys[0][tid] + Ys[0][64 + tid]) + (Ys[0][128 + tid] + Ys[0][192 + tid]);
+  }
+}
+
+// ---- LayerNorm --------------------------------------------------------------------------------
+// One wave per cell, lane l holding features 4l .. 4l+3 (E <= 256) in 16-byte pieces.
+template <class T>
+__global__ __launch_bounds__(256) void k_f32_add_ln(Geo g, const T* __restrict__ a, int amode,
+                                                    const T* __restrict__ b,
+                                                    const float* __restrict__ gamma,
+                                                    const float* __restrict__ beta,
+                                                    T* __restrict__ h, int hmode,
+                                                    T* __restrict__ xhat,
+                                                    float* __restrict__ rstd) {
+  const int lane = threadIdx.x & 63, E = g.E;
+  const int64_t p = (int64_t)blockIdx.x * 4 + wave_id();
+  if (p >= g.N) return;
+  const bool act = 4 * lane < E;
+  const int64_t nat = amode == ROWS_NATIVE || hmode == ROWS_NATIVE ? native32(g, p) : 0;
+  float u[4] = {0.f, 0.f, 0.f, 0.f};
+  float4 gm = zf4(), be = zf4();
+  if (act) {
+    const float4 va = ld4(a + (amode == ROWS_NATIVE ? nat : p) * E + 4 * lane);
+    const float4 vb = ld4(b + p * E + 4 * lane);
+    gm = ld4(gamma + 4 * lane);
+    be = ld4(beta + 4 * lane);
+    u[0] = va.x + vb.x; u[1] = va.y + vb.y; u[2] = va.z + vb.z; u[3] = va.w + vb.w;
+  }
+  const float mean = wave_reduce_sum((u[0] + u[1]) + (u[2] + u[3])) / E;
+  float v = 0.f;
+  if (act) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u[i] -= mean;
+      v = fmaf(u[i], u[i], v);
+    }
+  }
+  const float rs = 1.0f / sqrtf(wave_reduce_sum(v) / E + 1e-5f);
+  if (act) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[i] *= rs;
+    st4(xhat + p * E + 4 * lane, make_float4(u[0], u[1], u[2], u[3]));
+    st4(h + (hmode == ROWS_NATIVE ? nat : p) * E + 4 * lane,
+        make_float4(fmaf(gm.x, u[0], be.x), fmaf(gm.y, u[1], be.y), fmaf(gm.z, u[2], be.z),
+                    fmaf(gm.w, u[3], be.w)));
+  }
+  if (lane == 0) rstd[p] = rs;
+}
+
+// Every wave takes cells blockIdx.x * 4 + wave, then a grid further on, and keeps running column
+// sums; the four waves' sums are added in order at the end.
+template <class T>
+__global__ __launch_bounds__(256) void k_f32_ln_bwd(Geo g, const T* __restrict__ dya, int amode,
+                                                    const T* __restrict__ dyb,
+                                                    const T* __restrict__ xhat,
+                                                    const float* __restrict__ rstd,
+                                                    const float* __restrict__ gamma,
+                                                    T* __restrict__ du, float* __restrict__ part) {
+  __shared__ float red[4][512];
+  const int lane = threadIdx.x & 63, w = wave_id(), E = g.E;
+  const bool act = 4 * lane < E;
+  const float4 gm = act ? ld4(gamma + 4 * lane) : zf4();
+  const float gv[4] = {gm.x, gm.y, gm.z, gm.w};
+  float c1[4] = {0.f, 0.f, 0.f, 0.f}, c2[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t p = (int64_t)blockIdx.x * 4 + w; p < g.N; p += (int64_t)gridDim.x * 4) {
+    float dy[4] = {0.f, 0.f, 0.f, 0.f}, x[4] = {0.f, 0.f, 0.f, 0.f};
+    const float rs = rstd[p];
+    if (act) {
+      const float4 a = ld4(dya + (amode == ROWS_NATIVE ? native32(g, p) : p) * E + 4 * lane);
+      const float4 b = dyb ? ld4(dyb + p * E + 4 * lane) : zf4();
+      const float4 xv = ld4(xhat + p * E + 4 * lane);
+      dy[0] = a.x + b.x; dy[1] = a.y + b.y; dy[2] = a.z + b.z; dy[3] = a.w + b.w;
+      x[0] = xv.x; x[1] = xv.y; x[2] = xv.z; x[3] = xv.w;
+    }
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      c1[i] = fmaf(dy[i], x[i], c1[i]);
+      c2[i] += dy[i];
+      s1 = fmaf(dy[i], gv[i], s1);
+      s2 = fmaf(dy[i] * gv[i], x[i], s2);
+    }
+    const float m1 = wave_reduce_sum(s1) / E, m2 = wave_reduce_sum(s2) / E;
+    if (act) {
+      float o[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = rs * (dy[i] * gv[i] - m1 - x[i] * m2);
+      st4(du + p * E + 4 * lane, make_float4(o[0], o[1], o[2], o[3]));
+    }
+  }
+  if (act) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      red[w][4 * lane + i] = c1[i];
+      red[w][E + 4 * lane + i] = c2[i];
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * E; i += 256)
+    part[(int64_t)blockIdx.x * 2 * E + i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+}
+
+int f32_tiles(int N, int K) { return ((N + 63) / 64) * ((K + 63) / 64); }
+
+}  // namespace
+
+F32Split f32_split(int64_t N, int E, int H) {
+  const int tiles = 2 * (f32_tiles(3 * E, E) + f32_tiles(E, E) + f32_tiles(H, E));
+  // enough workgroups for the chip, at least 64 cells and at most 2,048 in a chunk: a chunk's
+  // partial tile (16 KB, written and read once) is then no more than its operands' traffic, and
+  // no chain of sums is longer
+  const int64_t fill = (2048 + tiles - 1) / tiles;
+  int64_t Z = std::min<int64_t>((N + 63) / 64, std::max<int64_t>(fill, (N + 2047) / 2048));
+  if (Z < 1) Z = 1;
+  int64_t chunk = (N + Z - 1) / Z;
+  chunk = std::max<int64_t>((chunk + WM - 1) / WM * WM, WM);
+  return F32Split{(int)std::max<int64_t>((N + chunk - 1) / chunk, 1), chunk};
+}
+
+int f32_ln_rows(int64_t N) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (N + 15) / 16));
+}
+
+size_t f32_wpart_floats(int64_t Nmax, int E, int H) {
+  // chunk rounding may leave fewer chunks than asked for, never more
+  const int tiles = 2 * (f32_tiles(3 * E, E) + f32_tiles(E, E) + f32_tiles(H, E));
+  const int64_t fill = (2048 + tiles - 1) / tiles;
+  const int64_t Z = std::max<int64_t>(
+      1, std::min<int64_t>((Nmax + 63) / 64, std::max<int64_t>(fill, (Nmax + 2047) / 2048)));
+  return (size_t)Z * (8 * (size_t)E * E + 2 * (size_t)E * H + 9 * (size_t)E + H);
+}
+
+size_t f32_lnpart_floats(int64_t Nmax, int E) { return (size_t)f32_ln_rows(Nmax) * 2 * E * 3; }
+
+template <class T>
+hipError_t launch_f32_wgrads(F32WgradArgs<T>& a, const F32Split& sp, hipStream_t s) {
+  if (a.n < 1 || a.n > F32_WGRADS) return hipErrorInvalidValue;
+  a.M = a.g.N;
+  a.Z = sp.Z;
+  a.chunk = sp.chunk;
+  a.tiles = 0;
+  for (int i = 0; i < a.n; ++i) {
+    a.j[i].tile0 = a.tiles;
+    a.j[i].ntn = (a.j[i].N + 63) / 64;
+    a.tiles += f32_tiles(a.j[i].N, a.j[i].K);
+  }
+  k_f32_wgrads<T><<<(unsigned)((sp.Z + 7) / 8 * 8 * a.tiles), 256, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_f32_add_ln(const Geo& g, const T* a, int amode, const T* b, const float* gamma,
+                             const float* beta, T* h, int hmode, T* xhat, float* rstd,
+                             hipStream_t s) {
+  if (g.N <= 0) return hipSuccess;
+  k_f32_add_ln<T><<<(unsigned)((g.N + 3) / 4), 256, 0, s>>>(g, a, amode, b, gamma, beta, h, hmode,
+                                                            xhat, rstd);
+  return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_f32_ln_bwd(const Geo& g, const T* dya, int amode, const T* dyb, const T* xhat,
+                             const float* rstd, const float* gamma, T* du, float* part,
+                             hipStream_t s) {
+  if (g.N <= 0) return hipSuccess;
+  k_f32_ln_bwd<T><<<f32_ln_rows(g.N), 256, 0, s>>>(g, dya, amode, dyb, xhat, rstd, gamma, du,
+                                                   part);
+  return hipGetLastError();
+}
+
+#define INST(T)                                                                               \
+  template hipError_t launch_f32_wgrads<T>(F32WgradArgs<T>&, const F32Split&, hipStream_t);   \
+  template hipError_t launch_f32_add_ln<T>(const Geo&, const T*, int, const T*, const float*, \
+                                           const float*, T*, int, T*, float*, hipStream_t);   \
+  template hipError_t launch_f32_ln_bwd<T>(const Geo&, const T*, int, const T*, const T*,     \
+                                           const float*, const float*, T*, float*, hipStream_t);
+INST(float)
+INST(bf16)
+
+}  // namespace tfm

@@ -113,8 +113,8 @@ hipError_t launch_reduce_wfold(int Z, int N, int K, float* wpart, float* bpart,
                                const float* gamma, const float* beta, float* grad,
                                int accumulate, hipStream_t s);
 
-// Writes 0 to every element of the native tensor that lies in an inactive cell.
-hipError_t launch_zero_inactive(const Geo& g, bf16* native, hipStream_t s);
+// Writes 0 to every element (elt bytes each) of the native tensor that lies in an inactive cell.
+hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStream_t s);
 
 // Weight gradient dW[n][k] = sum_m dY[m][n] X[m][k] (+ db[n] = sum_m dY[m][n]) over M cells,
 // split into Z = wgrad_chunks(M) chunks of wgrad_chunk(M) cells (a multiple of 32, at most

@@ -84,25 +84,26 @@ hipError_t launch_weight_prep(const float* params, int E, int H, bf16* w, bf16* 
   return hipGetLastError();
 }
 
-// One wave per native row (b, r): the row's S cells are S * E contiguous elements, written in
-// 16-byte pieces with consecutive lanes on consecutive pieces, zero where the piece's cell is
+// One wave per native row (b, r): the row's S cells are S * per contiguous 16-byte pieces,
+// written with consecutive lanes on consecutive pieces, zero where the piece's cell is
 // inactive.  Rows of datasets with every cell active leave at once.
-__global__ void k_zero_inactive(Geo g, bf16* __restrict__ x) {
+__global__ void k_zero_inactive(Geo g, uint4* __restrict__ x, int per) {
   const int64_t row = (int64_t)blockIdx.x * 4 + wave_id();
   if (row >= (int64_t)g.B * g.R) return;
   const int b = (int)(row / g.R);
   if (g.ds[b].S == g.S) return;
-  const int lane = threadIdx.x & 63, per = g.E / 8;
+  const int lane = threadIdx.x & 63;
   const int32_t* cm = g.colmap + (int64_t)b * g.S;
-  uint4* p = reinterpret_cast<uint4*>(x + row * g.S * g.E);
+  uint4* p = x + row * g.S * per;
   const uint4 z = make_uint4(0, 0, 0, 0);
   for (int i = lane; i < g.S * per; i += 64)
     if (cm[i / per] < 0) p[i] = z;
 }
 
-hipError_t launch_zero_inactive(const Geo& g, bf16* native, hipStream_t s) {
+hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStream_t s) {
   const int64_t rows = (int64_t)g.B * g.R;
-  k_zero_inactive<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(g, native);
+  k_zero_inactive<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(
+      g, reinterpret_cast<uint4*>(native), (int)(g.E * elt / 16));
   return hipGetLastError();
 }
 

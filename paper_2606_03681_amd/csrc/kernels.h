@@ -33,26 +33,10 @@ hipError_t launch_linear(int64_t M, int Nout, int K, const TA* A, int64_t lda, c
 template <class T>
 hipError_t launch_linear_item_qkv(const Geo& g, const T* A, const float* w, const float* bias,
                                   T* q, T* k, T* v, hipStream_t s);
-// partial[z][j][i] = sum over rows m of chunk z of dY[m*ldy + j] * X[m*ldx + i]
-template <class T>
-hipError_t launch_wgrad(int64_t M, int Nj, int Ki, const T* dY, int64_t ldy, const T* X,
-                        int64_t ldx, int64_t chunk, float* partial, hipStream_t s);
 // partial[z][j] = sum over rows m of chunk z of A[m*lda+j] (* B[m*ldb+j] if B non-null)
 template <class T>
 hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B, int64_t ldb,
                          int64_t chunk, float* partial, hipStream_t s);
-// grad[i] = (accumulate ? grad[i] : 0) + sum_z partial[z*count + i], z ascending
-hipError_t launch_reduce_partials(int Z, int64_t count, const float* partial, float* grad,
-                                  int accumulate, hipStream_t s);
-
-// h = LN(a + b) (b may be null); xhat and rstd saved for the backward pass.
-template <class T>
-hipError_t launch_add_ln(int64_t N, int E, const T* a, const T* b, const float* gamma,
-                         const float* beta, T* h, T* xhat, float* rstd, hipStream_t s);
-// du = LN'(dy) with dy = dya (+ dyb); dysum (nullable) receives dy.
-template <class T>
-hipError_t launch_ln_bwd(int64_t N, int E, const T* dya, const T* dyb, const T* xhat,
-                         const float* rstd, const float* gamma, T* du, T* dysum, hipStream_t s);
 template <class T>
 hipError_t launch_gelu(int64_t count, const T* g, T* u, hipStream_t s);
 // du <- du * GELU'(g), in place

@@ -219,68 +219,7 @@ hipError_t launch_linear_item_qkv(const Geo& g, const T* A, const float* w, cons
   return hipGetLastError();
 }
 
-// ============================================================================ reductions
-template <class T>
-__global__ __launch_bounds__(256) void k_wgrad(int64_t M, int Nj, int Ki,
-                                               const T* __restrict__ dY, int64_t ldy,
-                                               const T* __restrict__ X, int64_t ldx,
-                                               int64_t chunk, float* __restrict__ part) {
-  __shared__ float Ys[16][65];
-  __shared__ float Xs[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int j0 = blockIdx.x * 64, i0 = blockIdx.y * 64;
-  const int64_t mb = (int64_t)blockIdx.z * chunk;
-  const int64_t me = (mb + chunk < M) ? mb + chunk : M;
-  float acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.f;
-  for (int64_t m0 = mb; m0 < me; m0 += 16) {
-    for (int t = threadIdx.x; t < 1024; t += 256) {
-      int mm = t >> 6, jj = t & 63;
-      int64_t m = m0 + mm;
-      Ys[mm][jj] = (m < me && j0 + jj < Nj) ? ld(dY + m * ldy + j0 + jj) : 0.f;
-      Xs[mm][jj] = (m < me && i0 + jj < Ki) ? ld(X + m * ldx + i0 + jj) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mm = 0; mm < 16; ++mm) {
-      float a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a[q] = Ys[mm][ty + 16 * q];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = Xs[mm][tx + 16 * q];
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] = fmaf(a[p], b[q], acc[p][q]);
-    }
-    __syncthreads();
-  }
-  float* out = part + (int64_t)blockIdx.z * Nj * Ki;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int j = j0 + ty + 16 * p;
-    if (j >= Nj) continue;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      int i = i0 + tx + 16 * q;
-      if (i < Ki) out[(int64_t)j * Ki + i] = acc[p][q];
-    }
-  }
-}
-
-template <class T>
-hipError_t launch_wgrad(int64_t M, int Nj, int Ki, const T* dY, int64_t ldy, const T* X,
-                        int64_t ldx, int64_t chunk, float* partial, hipStream_t s) {
-  int64_t Z = (M + chunk - 1) / chunk;
-  if (Z < 1) Z = 1;
-  dim3 grid((unsigned)((Nj + 63) / 64), (unsigned)((Ki + 63) / 64), (unsigned)Z);
-  k_wgrad<T><<<grid, 256, 0, s>>>(M, Nj, Ki, dY, ldy, X, ldx, chunk, partial);
-  return hipGetLastError();
-}
-
+// ============================================================================ column sums
 template <class T>
 __global__ void k_colsum(int64_t M, int Nj, const T* __restrict__ A, int64_t lda,
                          const T* __restrict__ B, int64_t ldb, int64_t chunk,
@@ -308,117 +247,7 @@ hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B,
   return hipGetLastError();
 }
 
-__global__ void k_reduce_partials(int Z, int64_t count, const float* __restrict__ part,
-                                  float* __restrict__ grad, int accumulate) {
-  for (int64_t i = gtid(); i < count; i += gstride()) {
-    float acc = accumulate ? grad[i] : 0.f;
-    float sum = 0.f;
-    for (int z = 0; z < Z; ++z) sum += part[(int64_t)z * count + i];
-    grad[i] = acc + sum;
-  }
-}
-
-hipError_t launch_reduce_partials(int Z, int64_t count, const float* partial, float* grad,
-                                  int accumulate, hipStream_t s) {
-  k_reduce_partials<<<grid_for(count), TFM_BLOCK, 0, s>>>(Z, count, partial, grad, accumulate);
-  return hipGetLastError();
-}
-
-// ============================================================================ LayerNorm, GELU
-// One wave per cell; each lane holds up to 4 of the E <= 256 values.
-template <class T>
-__global__ __launch_bounds__(256) void k_add_ln(int64_t N, int E, const T* __restrict__ a,
-                                                const T* __restrict__ b,
-                                                const float* __restrict__ gamma,
-                                                const float* __restrict__ beta,
-                                                T* __restrict__ h, T* __restrict__ xhat,
-                                                float* __restrict__ rstd) {
-  const int lane = threadIdx.x & 63;
-  const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (cell >= N) return;
-  float u[4];
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int e = lane + 64 * i;
-    u[i] = 0.f;
-    if (e < E) {
-      u[i] = ld(a + cell * E + e) + (b ? ld(b + cell * E + e) : 0.f);
-      s += u[i];
-    }
-  }
-  const float mean = wave_sum(s) / E;
-  float v = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int e = lane + 64 * i;
-    if (e < E) v += (u[i] - mean) * (u[i] - mean);
-  }
-  const float rs = 1.0f / sqrtf(wave_sum(v) / E + 1e-5f);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int e = lane + 64 * i;
-    if (e < E) {
-      float x = (u[i] - mean) * rs;
-      st(xhat + cell * E + e, x);
-      st(h + cell * E + e, fmaf(gamma[e], x, beta[e]));
-    }
-  }
-  if (lane == 0) rstd[cell] = rs;
-}
-
-template <class T>
-hipError_t launch_add_ln(int64_t N, int E, const T* a, const T* b, const float* gamma,
-                         const float* beta, T* h, T* xhat, float* rstd, hipStream_t s) {
-  if (N <= 0) return hipSuccess;
-  k_add_ln<T><<<(unsigned)((N + 3) / 4), 256, 0, s>>>(N, E, a, b, gamma, beta, h, xhat, rstd);
-  return hipGetLastError();
-}
-
-template <class T>
-__global__ __launch_bounds__(256) void k_ln_bwd(int64_t N, int E, const T* __restrict__ dya,
-                                                const T* __restrict__ dyb,
-                                                const T* __restrict__ xhat,
-                                                const float* __restrict__ rstd,
-                                                const float* __restrict__ gamma,
-                                                T* __restrict__ du, T* __restrict__ dysum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t cell = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (cell >= N) return;
-  float gv[4], xv[4];
-  float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int e = lane + 64 * i;
-    gv[i] = 0.f;
-    xv[i] = 0.f;
-    if (e < E) {
-      float dy = ld(dya + cell * E + e) + (dyb ? ld(dyb + cell * E + e) : 0.f);
-      if (dysum) st(dysum + cell * E + e, dy);
-      gv[i] = dy * gamma[e];
-      xv[i] = ld(xhat + cell * E + e);
-      s1 += gv[i];
-      s2 += gv[i] * xv[i];
-    }
-  }
-  const float m1 = wave_sum(s1) / E, m2 = wave_sum(s2) / E;
-  const float rs = rstd[cell];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int e = lane + 64 * i;
-    if (e < E) st(du + cell * E + e, rs * (gv[i] - m1 - xv[i] * m2));
-  }
-}
-
-template <class T>
-hipError_t launch_ln_bwd(int64_t N, int E, const T* dya, const T* dyb, const T* xhat,
-                         const float* rstd, const float* gamma, T* du, T* dysum, hipStream_t s) {
-  if (N <= 0) return hipSuccess;
-  k_ln_bwd<T><<<(unsigned)((N + 3) / 4), 256, 0, s>>>(N, E, dya, dyb, xhat, rstd, gamma, du,
-                                                       dysum);
-  return hipGetLastError();
-}
-
+// ============================================================================ GELU
 template <class T>
 __global__ void k_gelu(int64_t n, const T* __restrict__ g, T* __restrict__ u) {
   for (int64_t i = gtid(); i < n; i += gstride()) {
@@ -829,14 +658,8 @@ hipError_t launch_item_dqkv_to_cells(const Geo& g, const T* dq, const T* dk, con
                                           int64_t, hipStream_t);                             \
   template hipError_t launch_linear_item_qkv<T>(const Geo&, const T*, const float*,         \
                                                 const float*, T*, T*, T*, hipStream_t);      \
-  template hipError_t launch_wgrad<T>(int64_t, int, int, const T*, int64_t, const T*,        \
-                                      int64_t, int64_t, float*, hipStream_t);                \
   template hipError_t launch_colsum<T>(int64_t, int, const T*, int64_t, const T*, int64_t,   \
                                        int64_t, float*, hipStream_t);                        \
-  template hipError_t launch_add_ln<T>(int64_t, int, const T*, const T*, const float*,      \
-                                       const float*, T*, T*, float*, hipStream_t);           \
-  template hipError_t launch_ln_bwd<T>(int64_t, int, const T*, const T*, const T*,          \
-                                       const float*, const float*, T*, T*, hipStream_t);     \
   template hipError_t launch_gelu<T>(int64_t, const T*, T*, hipStream_t);                   \
   template hipError_t launch_gelu_bwd<T>(int64_t, const T*, T*, hipStream_t);               \
   template hipError_t launch_feat_attn_fwd_simple<T>(const Geo&, const T*, T*, float*,      \

@@ -17,8 +17,10 @@
 
 #include "kernels.h"
 #include "attn.h"
+#include "f32.h"
 #include "fast.h"
 #include "prof.h"
+#include "reduce.h"
 #include "static_scratch.h"
 
 namespace {
@@ -36,7 +38,6 @@ int fail(int code, const char* fmt, ...) {
 }
 
 constexpr size_t kAlign = 256;
-constexpr int64_t kChunk = 8192;  // rows per partial sum of the parameter-gradient reductions
 constexpr int64_t kMaxCells = int64_t(1) << 26;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -92,6 +93,12 @@ int check_dims(const tfm_dims* p, Dims& d) {
     if (!std::isfinite(d.decay)) return fail(TFM_ERR_DIMS, "decay must be finite");
   }
   return TFM_OK;
+}
+
+// Dims of the bfloat16 matrix-core path.
+bool fast_eligible(const Dims& d) {
+  return d.dtype == TFM_BF16 && (d.E == 64 || d.E == 128 || d.E == 192 || d.E == 256) &&
+         d.H % d.E == 0;
 }
 
 // ---- parameter offsets (floats) -------------------------------------------------------------
@@ -224,10 +231,10 @@ size_t saved_total(const Dims& d) {
 
 struct WsLayout {
   MetaOff meta;
-  size_t xc, ta, tb, tc, td, te, tf, th1, th2, tq, tk, tv, tqkv, D, part, cpart, cpart2;
-  size_t fast;  // region owned by the MFMA path
+  size_t xc, ta, tb, tc, td, te, tf, th1, th2, tq, tk, tv, tqkv, D;
+  size_t part, lnpart;  // float32 mode: weight / bias partials, norm partials
+  size_t fast;          // region owned by the MFMA path
   size_t total;
-  int64_t Z;    // partial-sum chunks
 };
 
 WsLayout ws_layout(const Dims& d) {
@@ -249,13 +256,9 @@ WsLayout ws_layout(const Dims& d) {
   L.tv = a.take(N * E * t);
   L.tqkv = a.take(N * 3 * E * t);
   L.D = a.take(N * d.heads * 4);
-  L.Z = (d.Nmax + kChunk - 1) / kChunk;
-  size_t maxw = (size_t)3 * E * E;
-  if ((size_t)d.H * E > maxw) maxw = (size_t)d.H * E;
-  L.part = a.take((size_t)L.Z * maxw * 4);
-  size_t maxc = 3 * E > (size_t)d.H ? 3 * E : (size_t)d.H;
-  L.cpart = a.take((size_t)L.Z * maxc * 4);
-  L.cpart2 = a.take((size_t)L.Z * maxc * 4);
+  const bool f32 = !fast_eligible(d);
+  L.part = a.take(f32 ? tfm::f32_wpart_floats(d.Nmax, d.E, d.H) * 4 : 0);
+  L.lnpart = a.take(f32 ? tfm::f32_lnpart_floats(d.Nmax, d.E) * 4 : 0);
   L.fast = a.take(tfm::fast_workspace_bytes(d.B, d.R, d.S, d.E, d.heads, d.H,
                                             d.dtype == TFM_BF16));
   L.total = a.off;
@@ -313,6 +316,13 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
     tfm::prof_begin(name, s);        \
     HIPCHK(__VA_ARGS__);             \
     tfm::prof_end(s);                \
+  } while (0)
+
+// Zeros at the inactive cells of a native output; nothing to launch when every cell is active.
+#define ZERO_INACTIVE(g, out)                                                            \
+  do {                                                                                   \
+    if ((g).NC < (g).B * (g).S)                                                          \
+      STEP("zero_inactive/hbm", tfm::launch_zero_inactive(g, out, sizeof(*(out)), s));   \
   } while (0)
 
 #define STEP_ERR(...)                \
@@ -409,60 +419,30 @@ int fwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, T
   T* h2 = (T*)(sv + S.h2);
   T* oi = (T*)(sv + S.oi);
   T* gp = (T*)(sv + S.g);
-  T* yc = (T*)(ws + W.tb);
   STEP("gather/hbm", launch_gather<T>(g, X, xc, s));
   STEP("feat_qkv/valu", launch_linear<T, T>(N, 3 * E, E, xc, E, prm + o.Wqkv_f, E, 1, prm + o.bqkv_f, qkvf,
                              3 * E, s));
   STEP("feat_attn_fwd/valu", launch_feat_attn_fwd_simple<T>(g, qkvf, of, (float*)(sv + S.lsef), s));
   STEP("feat_out/valu", launch_linear<T, T>(N, E, E, of, E, prm + o.Wo_f, E, 1, prm + o.bo_f, ta, E, s));
-  STEP("ln1/hbm", launch_add_ln<T>(N, E, xc, ta, prm + o.g1, prm + o.be1, h1, (T*)(sv + S.xh1),
-                          (float*)(sv + S.rs1), s));
+  STEP("ln1/hbm", launch_f32_add_ln<T>(g, X, ROWS_NATIVE, ta, prm + o.g1, prm + o.be1, h1,
+                                       ROWS_COMPACT, (T*)(sv + S.xh1), (float*)(sv + S.rs1), s));
   STEP("item_qkv/valu", launch_linear_item_qkv<T>(g, h1, prm + o.Wqkv_i, prm + o.bqkv_i, (T*)(sv + S.qi),
                                    (T*)(sv + S.ki), (T*)(sv + S.vi), s));
   STEP("item_attn_fwd/valu", launch_item_attn_fwd_simple<T>(g, (T*)(sv + S.qi), (T*)(sv + S.ki), (T*)(sv + S.vi),
                                         oi, (float*)(sv + S.lsei), s));
   STEP("item_out/valu", launch_linear<T, T>(N, E, E, oi, E, prm + o.Wo_i, E, 1, prm + o.bo_i, ta, E, s));
-  STEP("ln2/hbm", launch_add_ln<T>(N, E, h1, ta, prm + o.g2, prm + o.be2, h2, (T*)(sv + S.xh2),
-                          (float*)(sv + S.rs2), s));
+  STEP("ln2/hbm", launch_f32_add_ln<T>(g, h1, ROWS_COMPACT, ta, prm + o.g2, prm + o.be2, h2,
+                                       ROWS_COMPACT, (T*)(sv + S.xh2), (float*)(sv + S.rs2), s));
   STEP("mlp_up/valu", launch_linear<T, T>(N, H, E, h2, E, prm + o.W1, E, 1, prm + o.b1, gp, H, s));
   STEP("gelu/hbm", launch_gelu<T>(N * H, gp, tu, s));
   STEP("mlp_down/valu", launch_linear<T, T>(N, E, H, tu, H, prm + o.W2, H, 1, prm + o.b2, ta, E, s));
-  STEP("ln3/hbm", launch_add_ln<T>(N, E, h2, ta, prm + o.g3, prm + o.be3, yc, (T*)(sv + S.xh3),
-                          (float*)(sv + S.rs3), s));
-  STEP("scatter/hbm", launch_scatter<T>(g, yc, (const T*)nullptr, Y, s));
+  STEP("ln3/hbm", launch_f32_add_ln<T>(g, h2, ROWS_COMPACT, ta, prm + o.g3, prm + o.be3, Y,
+                                       ROWS_NATIVE, (T*)(sv + S.xh3), (float*)(sv + S.rs3), s));
+  ZERO_INACTIVE(g, Y);
   return TFM_OK;
 }
 
 // ---- backward --------------------------------------------------------------------------------
-template <class T>
-struct GradSink {
-  const WsLayout& W;
-  char* ws;
-  float* grads;
-  int accumulate;
-  int64_t M;
-  hipStream_t s;
-  // dW[j][i] = sum_m dY[m][j] X[m][i]
-  int wgrad(const T* dY, int Nj, const T* X, int Ki, size_t off) {
-    float* part = (float*)(ws + W.part);
-    int64_t Z = (M + kChunk - 1) / kChunk;
-    if (Z < 1) Z = 1;
-    STEP("wgrad/valu", tfm::launch_wgrad<T>(M, Nj, Ki, dY, Nj, X, Ki, kChunk, part, s));
-    STEP("reduce/hbm", tfm::launch_reduce_partials((int)Z, (int64_t)Nj * Ki, part, grads + off,
-                                               accumulate, s));
-    return TFM_OK;
-  }
-  // g[j] = sum_m A[m][j] (* B[m][j])
-  int colsum(const T* A, const T* B, int Nj, size_t off) {
-    float* part = (float*)(ws + W.cpart);
-    int64_t Z = (M + kChunk - 1) / kChunk;
-    if (Z < 1) Z = 1;
-    STEP("colsum/hbm", tfm::launch_colsum<T>(M, Nj, A, Nj, B, Nj, kChunk, part, s));
-    STEP("reduce/hbm", tfm::launch_reduce_partials((int)Z, Nj, part, grads + off, accumulate, s));
-    return TFM_OK;
-  }
-};
-
 #define CHK(...)                 \
   do {                           \
     int c_ = (__VA_ARGS__);      \
@@ -477,12 +457,8 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   const POff o = param_offsets(d.E, d.H);
   const int E = d.E, H = d.H;
   const int64_t N = g.N;
-  GradSink<T> G{W, ws, grads, accumulate, N, s};
-  T* xc = (T*)(ws + W.xc);
-  T* dyc = (T*)(ws + W.ta);
   T* dz3 = (T*)(ws + W.tb);
   T* tmp = (T*)(ws + W.tc);
-  T* dh = (T*)(ws + W.td);
   T* dz2 = (T*)(ws + W.te);
   T* dz1 = (T*)(ws + W.tf);
   T* du = (T*)(ws + W.th1);
@@ -491,32 +467,25 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   const T* h1 = (const T*)(sv + S.h1);
   const T* h2 = (const T*)(sv + S.h2);
   const T* gp = (const T*)(sv + S.g);
-  STEP("gather/hbm", launch_gather<T>(g, dY, dyc, s));
-  STEP("gather/hbm", launch_gather<T>(g, X, xc, s));
-  // LN3
-  STEP("ln3_bwd/hbm", launch_ln_bwd<T>(N, E, dyc, (const T*)nullptr, (const T*)(sv + S.xh3),
-                          (const float*)(sv + S.rs3), prm + o.g3, dz3, (T*)nullptr, s));
-  CHK(G.colsum(dyc, (const T*)(sv + S.xh3), E, o.g3));
-  CHK(G.colsum(dyc, (const T*)nullptr, E, o.be3));
+  const int lnr = f32_ln_rows(N);
+  float* lnp[3];
+  for (int i = 0; i < 3; ++i) lnp[i] = (float*)(ws + W.lnpart) + (size_t)i * lnr * 2 * E;
+  // LN3, from the native dY
+  STEP("ln3_bwd/hbm", launch_f32_ln_bwd<T>(g, dY, ROWS_NATIVE, nullptr, (const T*)(sv + S.xh3),
+                                           (const float*)(sv + S.rs3), prm + o.g3, dz3, lnp[2],
+                                           s));
   // MLP
   STEP("mlp_down_dx/valu", launch_linear<T, T>(N, H, E, dz3, E, prm + o.W2, 1, H, nullptr, du, H, s));
   STEP("gelu/hbm", launch_gelu<T>(N * H, gp, uu, s));
-  CHK(G.wgrad(dz3, E, uu, H, o.W2));
-  CHK(G.colsum(dz3, (const T*)nullptr, E, o.b2));
   STEP("gelu_bwd/hbm", launch_gelu_bwd<T>(N * H, gp, du, s));
-  CHK(G.wgrad(du, H, h2, E, o.W1));
-  CHK(G.colsum(du, (const T*)nullptr, H, o.b1));
   STEP("mlp_up_dx/valu", launch_linear<T, T>(N, E, H, du, H, prm + o.W1, 1, E, nullptr, tmp, E, s));
   // LN2
-  STEP("ln2_bwd/hbm", launch_ln_bwd<T>(N, E, dz3, tmp, (const T*)(sv + S.xh2), (const float*)(sv + S.rs2),
-                          prm + o.g2, dz2, dh, s));
-  CHK(G.colsum(dh, (const T*)(sv + S.xh2), E, o.g2));
-  CHK(G.colsum(dh, (const T*)nullptr, E, o.be2));
+  STEP("ln2_bwd/hbm", launch_f32_ln_bwd<T>(g, dz3, ROWS_COMPACT, tmp, (const T*)(sv + S.xh2),
+                                           (const float*)(sv + S.rs2), prm + o.g2, dz2, lnp[1],
+                                           s));
   // item attention
   T* doi = (T*)(ws + W.tc);
   STEP("item_out_dx/valu", launch_linear<T, T>(N, E, E, dz2, E, prm + o.Wo_i, 1, E, nullptr, doi, E, s));
-  CHK(G.wgrad(dz2, E, (const T*)(sv + S.oi), E, o.Wo_i));
-  CHK(G.colsum(dz2, (const T*)nullptr, E, o.bo_i));
   T* dq = (T*)(ws + W.tq);
   T* dk = (T*)(ws + W.tk);
   T* dv = (T*)(ws + W.tv);
@@ -525,36 +494,51 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
                                         (const float*)(sv + S.lsei), (float*)(ws + W.D), dq, dk,
                                         dv, s));
   STEP("item_dqkv_cells/hbm", launch_item_dqkv_to_cells<T>(g, dq, dk, dv, dqkv, s));
-  CHK(G.wgrad(dqkv, 3 * E, h1, E, o.Wqkv_i));
-  CHK(G.colsum(dqkv, (const T*)nullptr, 3 * E, o.bqkv_i));
   STEP("item_qkv_dx/valu", launch_linear<T, T>(N, E, 3 * E, dqkv, 3 * E, prm + o.Wqkv_i, 1, E, nullptr, tmp, E,
                              s));
   // LN1
-  STEP("ln1_bwd/hbm", launch_ln_bwd<T>(N, E, dz2, tmp, (const T*)(sv + S.xh1), (const float*)(sv + S.rs1),
-                          prm + o.g1, dz1, dh, s));
-  CHK(G.colsum(dh, (const T*)(sv + S.xh1), E, o.g1));
-  CHK(G.colsum(dh, (const T*)nullptr, E, o.be1));
+  STEP("ln1_bwd/hbm", launch_f32_ln_bwd<T>(g, dz2, ROWS_COMPACT, tmp, (const T*)(sv + S.xh1),
+                                           (const float*)(sv + S.rs1), prm + o.g1, dz1, lnp[0],
+                                           s));
   // feature attention
   T* dof = (T*)(ws + W.tc);
   STEP("feat_out_dx/valu", launch_linear<T, T>(N, E, E, dz1, E, prm + o.Wo_f, 1, E, nullptr, dof, E, s));
-  CHK(G.wgrad(dz1, E, (const T*)(sv + S.of), E, o.Wo_f));
-  CHK(G.colsum(dz1, (const T*)nullptr, E, o.bo_f));
   STEP("feat_attn_bwd/valu", launch_feat_attn_bwd_simple<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
-  CHK(G.wgrad(dqkv, 3 * E, xc, E, o.Wqkv_f));
-  CHK(G.colsum(dqkv, (const T*)nullptr, 3 * E, o.bqkv_f));
   STEP("feat_qkv_dx/valu", launch_linear<T, T>(N, E, 3 * E, dqkv, 3 * E, prm + o.Wqkv_f, 1, E, nullptr, tmp, E,
                              s));
   STEP("scatter/hbm", launch_scatter<T>(g, dz1, tmp, dX, s));
+  // every weight and bias gradient in one launch (their operands are all still there), and the
+  // sums of all partials in another
+  const F32Split sp = f32_split(N, E, H);
+  F32WgradArgs<T> wa{};
+  ReduceList rl;
+  wa.g = g;
+  float* part = (float*)(ws + W.part);
+  auto wgrad = [&](const T* Y, const T* Y2, const T* Y3, int Nj, const T* Xm, int Kj, int xmode,
+                   size_t offW, size_t offb) {
+    F32WgradJob<T>& j = wa.j[wa.n++];
+    j = F32WgradJob<T>{Y, Y2, Y3, Xm, part, part + (size_t)sp.Z * Nj * Kj, Nj, Kj,
+                       Y2 ? ROWS_ITEM_HM : ROWS_COMPACT, xmode, 0, 0};
+    part = j.bpart + (size_t)sp.Z * Nj;
+    rl.add(j.part, (int64_t)Nj * Kj, sp.Z, (int64_t)Nj * Kj, grads + offW);
+    rl.add(j.bpart, Nj, sp.Z, Nj, grads + offb);
+  };
+  wgrad(dqkv, nullptr, nullptr, 3 * E, X, E, ROWS_NATIVE, o.Wqkv_f, o.bqkv_f);
+  wgrad(dz1, nullptr, nullptr, E, (const T*)(sv + S.of), E, ROWS_COMPACT, o.Wo_f, o.bo_f);
+  wgrad(dq, dk, dv, 3 * E, h1, E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i);
+  wgrad(dz2, nullptr, nullptr, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i);
+  wgrad(du, nullptr, nullptr, H, h2, E, ROWS_COMPACT, o.W1, o.b1);
+  wgrad(dz3, nullptr, nullptr, E, uu, H, ROWS_COMPACT, o.W2, o.b2);
+  // norm scales and shifts are adjacent in the packed order: one sum over 2E columns each
+  const size_t og[3] = {o.g1, o.g2, o.g3};
+  for (int i = 0; i < 3; ++i) rl.add(lnp[i], 2 * E, lnr, 2 * E, grads + og[i]);
+  STEP("wgrad/mfma", launch_f32_wgrads<T>(wa, sp, s));
+  STEP("reduce/hbm", launch_reduce_list(rl, accumulate, s));
   return TFM_OK;
 }
 
 // ---- MFMA path (bfloat16) -------------------------------------------------------------------
-bool fast_eligible(const Dims& d) {
-  return d.dtype == TFM_BF16 && (d.E == 64 || d.E == 128 || d.E == 192 || d.E == 256) &&
-         d.H % d.E == 0;
-}
-
 struct FastWs {
   tfm::bf16* w;
   tfm::bf16* wt;
@@ -678,7 +662,7 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
     m.xh2 = b.save ? b.h2 : nullptr; m.rs2 = b.save ? b.rs2 : nullptr;
     m.y = Y; m.xh3 = b.save ? b.xh3 : nullptr; m.rs3 = b.save ? b.rs3 : nullptr; m.g = g;
     STEP("mlp_fused/mfma", launch_mlp_fwd(m, s));
-    STEP("zero_inactive/hbm", launch_zero_inactive(g, Y, s));
+    ZERO_INACTIVE(g, Y);
     return TFM_OK;
   }
   // x-hat2 of H2 = LN2(H1 + O_i Wo_i^T + bo_i), H1 = g1 x-hat1 + be1
@@ -700,7 +684,7 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
   a.gamma = prm + o.g3; a.beta = prm + o.be3;
   a.out = Y; a.omode = ROWS_NATIVE; a.xhat = b.xh3; a.rstd = b.rs3;
   STEP("mlp_down_ln3/mfma", launch_gemm(a, s));
-  STEP("zero_inactive/hbm", launch_zero_inactive(g, Y, s));
+  ZERO_INACTIVE(g, Y);
   return TFM_OK;
 }
 
@@ -851,7 +835,7 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   a = gemm_base(g, N, E, 3 * E, EPI_DX);
   a.A = dqkv; a.lda = 3 * E; a.Bt = f.wt + f.wo.qkv_f; a.resid = dz1; a.out = dX;
   STEP("feat_qkv_dx/mfma", launch_gemm(a, s));
-  STEP("zero_inactive/hbm", launch_zero_inactive(g, dX, s));
+  ZERO_INACTIVE(g, dX);
   return TFM_OK;
 }
 
@@ -911,7 +895,7 @@ int fwd_pre(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* p
   a.A = b.u; a.lda = H; a.Bt = f.w + f.wo.w2; a.bias = prm + o.b2; a.resid = b.h2;
   a.out = Y;
   STEP("mlp_down_res/mfma", launch_gemm(a, s));
-  STEP("zero_inactive/hbm", launch_zero_inactive(g, Y, s));
+  ZERO_INACTIVE(g, Y);
   return TFM_OK;
 }
 
@@ -995,7 +979,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   a.eps = kRmsEps; a.oscale = d.decay; a.omode = ROWS_NATIVE; a.out = dX; a.part = f.lnpart;
   STEP("feat_qkv_dx_rms1/mfma", launch_gemm(a, s));
   STEP("reduce/hbm", launch_reduce_z(tiles, E, E, f.lnpart, grads + o.g1, accumulate, s));
-  STEP("zero_inactive/hbm", launch_zero_inactive(g, dX, s));
+  ZERO_INACTIVE(g, dX);
   return TFM_OK;
 }
 

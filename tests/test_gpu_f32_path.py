@@ -1,0 +1,39 @@
+"""GPU parity of the float32-arithmetic path (float32 storage, and bfloat16 shapes outside the
+bf16 matrix-core envelope) at the edges of its tiles: widths that are not multiples of the 64-wide
+product tiles, fewer cells than one tile or one chunk of the weight gradients, more cells than
+the chip has chunks for, train prefixes of 1 and R, inactive columns, every head width.  Against
+the float64 oracle with the tolerances of the parity tests (float32 arithmetic: 1e-4 of each
+tensor's largest value; bfloat16 storage: 2e-2)."""
+
+import pytest
+
+from paper_2606_03681_amd import workloads as wl
+
+from _harness import compare_all, gpu_stack, oracle_stack
+
+pytestmark = pytest.mark.gpu
+
+# dtype, B, R, n_train, C, active, E, heads, H
+CASES = [
+    ("f32", 1, 1, 1, 0, None, 32, 2, 32),            # one cell
+    ("f32", 1, 5, 3, 1, None, 32, 1, 32),            # fewer cells than any tile
+    ("f32", 3, 33, (1, 33), 4, (0, 4), 96, 3, 160),  # widths between the 64-wide tiles
+    ("f32", 2, 65, (1, 65), 6, (0, 6), 160, 10, 96),  # head width 16, rows one past a tile
+    ("f32", 2, 40, 17, 3, None, 224, 7, 352),
+    ("f32", 1, 130, 129, 2, None, 256, 4, 1024),     # the widest block, head width 64
+    ("f32", 3, 900, (1, 900), 15, (3, 15), 32, 1, 64),  # several cells per chunk and tile
+    ("f32", 4, 20, (1, 20), 150, (130, 150), 32, 2, 32),  # rows of more than 128 cells
+    ("bf16", 3, 70, (1, 70), 5, (0, 5), 96, 3, 96),  # bfloat16 widths without a bf16 path
+    ("bf16", 2, 31, 30, 3, None, 192, 6, 96),        # H not a multiple of E
+]
+
+
+@pytest.mark.parametrize("dtype,B,R,n,C,active,E,heads,H", CASES)
+def test_f32_path_edges(monkeypatch, dtype, B, R, n, C, active, E, heads, H):
+    cfg = dict(name="edge", dtype=dtype, B=B, R=R, n_train=n, C=C, E=E, heads=heads, H=H,
+               layers=1, cells="normal", weights="xavier_bias")
+    if active:
+        cfg.update(active=active, mask="random")
+    monkeypatch.setitem(wl.TEST_CONFIGS, "edge", cfg)
+    w = wl.make_workload("edge")
+    compare_all(w, gpu_stack(w), oracle_stack(w))
