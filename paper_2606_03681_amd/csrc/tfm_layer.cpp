@@ -166,9 +166,9 @@ SavedLayout saved_layout(const Dims& d) {
   L.qkvf = a.take(N * 3 * E * t);
   L.of = a.take(N * E * t);
   L.lsef = a.take(N * d.heads * 4);
-  // the float32 path keeps H and x-hat of LN1 and LN2; the MFMA path keeps x-hat only, in the
-  // H slots (its LN1 / LN2 affines are folded into the consumers)
-  const size_t xhn = d.dtype == TFM_F32 ? N * E * t : 0;
+  // the float32-arithmetic path (either storage type) keeps H and x-hat of LN1 and LN2; the MFMA
+  // path keeps x-hat only, in the H slots (its LN1 / LN2 affines are folded into the consumers)
+  const size_t xhn = fast_eligible(d) ? 0 : N * E * t;
   L.h1 = a.take(N * E * t);
   L.xh1 = a.take(xhn);
   L.rs1 = a.take(N * 4);
