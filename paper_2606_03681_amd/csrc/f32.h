@@ -56,4 +56,26 @@ hipError_t launch_f32_ln_bwd(const Geo& g, const T* dya, int amode, const T* dyb
                              const float* rstd, const float* gamma, T* du, float* part,
                              hipStream_t s);
 
+// out[m][n] = sum_k A[m][k] W(n, k) with an epilogue; W(n, k) = W[n * K + k], or W[k * N + n] with
+// wt (the transposed product of a backward pass).
+enum {
+  F32_BIAS = 0,      // out = acc (+ bias), compact
+  F32_GELU = 1,      // out = acc + bias, out2 = GELU(out)
+  F32_GELU_BWD = 2,  // out = acc * GELU'(aux)
+  F32_ITEM_QKV = 3,  // acc + bias head-major into out, out2, out3 (K and V at train rows only)
+  F32_DX = 4         // out (native rows) = acc + aux
+};
+template <class T>
+struct F32LinArgs {
+  int64_t M;
+  int32_t N, K, amode, wt, epi;
+  const T *A, *A2, *A3;  // rows of K values: compact, native, or ROWS_ITEM_HM (dQ, dK, dV)
+  const float *W, *bias;
+  const T* aux;          // compact [M][N]
+  T *out, *out2, *out3;
+  Geo g;
+};
+template <class T>
+hipError_t launch_f32_linear(const F32LinArgs<T>& a, hipStream_t s);
+
 }  // namespace tfm

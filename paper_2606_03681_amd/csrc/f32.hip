@@ -259,6 +259,176 @@ __global__ __launch_bounds__(256) void k_f32_ln_bwd(Geo g, const T* __restrict__
     part[(int64_t)blockIdx.x * 2 * E + i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
 }
 
+// ---- linear layers ----------------------------------------------------------------------------
+// 64 cells x 64 features a workgroup, four waves of 32 x 32, 32 values of k a stage through two
+// LDS buffers, the next stage's rows in flight.  The weights are the A operand, so a lane ends
+// with 4 consecutive features of one cell and the epilogues move 16 bytes per lane.  The 16 x 4
+// products of a stage take k = 4g + j from lane group g in product j, so a lane reads 4
+// consecutive k of its row at once; LDS rows of 36 floats keep those 16-byte reads apart.  A
+// transposed weight is staged as it lies ([k][n], rows of 68 floats) and read one float a lane.
+constexpr int LK = 32, LSR = 36, LST = 68;
+
+__device__ __forceinline__ float gelu_exact(float x) {
+  return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
+}
+__device__ __forceinline__ float gelu_exact_grad(float x) {
+  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  return cdf + x * 0.39894228040143268f * expf(-0.5f * x * x);
+}
+
+template <class T, int AM, bool WT, int EPI>
+__global__ __launch_bounds__(256) void k_f32_linear(F32LinArgs<T> a) {
+  constexpr int WSZ = WT ? LK * LST : 64 * LSR;
+  __shared__ __attribute__((aligned(16))) float As[2][64 * LSR];
+  __shared__ __attribute__((aligned(16))) float Ws[2][WSZ];
+  const Geo& g = a.g;
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+  const int lg = lane >> 4, c = lane & 15;
+  const int ntn = (a.N + 63) / 64;
+  const int64_t m0 = (int64_t)(blockIdx.x / ntn) * 64;
+  const int n0 = (int)(blockIdx.x % ntn) * 64;
+  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+  // staging of A (and of W as stored): 4 values from 4 sc of rows sr, sr + 32
+  const int sc = tid & 7, sr = tid >> 3;
+  int64_t arow[2];
+  uint32_t acol[2];
+  int ar[2], antr[2];
+  bool aok[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t m = m0 + sr + 32 * i;
+    aok[i] = m < a.M;
+    arow[i] = aok[i] ? m * a.K : 0;
+    acol[i] = 0;
+    ar[i] = antr[i] = 0;
+    if (AM == ROWS_NATIVE && aok[i]) arow[i] = native32(g, m) * a.K;
+    if (AM == ROWS_ITEM_HM && aok[i]) {
+      acol[i] = (uint32_t)m / (uint32_t)g.R;
+      ar[i] = (int)((uint32_t)m - acol[i] * (uint32_t)g.R);
+      antr[i] = g.col_ntr[acol[i]];
+    }
+  }
+  float4 av[2], wv[2];
+  auto gload = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = k0 + 4 * sc;
+      av[i] = zf4();
+      if (AM == ROWS_ITEM_HM) {
+        const int part = k / g.E, within = k - part * g.E;
+        const int head = within / g.d, j = within - head * g.d;
+        if (aok[i] && (part == 0 || ar[i] < antr[i]))
+          av[i] = ld4((part == 0 ? a.A : (part == 1 ? a.A2 : a.A3)) +
+                      (((int64_t)acol[i] * g.heads + head) * g.R + ar[i]) * g.d + j);
+      } else if (aok[i]) {
+        av[i] = ld4(a.A + arow[i] + k);
+      }
+      wv[i] = zf4();
+      if (WT) {  // rows k = tid / 16 (+ 16), features 4 (tid % 16)
+        const int kk = k0 + (tid >> 4) + 16 * i, n = n0 + 4 * (tid & 15);
+        if (n < a.N) wv[i] = ld4(a.W + (int64_t)kk * a.N + n);
+      } else {
+        const int n = n0 + sr + 32 * i;
+        if (n < a.N) wv[i] = ld4(a.W + (int64_t)n * a.K + k);
+      }
+    }
+  };
+  auto sstore = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      st4(&As[b][(sr + 32 * i) * LSR + 4 * sc], av[i]);
+      if (WT) st4(&Ws[b][((tid >> 4) + 16 * i) * LST + 4 * (tid & 15)], wv[i]);
+      else st4(&Ws[b][(sr + 32 * i) * LSR + 4 * sc], wv[i]);
+    }
+  };
+  f32x4 acc[2][2];  // [feature block][cell block]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = zero4();
+  gload(0);
+  sstore(0);
+  __syncthreads();
+  int b = 0;
+  for (int k0 = 0; k0 < a.K; k0 += LK, b ^= 1) {
+    const bool more = k0 + LK < a.K;
+    if (more) gload(k0 + LK);
+#pragma unroll
+    for (int q = 0; q < LK / 16; ++q) {
+      float4 xf[2];
+      float wf[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        xf[i] = ld4(&As[b][(wm + 16 * i + c) * LSR + 16 * q + 4 * lg]);
+        if (WT) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            wf[i][j] = Ws[b][(16 * q + 4 * lg + j) * LST + wn + 16 * i + c];
+        } else {
+          const float4 t = ld4(&Ws[b][(wn + 16 * i + c) * LSR + 16 * q + 4 * lg]);
+          wf[i][0] = t.x; wf[i][1] = t.y; wf[i][2] = t.z; wf[i][3] = t.w;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            const float xj = j == 0 ? xf[x].x : (j == 1 ? xf[x].y : (j == 2 ? xf[x].z : xf[x].w));
+            acc[i][x] = mfma32(wf[i][j], xj, acc[i][x]);
+          }
+    }
+    if (more) sstore(b ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int64_t m = m0 + wm + 16 * x + c;
+    if (m >= a.M) continue;
+    uint32_t col = 0;
+    int r = 0, ntr = 0;
+    int64_t nat = 0;
+    if (EPI == F32_ITEM_QKV) {
+      col = (uint32_t)m / (uint32_t)g.R;
+      r = (int)((uint32_t)m - col * (uint32_t)g.R);
+      ntr = g.col_ntr[col];
+    }
+    if (EPI == F32_DX) nat = native32(g, m);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int n = n0 + wn + 16 * i + 4 * lg;
+      if (n >= a.N) continue;
+      float4 v = make_float4(acc[i][x][0], acc[i][x][1], acc[i][x][2], acc[i][x][3]);
+      if (EPI != F32_GELU_BWD && EPI != F32_DX && a.bias) {
+        const float4 bb = ld4(a.bias + n);
+        v = make_float4(v.x + bb.x, v.y + bb.y, v.z + bb.z, v.w + bb.w);
+      }
+      if (EPI == F32_BIAS) {
+        st4(a.out + m * a.N + n, v);
+      } else if (EPI == F32_GELU) {
+        st4(a.out + m * a.N + n, v);
+        st4(a.out2 + m * a.N + n, make_float4(gelu_exact(v.x), gelu_exact(v.y), gelu_exact(v.z),
+                                              gelu_exact(v.w)));
+      } else if (EPI == F32_GELU_BWD) {
+        const float4 p = ld4(a.aux + m * a.N + n);
+        st4(a.out + m * a.N + n,
+            make_float4(v.x * gelu_exact_grad(p.x), v.y * gelu_exact_grad(p.y),
+                        v.z * gelu_exact_grad(p.z), v.w * gelu_exact_grad(p.w)));
+      } else if (EPI == F32_ITEM_QKV) {
+        const int part = n / g.E, within = n - part * g.E;
+        const int head = within / g.d, j = within - head * g.d;
+        if (part > 0 && r >= ntr) continue;
+        T* base = part == 0 ? a.out : (part == 1 ? a.out2 : a.out3);
+        st4(base + (((int64_t)col * g.heads + head) * g.R + r) * g.d + j, v);
+      } else {
+        const float4 p = ld4(a.aux + m * a.N + n);
+        st4(a.out + nat * a.N + n, make_float4(v.x + p.x, v.y + p.y, v.z + p.z, v.w + p.w));
+      }
+    }
+  }
+}
+
 int f32_tiles(int N, int K) { return ((N + 63) / 64) * ((K + 63) / 64); }
 
 }  // namespace
@@ -327,8 +497,31 @@ hipError_t launch_f32_ln_bwd(const Geo& g, const T* dya, int amode, const T* dyb
   return hipGetLastError();
 }
 
+template <class T>
+hipError_t launch_f32_linear(const F32LinArgs<T>& a, hipStream_t s) {
+  if (a.M <= 0) return hipSuccess;
+  if (a.K % LK || a.N % 16) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)((a.M + 63) / 64 * ((a.N + 63) / 64));
+#define RUN(AM, WT, EPI) k_f32_linear<T, AM, WT, EPI><<<grid, 256, 0, s>>>(a)
+  const int form = (a.wt ? 100 : 0) + a.amode * 10 + a.epi;
+  switch (form) {
+    case ROWS_NATIVE * 10 + F32_BIAS: RUN(ROWS_NATIVE, false, F32_BIAS); break;
+    case ROWS_COMPACT * 10 + F32_BIAS: RUN(ROWS_COMPACT, false, F32_BIAS); break;
+    case ROWS_COMPACT * 10 + F32_GELU: RUN(ROWS_COMPACT, false, F32_GELU); break;
+    case ROWS_COMPACT * 10 + F32_ITEM_QKV: RUN(ROWS_COMPACT, false, F32_ITEM_QKV); break;
+    case 100 + ROWS_COMPACT * 10 + F32_BIAS: RUN(ROWS_COMPACT, true, F32_BIAS); break;
+    case 100 + ROWS_COMPACT * 10 + F32_GELU_BWD: RUN(ROWS_COMPACT, true, F32_GELU_BWD); break;
+    case 100 + ROWS_COMPACT * 10 + F32_DX: RUN(ROWS_COMPACT, true, F32_DX); break;
+    case 100 + ROWS_ITEM_HM * 10 + F32_BIAS: RUN(ROWS_ITEM_HM, true, F32_BIAS); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef RUN
+  return hipGetLastError();
+}
+
 #define INST(T)                                                                               \
   template hipError_t launch_f32_wgrads<T>(F32WgradArgs<T>&, const F32Split&, hipStream_t);   \
+  template hipError_t launch_f32_linear<T>(const F32LinArgs<T>&, hipStream_t);                \
   template hipError_t launch_f32_add_ln<T>(const Geo&, const T*, int, const T*, const float*, \
                                            const float*, T*, int, T*, float*, hipStream_t);   \
   template hipError_t launch_f32_ln_bwd<T>(const Geo&, const T*, int, const T*, const T*,     \

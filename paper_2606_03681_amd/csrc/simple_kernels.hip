@@ -85,140 +85,6 @@ hipError_t launch_expand_meta(const int32_t* blob, int B, int R, int S, int word
   return hipGetLastError();
 }
 
-// ============================================================================ gather / scatter
-template <class T>
-__global__ void k_gather(Geo g, const T* __restrict__ src, T* __restrict__ dst) {
-  int64_t total = g.N * g.E;
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    int64_t p = i / g.E;
-    int e = (int)(i - p * g.E);
-    dst[i] = src[native_cell(g, p) * g.E + e];
-  }
-}
-
-template <class T>
-hipError_t launch_gather(const Geo& g, const T* native, T* cells, hipStream_t s) {
-  k_gather<T><<<grid_for(g.N * g.E), TFM_BLOCK, 0, s>>>(g, native, cells);
-  return hipGetLastError();
-}
-
-template <class T>
-__global__ void k_scatter(Geo g, const T* __restrict__ a, const T* __restrict__ b,
-                          T* __restrict__ dst) {
-  int64_t total = (int64_t)g.B * g.R * g.S * g.E;
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    int64_t cell = i / g.E;
-    int e = (int)(i - cell * g.E);
-    int c = (int)(cell % g.S);
-    int64_t br = cell / g.S;
-    int r = (int)(br % g.R);
-    int bb = (int)(br / g.R);
-    int gcol = g.colmap[bb * g.S + c];
-    float v = 0.f;
-    if (gcol >= 0) {
-      int64_t p = ((int64_t)gcol * g.R + r) * g.E + e;
-      v = ld(a + p);
-      if (b) v += ld(b + p);
-    }
-    st(dst + i, v);
-  }
-}
-
-template <class T>
-hipError_t launch_scatter(const Geo& g, const T* a, const T* b, T* native, hipStream_t s) {
-  k_scatter<T><<<grid_for((int64_t)g.B * g.R * g.S * g.E), TFM_BLOCK, 0, s>>>(g, a, b, native);
-  return hipGetLastError();
-}
-
-// ============================================================================ linear
-// 64 x 64 output tile per block, 4 x 4 outputs per thread, K in steps of 16 through LDS.
-template <class TA, class TO, bool ITEM>
-__global__ __launch_bounds__(256) void k_linear(int64_t M, int Nout, int K,
-                                                const TA* __restrict__ A, int64_t lda,
-                                                const float* __restrict__ w, int64_t wsj,
-                                                int64_t wsi, const float* __restrict__ bias,
-                                                TO* __restrict__ out, int64_t ldo, Geo g,
-                                                TO* __restrict__ kout, TO* __restrict__ vout) {
-  __shared__ float As[16][65];
-  __shared__ float Ws[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
-  const int n0 = blockIdx.y * 64;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 1024; i += 256) {
-      int mm = i >> 4, kk = i & 15;
-      int64_t m = m0 + mm;
-      int k = k0 + kk;
-      As[kk][mm] = (m < M && k < K) ? ld(A + m * lda + k) : 0.f;
-      int n = n0 + mm;
-      Ws[kk][mm] = (n < Nout && k < K) ? w[n * wsj + (int64_t)k * wsi] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int64_t m = m0 + ty + 16 * i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int n = n0 + tx + 16 * j;
-      if (n >= Nout) continue;
-      float v = acc[i][j] + (bias ? bias[n] : 0.f);
-      if (!ITEM) {
-        st(out + m * ldo + n, v);
-      } else {
-        int part = n / g.E, within = n - part * g.E;
-        int head = within / g.d, jj = within - head * g.d;
-        int64_t col = m / g.R;
-        int r = (int)(m - col * g.R);
-        if (part > 0 && r >= g.col_ntr[col]) continue;
-        TO* base = part == 0 ? out : (part == 1 ? kout : vout);
-        st(base + (((int64_t)col * g.heads + head) * g.R + r) * g.d + jj, v);
-      }
-    }
-  }
-}
-
-template <class TA, class TO>
-hipError_t launch_linear(int64_t M, int Nout, int K, const TA* A, int64_t lda, const float* w,
-                         int64_t wsj, int64_t wsi, const float* bias, TO* out, int64_t ldo,
-                         hipStream_t s) {
-  if (M <= 0) return hipSuccess;
-  dim3 grid((unsigned)((M + 63) / 64), (unsigned)((Nout + 63) / 64));
-  Geo g{};
-  k_linear<TA, TO, false><<<grid, 256, 0, s>>>(M, Nout, K, A, lda, w, wsj, wsi, bias, out, ldo,
-                                               g, nullptr, nullptr);
-  return hipGetLastError();
-}
-
-template <class T>
-hipError_t launch_linear_item_qkv(const Geo& g, const T* A, const float* w, const float* bias,
-                                  T* q, T* k, T* v, hipStream_t s) {
-  if (g.N <= 0) return hipSuccess;
-  dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((3 * g.E + 63) / 64));
-  k_linear<T, T, true><<<grid, 256, 0, s>>>(g.N, 3 * g.E, g.E, A, g.E, w, g.E, 1, bias, q, 0,
-                                            g, k, v);
-  return hipGetLastError();
-}
-
 // ============================================================================ column sums
 template <class T>
 __global__ void k_colsum(int64_t M, int Nj, const T* __restrict__ A, int64_t lda,
@@ -244,37 +110,6 @@ hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B,
   if (Z < 1) Z = 1;
   dim3 grid((unsigned)((Nj + 255) / 256), (unsigned)Z);
   k_colsum<T><<<grid, 256, 0, s>>>(M, Nj, A, lda, B, ldb, chunk, partial);
-  return hipGetLastError();
-}
-
-// ============================================================================ GELU
-template <class T>
-__global__ void k_gelu(int64_t n, const T* __restrict__ g, T* __restrict__ u) {
-  for (int64_t i = gtid(); i < n; i += gstride()) {
-    float x = ld(g + i);
-    st(u + i, 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)));
-  }
-}
-
-template <class T>
-hipError_t launch_gelu(int64_t count, const T* g, T* u, hipStream_t s) {
-  k_gelu<T><<<grid_for(count), TFM_BLOCK, 0, s>>>(count, g, u);
-  return hipGetLastError();
-}
-
-template <class T>
-__global__ void k_gelu_bwd(int64_t n, const T* __restrict__ g, T* __restrict__ du) {
-  for (int64_t i = gtid(); i < n; i += gstride()) {
-    float x = ld(g + i);
-    float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-    float pdf = 0.39894228040143268f * expf(-0.5f * x * x);
-    st(du + i, ld(du + i) * (cdf + x * pdf));
-  }
-}
-
-template <class T>
-hipError_t launch_gelu_bwd(int64_t count, const T* g, T* du, hipStream_t s) {
-  k_gelu_bwd<T><<<grid_for(count), TFM_BLOCK, 0, s>>>(count, g, du);
   return hipGetLastError();
 }
 
@@ -621,47 +456,10 @@ hipError_t launch_item_attn_bwd_simple(const Geo& g, const T* q, const T* k, con
   return hipGetLastError();
 }
 
-template <class T>
-__global__ void k_item_dqkv_to_cells(Geo g, const T* __restrict__ dq, const T* __restrict__ dk,
-                                     const T* __restrict__ dv, T* __restrict__ dqkv) {
-  const int E3 = 3 * g.E;
-  int64_t total = g.N * E3;
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    int64_t p = i / E3;
-    int nn = (int)(i - p * E3);
-    int part = nn / g.E, within = nn - part * g.E;
-    int head = within / g.d, j = within - head * g.d;
-    int64_t col = p / g.R;
-    int r = (int)(p - col * g.R);
-    const T* src = part == 0 ? dq : (part == 1 ? dk : dv);
-    if (part > 0 && r >= g.col_ntr[col]) {
-      st(dqkv + i, 0.f);
-    } else {
-      dqkv[i] = src[((col * g.heads + head) * g.R + r) * g.d + j];
-    }
-  }
-}
-
-template <class T>
-hipError_t launch_item_dqkv_to_cells(const Geo& g, const T* dq, const T* dk, const T* dv,
-                                     T* dqkv, hipStream_t s) {
-  k_item_dqkv_to_cells<T><<<grid_for(g.N * 3 * g.E), TFM_BLOCK, 0, s>>>(g, dq, dk, dv, dqkv);
-  return hipGetLastError();
-}
-
 // ============================================================================ instantiations
 #define INST(T)                                                                               \
-  template hipError_t launch_gather<T>(const Geo&, const T*, T*, hipStream_t);              \
-  template hipError_t launch_scatter<T>(const Geo&, const T*, const T*, T*, hipStream_t);   \
-  template hipError_t launch_linear<T, T>(int64_t, int, int, const T*, int64_t,             \
-                                          const float*, int64_t, int64_t, const float*, T*,  \
-                                          int64_t, hipStream_t);                             \
-  template hipError_t launch_linear_item_qkv<T>(const Geo&, const T*, const float*,         \
-                                                const float*, T*, T*, T*, hipStream_t);      \
   template hipError_t launch_colsum<T>(int64_t, int, const T*, int64_t, const T*, int64_t,   \
                                        int64_t, float*, hipStream_t);                        \
-  template hipError_t launch_gelu<T>(int64_t, const T*, T*, hipStream_t);                   \
-  template hipError_t launch_gelu_bwd<T>(int64_t, const T*, T*, hipStream_t);               \
   template hipError_t launch_feat_attn_fwd_simple<T>(const Geo&, const T*, T*, float*,      \
                                                      hipStream_t);                           \
   template hipError_t launch_feat_attn_bwd_simple<T>(const Geo&, const T*, const T*,        \
@@ -672,9 +470,7 @@ hipError_t launch_item_dqkv_to_cells(const Geo& g, const T* dq, const T* dk, con
   template hipError_t launch_item_attn_bwd_simple<T>(const Geo&, const T*, const T*,        \
                                                      const T*, const T*, const T*,           \
                                                      const float*, float*, T*, T*, T*,       \
-                                                     hipStream_t);                           \
-  template hipError_t launch_item_dqkv_to_cells<T>(const Geo&, const T*, const T*,          \
-                                                   const T*, T*, hipStream_t);
+                                                     hipStream_t);
 
 INST(float)
 INST(bf16)

@@ -402,40 +402,64 @@ int item_attn_bwd(const Dims& d, const tfm::Geo& g, const Plan& P, char* ws, con
   return TFM_OK;
 }
 
-// ---- forward ---------------------------------------------------------------------------------
+// ---- float32 mode ----------------------------------------------------------------------------
+// A linear layer over every active cell: rows of K values, weights W [N][K].
+template <class T>
+tfm::F32LinArgs<T> f32_linear(const tfm::Geo& g, const T* A, int amode, int K, const float* W,
+                              int N, int epi, T* out) {
+  tfm::F32LinArgs<T> a{};
+  a.M = g.N; a.N = N; a.K = K; a.A = A; a.amode = amode; a.W = W; a.epi = epi; a.out = out;
+  a.g = g;
+  return a;
+}
+// Its input gradient: rows of N values (dY) times the weights W [N][K] of the layer, K outputs.
+template <class T>
+tfm::F32LinArgs<T> f32_linear_dx(const tfm::Geo& g, const T* dY, int N, const float* W, int K,
+                                 int epi, T* out) {
+  tfm::F32LinArgs<T> a = f32_linear<T>(g, dY, tfm::ROWS_COMPACT, N, W, K, epi, out);
+  a.wt = 1;
+  return a;
+}
+
 template <class T>
 int fwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, T* Y, char* sv,
                const SavedLayout& S, char* ws, const WsLayout& W, hipStream_t s) {
   using namespace tfm;
   const POff o = param_offsets(d.E, d.H);
   const int E = d.E, H = d.H;
-  const int64_t N = g.N;
-  T* xc = (T*)(ws + W.xc);
   T* ta = (T*)(ws + W.ta);
-  T* tu = (T*)(ws + W.th1);
+  T* u = (T*)(sv + S.u);
   T* qkvf = (T*)(sv + S.qkvf);
   T* of = (T*)(sv + S.of);
   T* h1 = (T*)(sv + S.h1);
   T* h2 = (T*)(sv + S.h2);
   T* oi = (T*)(sv + S.oi);
   T* gp = (T*)(sv + S.g);
-  STEP("gather/hbm", launch_gather<T>(g, X, xc, s));
-  STEP("feat_qkv/valu", launch_linear<T, T>(N, 3 * E, E, xc, E, prm + o.Wqkv_f, E, 1, prm + o.bqkv_f, qkvf,
-                             3 * E, s));
+  F32LinArgs<T> a = f32_linear<T>(g, X, ROWS_NATIVE, E, prm + o.Wqkv_f, 3 * E, F32_BIAS, qkvf);
+  a.bias = prm + o.bqkv_f;
+  STEP("feat_qkv/mfma", launch_f32_linear(a, s));
   STEP("feat_attn_fwd/valu", launch_feat_attn_fwd_simple<T>(g, qkvf, of, (float*)(sv + S.lsef), s));
-  STEP("feat_out/valu", launch_linear<T, T>(N, E, E, of, E, prm + o.Wo_f, E, 1, prm + o.bo_f, ta, E, s));
+  a = f32_linear<T>(g, of, ROWS_COMPACT, E, prm + o.Wo_f, E, F32_BIAS, ta);
+  a.bias = prm + o.bo_f;
+  STEP("feat_out/mfma", launch_f32_linear(a, s));
   STEP("ln1/hbm", launch_f32_add_ln<T>(g, X, ROWS_NATIVE, ta, prm + o.g1, prm + o.be1, h1,
                                        ROWS_COMPACT, (T*)(sv + S.xh1), (float*)(sv + S.rs1), s));
-  STEP("item_qkv/valu", launch_linear_item_qkv<T>(g, h1, prm + o.Wqkv_i, prm + o.bqkv_i, (T*)(sv + S.qi),
-                                   (T*)(sv + S.ki), (T*)(sv + S.vi), s));
+  a = f32_linear<T>(g, h1, ROWS_COMPACT, E, prm + o.Wqkv_i, 3 * E, F32_ITEM_QKV, (T*)(sv + S.qi));
+  a.bias = prm + o.bqkv_i; a.out2 = (T*)(sv + S.ki); a.out3 = (T*)(sv + S.vi);
+  STEP("item_qkv/mfma", launch_f32_linear(a, s));
   STEP("item_attn_fwd/valu", launch_item_attn_fwd_simple<T>(g, (T*)(sv + S.qi), (T*)(sv + S.ki), (T*)(sv + S.vi),
                                         oi, (float*)(sv + S.lsei), s));
-  STEP("item_out/valu", launch_linear<T, T>(N, E, E, oi, E, prm + o.Wo_i, E, 1, prm + o.bo_i, ta, E, s));
+  a = f32_linear<T>(g, oi, ROWS_COMPACT, E, prm + o.Wo_i, E, F32_BIAS, ta);
+  a.bias = prm + o.bo_i;
+  STEP("item_out/mfma", launch_f32_linear(a, s));
   STEP("ln2/hbm", launch_f32_add_ln<T>(g, h1, ROWS_COMPACT, ta, prm + o.g2, prm + o.be2, h2,
                                        ROWS_COMPACT, (T*)(sv + S.xh2), (float*)(sv + S.rs2), s));
-  STEP("mlp_up/valu", launch_linear<T, T>(N, H, E, h2, E, prm + o.W1, E, 1, prm + o.b1, gp, H, s));
-  STEP("gelu/hbm", launch_gelu<T>(N * H, gp, tu, s));
-  STEP("mlp_down/valu", launch_linear<T, T>(N, E, H, tu, H, prm + o.W2, H, 1, prm + o.b2, ta, E, s));
+  a = f32_linear<T>(g, h2, ROWS_COMPACT, E, prm + o.W1, H, F32_GELU, gp);
+  a.bias = prm + o.b1; a.out2 = u;
+  STEP("mlp_up/mfma", launch_f32_linear(a, s));
+  a = f32_linear<T>(g, u, ROWS_COMPACT, H, prm + o.W2, E, F32_BIAS, ta);
+  a.bias = prm + o.b2;
+  STEP("mlp_down/mfma", launch_f32_linear(a, s));
   STEP("ln3/hbm", launch_f32_add_ln<T>(g, h2, ROWS_COMPACT, ta, prm + o.g3, prm + o.be3, Y,
                                        ROWS_NATIVE, (T*)(sv + S.xh3), (float*)(sv + S.rs3), s));
   ZERO_INACTIVE(g, Y);
@@ -462,11 +486,9 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   T* dz2 = (T*)(ws + W.te);
   T* dz1 = (T*)(ws + W.tf);
   T* du = (T*)(ws + W.th1);
-  T* uu = (T*)(ws + W.th2);
   T* dqkv = (T*)(ws + W.tqkv);
   const T* h1 = (const T*)(sv + S.h1);
   const T* h2 = (const T*)(sv + S.h2);
-  const T* gp = (const T*)(sv + S.g);
   const int lnr = f32_ln_rows(N);
   float* lnp[3];
   for (int i = 0; i < 3; ++i) lnp[i] = (float*)(ws + W.lnpart) + (size_t)i * lnr * 2 * E;
@@ -475,17 +497,19 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
                                            (const float*)(sv + S.rs3), prm + o.g3, dz3, lnp[2],
                                            s));
   // MLP
-  STEP("mlp_down_dx/valu", launch_linear<T, T>(N, H, E, dz3, E, prm + o.W2, 1, H, nullptr, du, H, s));
-  STEP("gelu/hbm", launch_gelu<T>(N * H, gp, uu, s));
-  STEP("gelu_bwd/hbm", launch_gelu_bwd<T>(N * H, gp, du, s));
-  STEP("mlp_up_dx/valu", launch_linear<T, T>(N, E, H, du, H, prm + o.W1, 1, E, nullptr, tmp, E, s));
+  F32LinArgs<T> a = f32_linear_dx<T>(g, dz3, E, prm + o.W2, H, F32_GELU_BWD, du);
+  a.aux = (const T*)(sv + S.g);
+  STEP("mlp_down_dx/mfma", launch_f32_linear(a, s));
+  STEP("mlp_up_dx/mfma",
+       launch_f32_linear(f32_linear_dx<T>(g, du, H, prm + o.W1, E, F32_BIAS, tmp), s));
   // LN2
   STEP("ln2_bwd/hbm", launch_f32_ln_bwd<T>(g, dz3, ROWS_COMPACT, tmp, (const T*)(sv + S.xh2),
                                            (const float*)(sv + S.rs2), prm + o.g2, dz2, lnp[1],
                                            s));
   // item attention
   T* doi = (T*)(ws + W.tc);
-  STEP("item_out_dx/valu", launch_linear<T, T>(N, E, E, dz2, E, prm + o.Wo_i, 1, E, nullptr, doi, E, s));
+  STEP("item_out_dx/mfma",
+       launch_f32_linear(f32_linear_dx<T>(g, dz2, E, prm + o.Wo_i, E, F32_BIAS, doi), s));
   T* dq = (T*)(ws + W.tq);
   T* dk = (T*)(ws + W.tk);
   T* dv = (T*)(ws + W.tv);
@@ -493,21 +517,23 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
                                         (const T*)(sv + S.vi), (const T*)(sv + S.oi), doi,
                                         (const float*)(sv + S.lsei), (float*)(ws + W.D), dq, dk,
                                         dv, s));
-  STEP("item_dqkv_cells/hbm", launch_item_dqkv_to_cells<T>(g, dq, dk, dv, dqkv, s));
-  STEP("item_qkv_dx/valu", launch_linear<T, T>(N, E, 3 * E, dqkv, 3 * E, prm + o.Wqkv_i, 1, E, nullptr, tmp, E,
-                             s));
+  a = f32_linear_dx<T>(g, dq, 3 * E, prm + o.Wqkv_i, E, F32_BIAS, tmp);
+  a.amode = ROWS_ITEM_HM; a.A2 = dk; a.A3 = dv;
+  STEP("item_qkv_dx/mfma", launch_f32_linear(a, s));
   // LN1
   STEP("ln1_bwd/hbm", launch_f32_ln_bwd<T>(g, dz2, ROWS_COMPACT, tmp, (const T*)(sv + S.xh1),
                                            (const float*)(sv + S.rs1), prm + o.g1, dz1, lnp[0],
                                            s));
   // feature attention
   T* dof = (T*)(ws + W.tc);
-  STEP("feat_out_dx/valu", launch_linear<T, T>(N, E, E, dz1, E, prm + o.Wo_f, 1, E, nullptr, dof, E, s));
+  STEP("feat_out_dx/mfma",
+       launch_f32_linear(f32_linear_dx<T>(g, dz1, E, prm + o.Wo_f, E, F32_BIAS, dof), s));
   STEP("feat_attn_bwd/valu", launch_feat_attn_bwd_simple<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
-  STEP("feat_qkv_dx/valu", launch_linear<T, T>(N, E, 3 * E, dqkv, 3 * E, prm + o.Wqkv_f, 1, E, nullptr, tmp, E,
-                             s));
-  STEP("scatter/hbm", launch_scatter<T>(g, dz1, tmp, dX, s));
+  a = f32_linear_dx<T>(g, dqkv, 3 * E, prm + o.Wqkv_f, E, F32_DX, dX);
+  a.aux = dz1;
+  STEP("feat_qkv_dx/mfma", launch_f32_linear(a, s));
+  ZERO_INACTIVE(g, dX);
   // every weight and bias gradient in one launch (their operands are all still there), and the
   // sums of all partials in another
   const F32Split sp = f32_split(N, E, H);
@@ -529,7 +555,7 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   wgrad(dq, dk, dv, 3 * E, h1, E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i);
   wgrad(dz2, nullptr, nullptr, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i);
   wgrad(du, nullptr, nullptr, H, h2, E, ROWS_COMPACT, o.W1, o.b1);
-  wgrad(dz3, nullptr, nullptr, E, uu, H, ROWS_COMPACT, o.W2, o.b2);
+  wgrad(dz3, nullptr, nullptr, E, (const T*)(sv + S.u), H, ROWS_COMPACT, o.W2, o.b2);
   // norm scales and shifts are adjacent in the packed order: one sum over 2E columns each
   const size_t og[3] = {o.g1, o.g2, o.g3};
   for (int i = 0; i < 3; ++i) rl.add(lnp[i], 2 * E, lnr, 2 * E, grads + og[i]);
