@@ -78,4 +78,22 @@ struct F32LinArgs {
 template <class T>
 hipError_t launch_f32_linear(const F32LinArgs<T>& a, hipStream_t s);
 
+// Item-axis attention (layouts as in attn.h), keys the first n_train rows of the column.  The
+// backward writes dq, dk, dv head-major (dk, dv at train rows only); Dbuf [NC * heads * R] is
+// scratch.
+template <class T>
+hipError_t launch_f32_item_fwd(const Geo& g, const T* q, const T* k, const T* v, T* o, float* lse,
+                               hipStream_t s);
+template <class T>
+hipError_t launch_f32_item_bwd(const Geo& g, const T* q, const T* k, const T* v, const T* o,
+                               const T* dout, const float* lse, float* Dbuf, T* dq, T* dk, T* dv,
+                               hipStream_t s);
+
+// Feature-axis attention over the active cells of a row (at most 256), layouts as in attn.h.
+template <class T>
+hipError_t launch_f32_feat_fwd(const Geo& g, const T* qkv, T* o, float* lse, hipStream_t s);
+template <class T>
+hipError_t launch_f32_feat_bwd(const Geo& g, const T* qkv, const T* o, const T* dout,
+                               const float* lse, T* dqkv, hipStream_t s);
+
 }  // namespace tfm

@@ -20,18 +20,4 @@ hipError_t launch_expand_meta(const int32_t* blob, int B, int R, int S, int word
 template <class T>
 hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B, int64_t ldb,
                          int64_t chunk, float* partial, hipStream_t s);
-template <class T>
-hipError_t launch_feat_attn_fwd_simple(const Geo& g, const T* qkv, T* o, float* lse,
-                                       hipStream_t s);
-template <class T>
-hipError_t launch_feat_attn_bwd_simple(const Geo& g, const T* qkv, const T* o, const T* dout,
-                                       const float* lse, T* dqkv, hipStream_t s);
-template <class T>
-hipError_t launch_item_attn_fwd_simple(const Geo& g, const T* q, const T* k, const T* v, T* o,
-                                       float* lse, hipStream_t s);
-// dq/dk/dv head-major; D is scratch [NC*heads*R]
-template <class T>
-hipError_t launch_item_attn_bwd_simple(const Geo& g, const T* q, const T* k, const T* v,
-                                       const T* o, const T* dout, const float* lse, float* D,
-                                       T* dq, T* dk, T* dv, hipStream_t s);
 }  // namespace tfm

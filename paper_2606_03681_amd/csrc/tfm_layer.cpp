@@ -438,7 +438,7 @@ int fwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, T
   F32LinArgs<T> a = f32_linear<T>(g, X, ROWS_NATIVE, E, prm + o.Wqkv_f, 3 * E, F32_BIAS, qkvf);
   a.bias = prm + o.bqkv_f;
   STEP("feat_qkv/mfma", launch_f32_linear(a, s));
-  STEP("feat_attn_fwd/valu", launch_feat_attn_fwd_simple<T>(g, qkvf, of, (float*)(sv + S.lsef), s));
+  STEP("feat_attn_fwd/mfma", launch_f32_feat_fwd<T>(g, qkvf, of, (float*)(sv + S.lsef), s));
   a = f32_linear<T>(g, of, ROWS_COMPACT, E, prm + o.Wo_f, E, F32_BIAS, ta);
   a.bias = prm + o.bo_f;
   STEP("feat_out/mfma", launch_f32_linear(a, s));
@@ -447,7 +447,7 @@ int fwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, T
   a = f32_linear<T>(g, h1, ROWS_COMPACT, E, prm + o.Wqkv_i, 3 * E, F32_ITEM_QKV, (T*)(sv + S.qi));
   a.bias = prm + o.bqkv_i; a.out2 = (T*)(sv + S.ki); a.out3 = (T*)(sv + S.vi);
   STEP("item_qkv/mfma", launch_f32_linear(a, s));
-  STEP("item_attn_fwd/valu", launch_item_attn_fwd_simple<T>(g, (T*)(sv + S.qi), (T*)(sv + S.ki), (T*)(sv + S.vi),
+  STEP("item_attn_fwd/mfma", launch_f32_item_fwd<T>(g, (T*)(sv + S.qi), (T*)(sv + S.ki), (T*)(sv + S.vi),
                                         oi, (float*)(sv + S.lsei), s));
   a = f32_linear<T>(g, oi, ROWS_COMPACT, E, prm + o.Wo_i, E, F32_BIAS, ta);
   a.bias = prm + o.bo_i;
@@ -513,7 +513,7 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   T* dq = (T*)(ws + W.tq);
   T* dk = (T*)(ws + W.tk);
   T* dv = (T*)(ws + W.tv);
-  STEP("item_attn_bwd/valu", launch_item_attn_bwd_simple<T>(g, (const T*)(sv + S.qi), (const T*)(sv + S.ki),
+  STEP("item_attn_bwd/mfma", launch_f32_item_bwd<T>(g, (const T*)(sv + S.qi), (const T*)(sv + S.ki),
                                         (const T*)(sv + S.vi), (const T*)(sv + S.oi), doi,
                                         (const float*)(sv + S.lsei), (float*)(ws + W.D), dq, dk,
                                         dv, s));
@@ -528,7 +528,7 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   T* dof = (T*)(ws + W.tc);
   STEP("feat_out_dx/mfma",
        launch_f32_linear(f32_linear_dx<T>(g, dz1, E, prm + o.Wo_f, E, F32_BIAS, dof), s));
-  STEP("feat_attn_bwd/valu", launch_feat_attn_bwd_simple<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
+  STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
   a = f32_linear_dx<T>(g, dqkv, 3 * E, prm + o.Wqkv_f, E, F32_DX, dX);
   a.aux = dz1;
@@ -643,7 +643,7 @@ int feat_fwd(const tfm::Geo& g, const tfm::bf16* x, int xmode, const float* bqkv
   if (feat_attn_mfma_ok(g))
     STEP("feat_attn_fwd/mfma", launch_feat_attn_fwd(g, b.qkvf, b.of, b.lsef, s));
   else
-    STEP("feat_attn_fwd/valu", launch_feat_attn_fwd_simple<bf16>(g, b.qkvf, b.of, b.lsef, s));
+    STEP("feat_attn_fwd/mfma", launch_f32_feat_fwd<bf16>(g, b.qkvf, b.of, b.lsef, s));
   return TFM_OK;
 }
 
@@ -853,8 +853,7 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
          launch_feat_attn_bwd(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                               (const float*)(sv + S.lsef), dqkv, s));
   else
-    STEP("feat_attn_bwd/valu",
-         launch_feat_attn_bwd_simple<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
+    STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
   CHK(G.run(dqkv, 3 * E, X, E, ROWS_NATIVE, o.Wqkv_f, o.bqkv_f));
   // dX = dZ1 + dQKV_f Wqkv_f, native layout
@@ -994,8 +993,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
          launch_feat_attn_bwd(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                               (const float*)(sv + S.lsef), dqkv, s));
   else
-    STEP("feat_attn_bwd/valu",
-         launch_feat_attn_bwd_simple<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
+    STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
   CHK(G.run(dqkv, 3 * E, (const T*)(sv + S.r1), E, ROWS_COMPACT, o.Wqkv_f, o.bqkv_f));
   // dX = decay (dh1 + RMS1'(dQKV_f Wqkv_f)), native
