@@ -104,45 +104,40 @@ struct WFold {
 hipError_t launch_weight_prep(const float* params, int E, int H, bf16* w, bf16* wt,
                               const WFold* fold, hipStream_t s);
 
-// Weight gradient of a product whose input was the folded x-hat (see WFold): with
-// h = gamma o x-hat + beta, dW[n][k] = (sum_z wpart)[n][k] gamma[k] + (sum_z bpart)[n] beta[k];
-// grad (N x K) = (accumulate ? grad : 0) + that, in the fixed summation order of
-// launch_reduce_z.  The bias sums are left in the first row of bpart (the other rows are
-// scratch afterwards): the bias gradient is then a one-row reduce of bpart.
-hipError_t launch_reduce_wfold(int Z, int N, int K, float* wpart, float* bpart,
-                               const float* gamma, const float* beta, float* grad,
-                               int accumulate, hipStream_t s);
-
 // Writes 0 to every element (elt bytes each) of the native tensor that lies in an inactive cell.
 hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStream_t s);
 
-// Weight gradient dW[n][k] = sum_m dY[m][n] X[m][k] (+ db[n] = sum_m dY[m][n]) over M cells,
-// split into Z = wgrad_chunks(M) chunks of wgrad_chunk(M) cells (a multiple of 32, at most
-// WGRAD_CHUNK_MAX): M / 256 cells rounded up while that is at most WGRAD_CHUNK_MAX, so that
-// the workgroups of one tile fill the 256 compute units in whole rounds; partials land in part
-// [Z][N][K] and bpart [Z][N].  wgrad_max_chunks(Mmax) bounds Z for every M <= Mmax.
+// Weight gradients dW[n][k] = sum_m dY[m][n] X[m][k] with db[n] = sum_m dY[m][n] over the N active
+// cells, all products of a backward pass in one launch, split into Z chunks of `chunk` cells (a
+// multiple of 32, at most WGRAD_CHUNK_MAX); partials land in part [Z][N][K] and bpart [Z][N].
+// wgrad_part_floats(Mmax) bounds the floats of all partials of a pass for every M <= Mmax.
 constexpr int WGRAD_CHUNK_MAX = 8192;
-constexpr int WGRAD_SLOTS = 256;
-int64_t wgrad_chunk(int64_t M);
-int64_t wgrad_max_chunks(int64_t Mmax);
-struct WgradArgs {
-  int64_t M;
-  int N, K;
-  const bf16* dY;  // compact rows, leading dimension ldy, or ROWS_ITEM_HM (dY, dY2, dY3)
+constexpr int WGRAD_CHUNK_MIN = 256;
+constexpr int WGRAD_SLOTS = 512;  // workgroups resident at once: two on each of 256 CUs
+struct WgradSplit {
+  int Z;
+  int64_t chunk;
+};
+WgradSplit wgrad_split(int64_t M, int E, int H);
+size_t wgrad_part_floats(int64_t Mmax, int E, int H);
+struct WgradJob {
+  int32_t N, K;
+  const bf16* dY;  // rows of N values: compact, native, or ROWS_ITEM_HM (dY, dY2, dY3)
   const bf16* dY2;
   const bf16* dY3;
-  int64_t ldy;
-  int ymode;
-  const bf16* X;   // rows per xmode (compact with ldx, or the native cell tensor)
-  int64_t ldx;
-  int xmode;
+  const bf16* X;   // rows of K values: compact or native (not both operands native)
+  int32_t ymode, xmode;
   float* part;
-  float* bpart;    // may be null: no bias gradient
-  int64_t chunk;
+  float* bpart;
+  int32_t tile0;   // first tile of the job (set by the launch)
+};
+struct WgradArgs {
+  WgradJob j[6];
+  int32_t n, tiles;
+  int64_t M, chunk;
   Geo g;
 };
-int wgrad_chunks(int64_t M);
-hipError_t launch_wgrad_mfma(const WgradArgs& a, hipStream_t s);
+hipError_t launch_wgrads(WgradArgs& a, const WgradSplit& sp, hipStream_t s);
 // out[i] = (accumulate ? out[i] : 0) + sum_z part[z * stride + i], fixed summation order.
 // With many partials and few outputs the sum runs in two passes, the first of which
 // overwrites part (it is scratch).
@@ -222,10 +217,11 @@ hipError_t launch_mlp_bwd_stream(const float* w1, const float* g2, const float* 
                                  bf16* out, hipStream_t s);
 hipError_t launch_mlp_bwd(const MlpBwdArgs& a, hipStream_t s);
 
-// Bytes of the LayerNorm-backward column partials for up to `cells` cells.
-size_t ln_partial_bytes(int64_t cells, int E);
+// Floats of one norm's column partials for up to `cells` cells: [64-cell tiles][2 E], which also
+// holds the LN3 backward's and (two norms together) the fused MLP backward's.
+int64_t ln_part_floats(int64_t cells, int E);
 
 // Scratch bytes that the MFMA path needs inside the workspace.
-size_t fast_workspace_bytes(int B, int R, int S, int E, int heads, int H, bool bf16);
+size_t fast_workspace_bytes(int64_t cells, int E, int H);
 
 }  // namespace tfm

@@ -334,28 +334,13 @@ template hipError_t launch_thinking_bwd<float>(const Geo&, int, const float*, fl
 template hipError_t launch_thinking_bwd<bf16>(const Geo&, int, const bf16*, float*, int,
                                               hipStream_t);
 
-size_t ln_partial_bytes(int64_t cells, int E) {
-  // LN-backward GEMM epilogues: [64-cell tiles][2 E]; fused MLP backward: [tiles][4 E]
-  const size_t a = (size_t)gemm_row_tiles(cells) * 2 * E * 4;
-  const size_t b = (size_t)mlp_bwd_tiles(cells) * 4 * E * 4;
-  return (a > b ? a : b) + 256;
-}
+int64_t ln_part_floats(int64_t cells, int E) { return gemm_row_tiles(cells) * 2 * E; }
 
-size_t fast_workspace_bytes(int B, int R, int S, int E, int heads, int H, bool bf16) {
-  (void)heads;
-  if (!bf16) return 0;
-  WOff wo = weight_offsets(E, H);
-  const int64_t tiles = gemm_row_tiles((int64_t)B * R * S);
-  size_t bytes = 2 * (size_t)wo.total * 2 + 1024;   // w and wt
-  (void)tiles;
-  bytes += ln_partial_bytes((int64_t)B * R * S, E);  // LN-backward column partials
-  const int64_t cells = (int64_t)B * R * S;
-  const int64_t zw = wgrad_max_chunks(cells);
-  const int64_t maxw = 3LL * E * E > (int64_t)H * E ? 3LL * E * E : (int64_t)H * E;
-  const int64_t maxn = 3LL * E > H ? 3LL * E : H;
-  bytes += (size_t)zw * maxw * 4 + 256;                // weight-gradient partials
-  bytes += (size_t)zw * maxn * 4 + 256;                // bias-gradient partials
-  return bytes;
+size_t fast_workspace_bytes(int64_t cells, int E, int H) {
+  const WOff wo = weight_offsets(E, H);
+  return 2 * (size_t)wo.total * 2 + 1024                   // w and wt
+         + 3 * (size_t)ln_part_floats(cells, E) * 4 + 256  // norm-backward column partials
+         + wgrad_part_floats(cells, E, H) * 4 + 256;       // weight and bias partials
 }
 
 }  // namespace tfm

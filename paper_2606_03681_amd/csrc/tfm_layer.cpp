@@ -259,8 +259,7 @@ WsLayout ws_layout(const Dims& d) {
   const bool f32 = !fast_eligible(d);
   L.part = a.take(f32 ? tfm::f32_wpart_floats(d.Nmax, d.E, d.H) * 4 : 0);
   L.lnpart = a.take(f32 ? tfm::f32_lnpart_floats(d.Nmax, d.E) * 4 : 0);
-  L.fast = a.take(tfm::fast_workspace_bytes(d.B, d.R, d.S, d.E, d.heads, d.H,
-                                            d.dtype == TFM_BF16));
+  L.fast = a.take(f32 ? 0 : tfm::fast_workspace_bytes(d.Nmax, d.E, d.H));
   L.total = a.off;
   return L;
 }
@@ -568,9 +567,8 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
 struct FastWs {
   tfm::bf16* w;
   tfm::bf16* wt;
-  float* lnpart;
-  float* wpart;
-  float* bpart;
+  float* lnpart[3];  // column partials of norm 1, 2, 3 (2 and 3 adjacent)
+  float* wpart;      // weight and bias partials
   tfm::WOff wo;
 };
 
@@ -582,13 +580,10 @@ FastWs fast_ws(const Dims& d, char* ws, const WsLayout& W) {
   p += align_up((size_t)f.wo.total * 2);
   f.wt = (tfm::bf16*)p;
   p += align_up((size_t)f.wo.total * 2);
-  f.lnpart = (float*)p;
-  p += align_up(tfm::ln_partial_bytes(d.Nmax, d.E));
-  const int64_t zw = tfm::wgrad_max_chunks(d.Nmax);
-  const int64_t maxw = 3LL * d.E * d.E > (int64_t)d.H * d.E ? 3LL * d.E * d.E : (int64_t)d.H * d.E;
+  const int64_t ln = tfm::ln_part_floats(d.Nmax, d.E);
+  for (int i = 0; i < 3; ++i) f.lnpart[i] = (float*)p + i * ln;
+  p += align_up(3 * (size_t)ln * 4);
   f.wpart = (float*)p;
-  p += align_up((size_t)zw * maxw * 4 + 256);
-  f.bpart = (float*)p;
   return f;
 }
 
@@ -714,35 +709,44 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
   return TFM_OK;
 }
 
-// Weight and bias gradients of one linear on the MFMA path (split over cells, fixed-order sums).
+// Weight, bias and norm gradients of one backward pass on the MFMA path: the passes note them
+// as their operands become final (every operand keeps its buffer to the end of the call), and
+// finish() forms all products in one launch and adds all partials in another.
 struct FastGrads {
-  const FastWs& f;
-  const tfm::Geo& g;
+  float* wpart;
   float* grads;
-  int accumulate;
-  hipStream_t s;
-  // ymode: layout of dY (compact, native; head-major item gradients when dY2 is given)
-  // xg, xb: X is the x-hat of a norm with affine (xg, xb): the weight gradient is formed for
-  // h = xg o X + xb (launch_reduce_wfold)
-  int run(const tfm::bf16* dY, int N, const tfm::bf16* X, int K, int xmode, size_t offW,
-          size_t offb, const tfm::bf16* dY2 = nullptr, const tfm::bf16* dY3 = nullptr,
-          int ymode = tfm::ROWS_COMPACT, const float* xg = nullptr, const float* xb = nullptr) {
-    tfm::WgradArgs a{};
-    a.M = g.N; a.N = N; a.K = K; a.dY = dY; a.ldy = N; a.X = X; a.ldx = K; a.xmode = xmode;
-    a.dY2 = dY2; a.dY3 = dY3; a.ymode = dY2 ? tfm::ROWS_ITEM_HM : ymode;
-    a.part = f.wpart; a.bpart = f.bpart; a.g = g;
-    const int Z = tfm::wgrad_chunks(g.N);
-    STEP("wgrad/mfma", tfm::launch_wgrad_mfma(a, s));
-    if (xg) {
-      // leaves the bias sums in the first row of bpart
-      STEP("reduce/hbm", tfm::launch_reduce_wfold(Z, N, K, f.wpart, f.bpart, xg, xb,
-                                                  grads + offW, accumulate, s));
-      STEP("reduce/hbm", tfm::launch_reduce_z(1, N, N, f.bpart, grads + offb, accumulate, s));
-    } else {
-      STEP("reduce/hbm", tfm::launch_reduce_z(Z, (int64_t)N * K, (int64_t)N * K, f.wpart,
-                                              grads + offW, accumulate, s));
-      STEP("reduce/hbm", tfm::launch_reduce_z(Z, N, N, f.bpart, grads + offb, accumulate, s));
-    }
+  tfm::WgradSplit sp;
+  tfm::WgradArgs wa{};
+  tfm::ReduceList rl;
+
+  FastGrads(const Dims& d, const tfm::Geo& g, const FastWs& f, float* grads)
+      : wpart(f.wpart), grads(grads), sp(tfm::wgrad_split(g.N, d.E, d.H)) {
+    wa.g = g;
+  }
+  // One linear: rows dY (N values; head-major item gradients when dY2 is given) and X (K values).
+  // xg, xb: X is the x-hat of a norm with affine (xg, xb), the gradient is formed for
+  // xg o X + xb.
+  void linear(const tfm::bf16* dY, int N, const tfm::bf16* X, int K, int xmode, size_t offW,
+              size_t offb, const tfm::bf16* dY2 = nullptr, const tfm::bf16* dY3 = nullptr,
+              int ymode = tfm::ROWS_COMPACT, const float* xg = nullptr,
+              const float* xb = nullptr) {
+    tfm::WgradJob& j = wa.j[wa.n++];
+    j = tfm::WgradJob{N, K, dY, dY2, dY3, X, dY2 ? tfm::ROWS_ITEM_HM : ymode, xmode,
+                      wpart, wpart + (size_t)sp.Z * N * K, 0};
+    wpart = j.bpart + (size_t)sp.Z * N;
+    if (xg)
+      rl.add_fold(j.part, (int64_t)N * K, sp.Z, N, K, grads + offW, j.bpart, N, xg, xb);
+    else
+      rl.add(j.part, (int64_t)N * K, sp.Z, (int64_t)N * K, grads + offW);
+    rl.add(j.bpart, N, sp.Z, N, grads + offb);
+  }
+  // Norm parameters: count column sums from rows of `stride` partials.
+  void norm(const float* part, int64_t stride, int rows, int64_t count, size_t off) {
+    rl.add(part, stride, rows, count, grads + off);
+  }
+  int finish(int accumulate, hipStream_t s) {
+    STEP("wgrad/mfma", tfm::launch_wgrads(wa, sp, s));
+    STEP("reduce/hbm", tfm::launch_reduce_list(rl, accumulate, s));
     return TFM_OK;
   }
 };
@@ -758,7 +762,7 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   const int E = d.E, H = d.H;
   const int64_t N = g.N;
   const int tiles = (int)tfm::gemm_tiles(tfm::EPI_LN_BWD, E, N);
-  FastGrads G{f, g, grads, accumulate, s};
+  FastGrads G(d, g, f, grads);
   const bool fused_mlp = mlp_fused_ok(E, H);
   // the backward reads the transposed copies only; the fold (x-hat2's affine in W1 and b1)
   // gives the fused MLP backward the folded up-projection bias it recomputes G with
@@ -783,37 +787,36 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
     m.xh2 = xh2; m.rs2 = (const float*)(sv + S.rs2); m.ws = ms;
     m.g3 = prm + o.g3; m.g2 = prm + o.g2;
     m.fb1 = reinterpret_cast<const float*>(f.w + f.wo.fb) + 3 * E;
-    m.dz3 = dz3; m.dz2 = dz2; m.dg = dgb; m.u = ub; m.part = f.lnpart; m.g = g;
+    m.dz3 = dz3; m.dz2 = dz2; m.dg = dgb; m.u = ub; m.part = f.lnpart[1]; m.g = g;
     STEP("mlp_bwd_fused/mfma", launch_mlp_bwd(m, s));
     const int nt = (int)mlp_bwd_tiles(N);
-    STEP("reduce/hbm", launch_reduce_z(nt, 2 * E, 4 * E, f.lnpart, grads + o.g3, accumulate, s));
-    STEP("reduce/hbm",
-         launch_reduce_z(nt, 2 * E, 4 * E, f.lnpart + 2 * E, grads + o.g2, accumulate, s));
-    CHK(G.run(dz3, E, ub, H, ROWS_COMPACT, o.W2, o.b2));
-    CHK(G.run(dgb, H, xh2, E, ROWS_COMPACT, o.W1, o.b1, nullptr, nullptr, ROWS_COMPACT,
-              prm + o.g2, prm + o.be2));
+    G.norm(f.lnpart[1], 4 * E, nt, 2 * E, o.g3);
+    G.norm(f.lnpart[1] + 2 * E, 4 * E, nt, 2 * E, o.g2);
+    G.linear(dz3, E, ub, H, ROWS_COMPACT, o.W2, o.b2);
+    G.linear(dgb, H, xh2, E, ROWS_COMPACT, o.W1, o.b1, nullptr, nullptr, ROWS_COMPACT,
+              prm + o.g2, prm + o.be2);
   } else {
     // LN3 (from the native dY), with its gamma/beta column sums
     int nb = 0;
     STEP("ln3_bwd/hbm", launch_ln_out_bwd(g, dY, (const T*)(sv + S.xh3),
-                                          (const float*)(sv + S.rs3), prm + o.g3, dz3, f.lnpart,
+                                          (const float*)(sv + S.rs3), prm + o.g3, dz3, f.lnpart[2],
                                           &nb, s));
     // gamma and beta gradients are adjacent in the packed order: one sum over 2E columns
-    STEP("reduce/hbm", launch_reduce_z(nb, 2 * E, 2 * E, f.lnpart, grads + o.g3, accumulate, s));
+    G.norm(f.lnpart[2], 2 * E, nb, 2 * E, o.g3);
     // MLP: dG = (dZ3 W2) * GELU'(G)
     GemmArgs a = gemm_base(g, N, H, E, EPI_GELU_BWD);
     a.A = dz3; a.lda = E; a.Bt = f.wt + f.wo.w2; a.out = dgb; a.ldo = H;
     a.aux = (const T*)(sv + S.g);
     STEP("mlp_down_dx/mfma", launch_gemm(a, s));
-    CHK(G.run(dz3, E, (const T*)(sv + S.u), H, ROWS_COMPACT, o.W2, o.b2));
-    CHK(G.run(dgb, H, xh2, E, ROWS_COMPACT, o.W1, o.b1, nullptr, nullptr, ROWS_COMPACT,
-              prm + o.g2, prm + o.be2));
+    G.linear(dz3, E, (const T*)(sv + S.u), H, ROWS_COMPACT, o.W2, o.b2);
+    G.linear(dgb, H, xh2, E, ROWS_COMPACT, o.W1, o.b1, nullptr, nullptr, ROWS_COMPACT,
+              prm + o.g2, prm + o.be2);
     // dZ2 = LN2'(dZ3 + dG W1)
     a = gemm_base(g, N, E, H, EPI_LN_BWD);
     a.A = dgb; a.lda = H; a.Bt = f.wt + f.wo.w1; a.resid = dz3; a.aux = xh2;
-    a.rstd_in = (const float*)(sv + S.rs2); a.gamma = prm + o.g2; a.out = dz2; a.part = f.lnpart;
+    a.rstd_in = (const float*)(sv + S.rs2); a.gamma = prm + o.g2; a.out = dz2; a.part = f.lnpart[1];
     STEP("mlp_up_dx_ln2/mfma", launch_gemm(a, s));
-    STEP("reduce/hbm", launch_reduce_z(tiles, 2 * E, 2 * E, f.lnpart, grads + o.g2, accumulate, s));
+    G.norm(f.lnpart[1], 2 * E, tiles, 2 * E, o.g2);
   }
   GemmArgs a;
   // item attention
@@ -821,7 +824,7 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   a = gemm_base(g, N, E, E, EPI_BIAS);
   a.A = dz2; a.lda = E; a.Bt = f.wt + f.wo.o_i; a.out = doi; a.ldo = E;
   STEP("item_out_dx/mfma", launch_gemm(a, s));
-  CHK(G.run(dz2, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i));
+  G.linear(dz2, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i);
   T* dq = (T*)(ws + W.tq);
   T* dk = (T*)(ws + W.tk);
   T* dv = (T*)(ws + W.tv);
@@ -832,22 +835,22 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   const float* lsei = (const float*)(sv + S.lsei);
   float* Dq = (float*)(ws + W.D);
   CHK(item_attn_bwd(d, g, P, ws, W.meta, qi, ki, vi, oi, doi, lsei, Dq, dq, dk, dv, s));
-  CHK(G.run(dq, 3 * E, xh1, E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i, dk, dv, ROWS_COMPACT,
-            prm + o.g1, prm + o.be1));
+  G.linear(dq, 3 * E, xh1, E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i, dk, dv, ROWS_COMPACT,
+            prm + o.g1, prm + o.be1);
   // dZ1 = LN1'(dZ2 + dQKV_i Wqkv_i), the gradients read head-major in place
   a = gemm_base(g, N, E, 3 * E, EPI_LN_BWD);
   a.A = dq; a.A2 = dk; a.A3 = dv; a.amode = ROWS_ITEM_HM; a.lda = 3 * E;
   a.Bt = f.wt + f.wo.qkv_i; a.resid = dz2;
   a.aux = xh1; a.rstd_in = (const float*)(sv + S.rs1); a.gamma = prm + o.g1;
-  a.out = dz1; a.part = f.lnpart;
+  a.out = dz1; a.part = f.lnpart[0];
   STEP("item_qkv_dx_ln1/mfma", launch_gemm(a, s));
-  STEP("reduce/hbm", launch_reduce_z(tiles, 2 * E, 2 * E, f.lnpart, grads + o.g1, accumulate, s));
+  G.norm(f.lnpart[0], 2 * E, tiles, 2 * E, o.g1);
   // feature attention
   T* dof = (T*)(ws + W.tc);
   a = gemm_base(g, N, E, E, EPI_BIAS);
   a.A = dz1; a.lda = E; a.Bt = f.wt + f.wo.o_f; a.out = dof; a.ldo = E;
   STEP("feat_out_dx/mfma", launch_gemm(a, s));
-  CHK(G.run(dz1, E, (const T*)(sv + S.of), E, ROWS_COMPACT, o.Wo_f, o.bo_f));
+  G.linear(dz1, E, (const T*)(sv + S.of), E, ROWS_COMPACT, o.Wo_f, o.bo_f);
   if (feat_attn_mfma_ok(g))
     STEP("feat_attn_bwd/mfma",
          launch_feat_attn_bwd(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
@@ -855,13 +858,13 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   else
     STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
-  CHK(G.run(dqkv, 3 * E, X, E, ROWS_NATIVE, o.Wqkv_f, o.bqkv_f));
+  G.linear(dqkv, 3 * E, X, E, ROWS_NATIVE, o.Wqkv_f, o.bqkv_f);
   // dX = dZ1 + dQKV_f Wqkv_f, native layout
   a = gemm_base(g, N, E, 3 * E, EPI_DX);
   a.A = dqkv; a.lda = 3 * E; a.Bt = f.wt + f.wo.qkv_f; a.resid = dz1; a.out = dX;
   STEP("feat_qkv_dx/mfma", launch_gemm(a, s));
   ZERO_INACTIVE(g, dX);
-  return TFM_OK;
+  return G.finish(accumulate, s);
 }
 
 // ---- pre-norm RMSNorm block (bfloat16, MFMA path) --------------------------------------------
@@ -934,7 +937,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   const int E = d.E, H = d.H;
   const int64_t N = g.N;
   const int tiles = (int)tfm::gemm_tiles(tfm::EPI_RMS_BWD, E, N);
-  FastGrads G{f, g, grads, accumulate, s};
+  FastGrads G(d, g, f, grads);
   STEP("weight_prep/hbm", launch_weight_prep(prm, E, H, f.w, f.wt, nullptr, s));
   T* dh2 = (T*)(ws + W.te);
   T* dh1 = (T*)(ws + W.tf);
@@ -946,23 +949,23 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   a.A = dY; a.amode = ROWS_NATIVE; a.lda = E; a.Bt = f.wt + f.wo.w2; a.out = dgb; a.ldo = H;
   a.aux = (const T*)(sv + S.g);
   STEP("mlp_down_dx/mfma", launch_gemm(a, s));
-  CHK(G.run(dY, E, (const T*)(sv + S.u), H, ROWS_COMPACT, o.W2, o.b2, nullptr, nullptr,
-            ROWS_NATIVE));
-  CHK(G.run(dgb, H, (const T*)(sv + S.r3), E, ROWS_COMPACT, o.W1, o.b1));
+  G.linear(dY, E, (const T*)(sv + S.u), H, ROWS_COMPACT, o.W2, o.b2, nullptr, nullptr,
+            ROWS_NATIVE);
+  G.linear(dgb, H, (const T*)(sv + S.r3), E, ROWS_COMPACT, o.W1, o.b1);
   // dh2 = dY + RMS3'(dG W1)
   a = gemm_base(g, N, E, H, EPI_RMS_BWD);
   a.A = dgb; a.lda = H; a.Bt = f.wt + f.wo.w1; a.resid = dY; a.rmode = ROWS_NATIVE;
   a.aux = (const T*)(sv + S.h2);
   a.rstd_in = (const float*)(sv + S.rs3); a.gamma = prm + o.g3; a.eps = kRmsEps;
-  a.oscale = 1.0f; a.omode = ROWS_COMPACT; a.out = dh2; a.part = f.lnpart;
+  a.oscale = 1.0f; a.omode = ROWS_COMPACT; a.out = dh2; a.part = f.lnpart[2];
   STEP("mlp_up_dx_rms3/mfma", launch_gemm(a, s));
-  STEP("reduce/hbm", launch_reduce_z(tiles, E, E, f.lnpart, grads + o.g3, accumulate, s));
+  G.norm(f.lnpart[2], E, tiles, E, o.g3);
   // item attention
   T* doi = (T*)(ws + W.tc);
   a = gemm_base(g, N, E, E, EPI_BIAS);
   a.A = dh2; a.lda = E; a.Bt = f.wt + f.wo.o_i; a.out = doi; a.ldo = E;
   STEP("item_out_dx/mfma", launch_gemm(a, s));
-  CHK(G.run(dh2, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i));
+  G.linear(dh2, E, (const T*)(sv + S.oi), E, ROWS_COMPACT, o.Wo_i, o.bo_i);
   T* dq = (T*)(ws + W.tq);
   T* dk = (T*)(ws + W.tk);
   T* dv = (T*)(ws + W.tv);
@@ -973,21 +976,21 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   const float* lsei = (const float*)(sv + S.lsei);
   float* Dq = (float*)(ws + W.D);
   CHK(item_attn_bwd(d, g, P, ws, W.meta, qi, ki, vi, oi, doi, lsei, Dq, dq, dk, dv, s));
-  CHK(G.run(dq, 3 * E, (const T*)(sv + S.r2), E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i, dk, dv));
+  G.linear(dq, 3 * E, (const T*)(sv + S.r2), E, ROWS_COMPACT, o.Wqkv_i, o.bqkv_i, dk, dv);
   // dh1 = dh2 + RMS2'(dQKV_i Wqkv_i), the gradients read head-major in place
   a = gemm_base(g, N, E, 3 * E, EPI_RMS_BWD);
   a.A = dq; a.A2 = dk; a.A3 = dv; a.amode = ROWS_ITEM_HM; a.lda = 3 * E;
   a.Bt = f.wt + f.wo.qkv_i; a.resid = dh2; a.aux = (const T*)(sv + S.h1);
   a.rstd_in = (const float*)(sv + S.rs2); a.gamma = prm + o.g2; a.eps = kRmsEps;
-  a.oscale = 1.0f; a.omode = ROWS_COMPACT; a.out = dh1; a.part = f.lnpart;
+  a.oscale = 1.0f; a.omode = ROWS_COMPACT; a.out = dh1; a.part = f.lnpart[1];
   STEP("item_qkv_dx_rms2/mfma", launch_gemm(a, s));
-  STEP("reduce/hbm", launch_reduce_z(tiles, E, E, f.lnpart, grads + o.g2, accumulate, s));
+  G.norm(f.lnpart[1], E, tiles, E, o.g2);
   // feature attention
   T* dof = (T*)(ws + W.tc);
   a = gemm_base(g, N, E, E, EPI_BIAS);
   a.A = dh1; a.lda = E; a.Bt = f.wt + f.wo.o_f; a.out = dof; a.ldo = E;
   STEP("feat_out_dx/mfma", launch_gemm(a, s));
-  CHK(G.run(dh1, E, (const T*)(sv + S.of), E, ROWS_COMPACT, o.Wo_f, o.bo_f));
+  G.linear(dh1, E, (const T*)(sv + S.of), E, ROWS_COMPACT, o.Wo_f, o.bo_f);
   if (feat_attn_mfma_ok(g))
     STEP("feat_attn_bwd/mfma",
          launch_feat_attn_bwd(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
@@ -995,16 +998,16 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   else
     STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
-  CHK(G.run(dqkv, 3 * E, (const T*)(sv + S.r1), E, ROWS_COMPACT, o.Wqkv_f, o.bqkv_f));
+  G.linear(dqkv, 3 * E, (const T*)(sv + S.r1), E, ROWS_COMPACT, o.Wqkv_f, o.bqkv_f);
   // dX = decay (dh1 + RMS1'(dQKV_f Wqkv_f)), native
   a = gemm_base(g, N, E, 3 * E, EPI_RMS_BWD);
   a.A = dqkv; a.lda = 3 * E; a.Bt = f.wt + f.wo.qkv_f; a.resid = dh1;
   a.aux = (const T*)(sv + S.xs); a.rstd_in = (const float*)(sv + S.rs1); a.gamma = prm + o.g1;
-  a.eps = kRmsEps; a.oscale = d.decay; a.omode = ROWS_NATIVE; a.out = dX; a.part = f.lnpart;
+  a.eps = kRmsEps; a.oscale = d.decay; a.omode = ROWS_NATIVE; a.out = dX; a.part = f.lnpart[0];
   STEP("feat_qkv_dx_rms1/mfma", launch_gemm(a, s));
-  STEP("reduce/hbm", launch_reduce_z(tiles, E, E, f.lnpart, grads + o.g1, accumulate, s));
+  G.norm(f.lnpart[0], E, tiles, E, o.g1);
   ZERO_INACTIVE(g, dX);
-  return TFM_OK;
+  return G.finish(accumulate, s);
 }
 
 // ---- forward-only calls ----------------------------------------------------------------------

@@ -4,7 +4,9 @@
 // The reduction runs over the cells (1.6 M at eval scale) while the output is one E x E tile
 // of the weight, so the cells are split into chunks (split-K): workgroup (n-tile, k-tile, z)
 // sums chunk z into a float32 partial, and a second kernel adds the partials in a fixed order
-// (bitwise reproducible).  The MFMA contraction index is the cell, the slow index in memory
+// (bitwise reproducible).  All products of a backward pass are one launch, so that the chip is
+// full with few chunks: on small tables (21,000 cells) the partials of one launch per product
+// were 1.3 GB of writes and reads against 0.1 GB of operands.  The MFMA contraction index is the cell, the slow index in memory
 // for both operands: 32-cell slices of dY and X are copied row-major into LDS with 16-byte
 // stores and read back transposed with ds_read_b64_tr_b16.  Slot t of a lane's 8-element
 // fragment (lane group g = lane / 16) holds cell 16 (t / 4) + 4 g + t % 4 of the slice, for A
@@ -103,52 +105,54 @@ __device__ __forceinline__ void cur_advance(Cursor& c, const Geo& g, int64_t ld,
 }
 }  // namespace
 
-// 512 threads = 8 waves in a 2 (n) x 4 (k) arrangement; tile BN x BK.  dY is in layout YM
-// (compact, native or head-major item gradients), X in layout XM (compact or native).  TBL: the
-// workgroup copies the metadata of the columns its chunk spans into LDS (requires R >= MS, so
-// that a chunk spans at most WGRAD_CHUNK_MAX / MS + 1 columns).
+// LDS of a workgroup: two slices of each operand, and the metadata of the columns its chunk
+// spans.
+constexpr int CT = WGRAD_CHUNK_MAX / MS + 2;
+template <int BN, int BK>
+struct WgradLds {
+  static constexpr int LSA = BN + 16;  // LDS row strides (elements): odd multiples of 32 bytes
+  static constexpr int LSB = BK + 16;
+  __attribute__((aligned(16))) bf16 As[2][MS * LSA];
+  __attribute__((aligned(16))) bf16 Bs[2][MS * LSB];
+  int64_t tcell[CT];
+  int32_t tntr[CT];
+};
+
+// One tile (tx, ty) of one product over chunk zb.  512 threads = 8 waves in a 2 (n) x 4 (k)
+// arrangement; tile BN x BK.  dY is in layout YM (compact, native or head-major item gradients),
+// X in layout XM (compact or native).  TBL: the workgroup copies the metadata of the columns its
+// chunk spans into LDS (requires R >= MS, so that a chunk spans at most WGRAD_CHUNK_MAX / MS + 1
+// columns).
 template <int BN, int BK, int YM, int XM, bool TBL>
-__global__ __launch_bounds__(512) void k_wgrad(WgradArgs a) {
+__device__ __forceinline__ void wgrad_tile(const WgradJob& a, const Geo& g, int64_t M,
+                                           int64_t chunk, int64_t zb, int tx, int ty,
+                                           WgradLds<BN, BK>& L) {
   constexpr int NBW = BN / 32;      // 16-row blocks per wave along n (BN/2 rows)
   constexpr int KBW = BK / 64;      // 16-col blocks per wave along k (BK/4 cols)
-  constexpr int LSA = BN + 16;      // LDS row strides (elements): odd multiples of 32 bytes
-  constexpr int LSB = BK + 16;
+  constexpr int LSA = WgradLds<BN, BK>::LSA, LSB = WgradLds<BN, BK>::LSB;
   constexpr int CPA = BN / 64;      // 16-byte chunks per staging thread and slice (dY)
   constexpr int CPB = BK / 64;      // (X)
-  __shared__ __attribute__((aligned(16))) bf16 As[2][MS * LSA];
-  __shared__ __attribute__((aligned(16))) bf16 Bs[2][MS * LSB];
+  auto& As = L.As;
+  auto& Bs = L.Bs;
 
   const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
   const int lg = lane >> 4, c = lane & 15;
   const int wn = w >> 2, wk = w & 3;
-  // Workgroup -> (cell chunk z, n-tile, k-tile).  The hardware deals consecutive workgroups
-  // round-robin over the 8 XCDs; all tiles of one chunk get consecutive slots of one XCD, so
-  // the chunk's rows come from memory once and are then served by that XCD's L2.
-  const int NX = a.N / BN, NT = NX * (a.K / BK);
-  const int idx = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
-  const int64_t zb = (int64_t)(idx / NT) * 8 + xcd;
-  const int tl = idx % NT;
-  const int tx = tl % NX, ty = tl / NX;
-  const int64_t mb = zb * a.chunk;
-  if (mb >= a.M) return;
+  const int64_t mb = zb * chunk;
   const int n0 = tx * BN, k0 = ty * BK;
-  const int64_t me = mb + a.chunk < a.M ? mb + a.chunk : a.M;
-  const Geo& g = a.g;
+  const int64_t me = mb + chunk < M ? mb + chunk : M;
 
-  constexpr int CT = WGRAD_CHUNK_MAX / MS + 2;
-  __shared__ int64_t tcell[TBL ? CT : 1];
-  __shared__ int32_t tntr[TBL ? CT : 1];
   const int lo = TBL ? (int)(mb / g.R) : 0;
   if (TBL) {
     const int ncol = (int)((me - 1) / g.R) - lo + 1;
     for (int i = tid; i < ncol && i < CT; i += 512) {
-      tcell[i] = g.col_cell0[lo + i];
-      tntr[i] = g.col_ntr[lo + i];
+      L.tcell[i] = g.col_cell0[lo + i];
+      L.tntr[i] = g.col_ntr[lo + i];
     }
     __syncthreads();
   }
-  const int64_t* cell0 = TBL ? tcell : g.col_cell0;
-  const int32_t* ntrp = TBL ? tntr : g.col_ntr;
+  const int64_t* cell0 = TBL ? L.tcell : g.col_cell0;
+  const int32_t* ntrp = TBL ? L.tntr : g.col_ntr;
 
   // staging: threads 0-255 stage dY features [n0, n0+BN), threads 256-511 X features
   // [k0, k0+BK); chunk ch -> cell ch / (width/8) of the slice, features (ch % (width/8)) * 8
@@ -163,9 +167,9 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradArgs a) {
   for (int i = 0; i < CPM; ++i) {
     const int ch = st + 256 * i;
     if (opa) {
-      if (i < CPA) cur_init<YM>(cu[i], g, mb + ch / (BN / 8), me, n0 + (ch % (BN / 8)) * 8, a.ldy);
+      if (i < CPA) cur_init<YM>(cu[i], g, mb + ch / (BN / 8), me, n0 + (ch % (BN / 8)) * 8, a.N);
     } else {
-      if (i < CPB) cur_init<XM>(cu[i], g, mb + ch / (BK / 8), me, k0 + (ch % (BK / 8)) * 8, a.ldx);
+      if (i < CPB) cur_init<XM>(cu[i], g, mb + ch / (BK / 8), me, k0 + (ch % (BK / 8)) * 8, a.K);
     }
   }
   // One role branch around all of a thread's loads (not one per load), so that the other
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradArgs a) {
         bool ok;
         r[i] = cur_load<YM>(cu[i], a.dY, a.dY2, a.dY3, &ok);
         okm |= ok ? 1u << i : 0u;
-        cur_advance<YM>(cu[i], g, a.ldy, n0 + (ch % (BN / 8)) * 8, cell0, ntrp, lo);
+        cur_advance<YM>(cu[i], g, a.N, n0 + (ch % (BN / 8)) * 8, cell0, ntrp, lo);
       }
     } else {
 #pragma unroll
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradArgs a) {
         bool ok;
         r[i] = cur_load<XM>(cu[i], a.X, nullptr, nullptr, &ok);
         okm |= ok ? 1u << i : 0u;
-        cur_advance<XM>(cu[i], g, a.ldx, k0 + (ch % (BK / 8)) * 8, cell0, ntrp, lo);
+        cur_advance<XM>(cu[i], g, a.K, k0 + (ch % (BK / 8)) * 8, cell0, ntrp, lo);
       }
     }
   };
@@ -293,20 +297,42 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradArgs a) {
   }
 }
 
+// Every weight gradient of a backward pass in one launch.  Workgroup -> (cell chunk z, tile over
+// all products).  The hardware deals consecutive workgroups round-robin over the 8 XCDs; all
+// tiles of one chunk get consecutive slots of one XCD, so the chunk's rows come from memory once
+// and are then served by that XCD's L2.
+template <int BN, bool TBL>
+__global__ __launch_bounds__(512) void k_wgrads(WgradArgs a) {
+  __shared__ WgradLds<BN, BN> L;
+  const int idx = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
+  const int64_t zb = (int64_t)(idx / a.tiles) * 8 + xcd;
+  const int tl = idx % a.tiles;
+  if (zb * a.chunk >= a.M) return;
+  int ji = 0;
+  while (ji + 1 < a.n && tl >= a.j[ji + 1].tile0) ++ji;
+  const WgradJob& J = a.j[ji];
+  const int t = tl - J.tile0, ntn = J.N / BN;
+  const int tx = t % ntn, ty = t / ntn;
+  if (J.ymode == ROWS_ITEM_HM)
+    wgrad_tile<BN, BN, ROWS_ITEM_HM, ROWS_COMPACT, TBL>(J, a.g, a.M, a.chunk, zb, tx, ty, L);
+  else if (J.ymode == ROWS_NATIVE)
+    wgrad_tile<BN, BN, ROWS_NATIVE, ROWS_COMPACT, TBL>(J, a.g, a.M, a.chunk, zb, tx, ty, L);
+  else if (J.xmode == ROWS_NATIVE)
+    wgrad_tile<BN, BN, ROWS_COMPACT, ROWS_NATIVE, TBL>(J, a.g, a.M, a.chunk, zb, tx, ty, L);
+  else
+    wgrad_tile<BN, BN, ROWS_COMPACT, ROWS_COMPACT, false>(J, a.g, a.M, a.chunk, zb, tx, ty, L);
+}
+
 // out[i] = (accumulate ? out[i] : 0) + sum over z in [z0, z1) of part[z * stride + i], with
 // z0 = blockIdx.y * zc, z1 = min(Z, z0 + zc), and out advanced by blockIdx.y * out_ystride.  A
 // block owns 32 groups of four consecutive outputs; 8 z-groups of threads each sum z = z0 + zg,
 // z0 + zg + 8, ... with four independent accumulators, combined in a fixed order (bitwise
 // reproducible).  out may be the first partial row of the block's own range (the first pass of
 // a two-pass sum): every read of the range precedes the barrier, every write follows it, and no
-// other block touches the range.  With fg given, output i = n K + k receives
-// sum * fg[k] + sb[n] * fb[k] instead of the sum (the folded LayerNorm affine of the product's
-// input; sb holds the bias-gradient sums).
+// other block touches the range.
 __global__ __launch_bounds__(256) void k_reduce_z(int Z, int zc, int64_t count, int64_t stride,
                                                   const float* part, float* out,
-                                                  int64_t out_ystride, int accumulate,
-                                                  const float* fg, const float* fb,
-                                                  const float* sb, int fK) {
+                                                  int64_t out_ystride, int accumulate) {
   __shared__ float4 red[8][32];
   const int o = threadIdx.x & 31, zg = threadIdx.x >> 5;
   const int64_t i4 = ((int64_t)blockIdx.x * 32 + o) * 4;
@@ -352,84 +378,85 @@ __global__ __launch_bounds__(256) void k_reduce_z(int Z, int zc, int64_t count, 
       t.x += red[k][o].x; t.y += red[k][o].y; t.z += red[k][o].z; t.w += red[k][o].w;
     }
     float tv[4] = {t.x, t.y, t.z, t.w};
-    if (fg) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t i = i4 + k;
-        const int n = (int)(i / fK), kk = (int)(i - (int64_t)n * fK);
-        if (i < count) tv[k] = fmaf(tv[k], fg[kk], sb[n] * fb[kk]);
-      }
-    }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (i4 + k < count) out[i4 + k] = (accumulate ? out[i4 + k] : 0.f) + tv[k];
   }
 }
 
-int64_t wgrad_chunk(int64_t M) {
-  int64_t c = (M + WGRAD_SLOTS - 1) / WGRAD_SLOTS;
+// Square tiles (the two staging roles then move equal chunk counts); E = 256 takes 128 x 128
+// tiles, whose accumulators fit the registers of a 512-thread workgroup.
+static int wgrad_bn(int E) { return E > 192 ? 128 : E; }
+
+static int wgrad_tiles(int E, int H) {
+  const int64_t bn = wgrad_bn(E);
+  return (int)((8LL * E * E + 2LL * E * H) / (bn * bn));
+}
+
+// Chunks asked for at M cells; never falls as M grows.
+static int64_t wgrad_want(int64_t M, int E, int H) {
+  const int T = wgrad_tiles(E, H);
+  // whole rounds of the WGRAD_SLOTS workgroups the chip holds at once, as few as keep a chunk
+  // within WGRAD_CHUNK_MAX; whole multiples of 8 chunks spread evenly over the XCDs
+  int64_t Z = 8;
+  for (int64_t k = 1;; ++k) {
+    Z = WGRAD_SLOTS * k / T / 8 * 8;
+    if (Z >= 8 && (M + Z - 1) / Z <= WGRAD_CHUNK_MAX) break;
+  }
+  // below WGRAD_CHUNK_MIN cells a chunk's partial tile costs more than its operands
+  const int64_t most = (M + WGRAD_CHUNK_MIN - 1) / WGRAD_CHUNK_MIN;
+  return Z < most ? Z : (most > 1 ? most : 1);
+}
+
+WgradSplit wgrad_split(int64_t M, int E, int H) {
+  const int64_t Z = wgrad_want(M, E, H);
+  int64_t c = (M + Z - 1) / Z;
   c = (c + MS - 1) / MS * MS;
   if (c < MS) c = MS;
-  return c < WGRAD_CHUNK_MAX ? c : WGRAD_CHUNK_MAX;
-}
-
-int wgrad_chunks(int64_t M) {
-  const int64_t c = wgrad_chunk(M);
+  if (c > WGRAD_CHUNK_MAX) c = WGRAD_CHUNK_MAX;
   const int64_t z = (M + c - 1) / c;
-  return (int)(z < 1 ? 1 : z);
+  return WgradSplit{(int)(z < 1 ? 1 : z), c};
 }
 
-int64_t wgrad_max_chunks(int64_t Mmax) {
-  const int64_t big = (Mmax + WGRAD_CHUNK_MAX - 1) / WGRAD_CHUNK_MAX;
-  return big > WGRAD_SLOTS ? big : WGRAD_SLOTS;
+size_t wgrad_part_floats(int64_t Mmax, int E, int H) {
+  return (size_t)wgrad_want(Mmax, E, H) *
+         (8 * (size_t)E * E + 2 * (size_t)E * H + 9 * (size_t)E + H);
 }
 
-template <int BN, int BK>
-static hipError_t wgrad_modes(const WgradArgs& b, dim3 grid, hipStream_t s) {
-  const bool yhm = b.ymode == ROWS_ITEM_HM, xnat = b.xmode == ROWS_NATIVE;
-  const bool ynat = b.ymode == ROWS_NATIVE;
-  if (b.ymode != ROWS_COMPACT && !yhm && !ynat) return hipErrorInvalidValue;
-  if (b.xmode != ROWS_COMPACT && !xnat) return hipErrorInvalidValue;
-  if (ynat && xnat) return hipErrorInvalidValue;
-  const bool tbl = b.g.R >= MS;
-  if (ynat) {
-    if (tbl) k_wgrad<BN, BK, ROWS_NATIVE, ROWS_COMPACT, true><<<grid, 512, 0, s>>>(b);
-    else k_wgrad<BN, BK, ROWS_NATIVE, ROWS_COMPACT, false><<<grid, 512, 0, s>>>(b);
-  } else if (yhm && xnat) {
-    if (tbl) k_wgrad<BN, BK, ROWS_ITEM_HM, ROWS_NATIVE, true><<<grid, 512, 0, s>>>(b);
-    else k_wgrad<BN, BK, ROWS_ITEM_HM, ROWS_NATIVE, false><<<grid, 512, 0, s>>>(b);
-  } else if (yhm) {
-    if (tbl) k_wgrad<BN, BK, ROWS_ITEM_HM, ROWS_COMPACT, true><<<grid, 512, 0, s>>>(b);
-    else k_wgrad<BN, BK, ROWS_ITEM_HM, ROWS_COMPACT, false><<<grid, 512, 0, s>>>(b);
-  } else if (xnat) {
-    if (tbl) k_wgrad<BN, BK, ROWS_COMPACT, ROWS_NATIVE, true><<<grid, 512, 0, s>>>(b);
-    else k_wgrad<BN, BK, ROWS_COMPACT, ROWS_NATIVE, false><<<grid, 512, 0, s>>>(b);
-  } else {
-    k_wgrad<BN, BK, ROWS_COMPACT, ROWS_COMPACT, false><<<grid, 512, 0, s>>>(b);
+hipError_t launch_wgrads(WgradArgs& a, const WgradSplit& sp, hipStream_t s) {
+  const int BN = wgrad_bn(a.g.E);
+  a.M = a.g.N;
+  a.chunk = sp.chunk;
+  a.tiles = 0;
+  for (int i = 0; i < a.n; ++i) {
+    WgradJob& J = a.j[i];
+    const bool plain = J.ymode == ROWS_COMPACT || J.xmode == ROWS_COMPACT;
+    if (J.N % BN || J.K % BN || !plain || J.xmode == ROWS_ITEM_HM) return hipErrorInvalidValue;
+    J.tile0 = a.tiles;
+    a.tiles += (J.N / BN) * (J.K / BN);
+  }
+  const dim3 grid((unsigned)(((int64_t)sp.Z + 7) / 8 * 8 * a.tiles));
+  const bool tbl = a.g.R >= MS;
+  switch (BN) {
+    case 64:
+      if (tbl) k_wgrads<64, true><<<grid, 512, 0, s>>>(a);
+      else k_wgrads<64, false><<<grid, 512, 0, s>>>(a);
+      break;
+    case 128:
+      if (tbl) k_wgrads<128, true><<<grid, 512, 0, s>>>(a);
+      else k_wgrads<128, false><<<grid, 512, 0, s>>>(a);
+      break;
+    case 192:
+      if (tbl) k_wgrads<192, true><<<grid, 512, 0, s>>>(a);
+      else k_wgrads<192, false><<<grid, 512, 0, s>>>(a);
+      break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad_mfma(const WgradArgs& a, hipStream_t s) {
-  const int Z = wgrad_chunks(a.M);
-  // Square tiles (the two staging roles then move equal chunk counts); E = 256 takes 128 x 128
-  // tiles, whose accumulators fit the registers of a 512-thread workgroup.
-  const int BN = a.g.E > 192 ? 128 : a.g.E, BK = BN;
-  if (a.N % BN || a.K % BK) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(((int64_t)Z + 7) / 8 * 8 * (a.N / BN) * (a.K / BK)));
-  WgradArgs b = a;
-  b.chunk = wgrad_chunk(a.M);
-  switch (BN) {
-    case 64: return wgrad_modes<64, 64>(b, grid, s);
-    case 128: return wgrad_modes<128, 128>(b, grid, s);
-    case 192: return wgrad_modes<192, 192>(b, grid, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-static hipError_t reduce_z(int Z, int64_t count, int64_t stride, float* part, float* out,
-                           int accumulate, const float* fg, const float* fb, const float* sb,
-                           int fK, hipStream_t s) {
+hipError_t launch_reduce_z(int Z, int64_t count, int64_t stride, float* part, float* out,
+                           int accumulate, hipStream_t s) {
   if (Z <= 0 || count <= 0) return hipSuccess;
   const unsigned bx = (unsigned)((count + 127) / 128);
   // Few output blocks and many partials: first fold groups of ZC partials into the first row
@@ -438,31 +465,12 @@ static hipError_t reduce_z(int Z, int64_t count, int64_t stride, float* part, fl
   if (bx < 512 && Z > 2 * ZC) {
     const unsigned groups = (unsigned)((Z + ZC - 1) / ZC);
     k_reduce_z<<<dim3(bx, groups), 256, 0, s>>>(Z, ZC, count, stride, part, part,
-                                                 (int64_t)ZC * stride, 0, nullptr, nullptr,
-                                                 nullptr, 1);
+                                                 (int64_t)ZC * stride, 0);
     Z = (int)groups;
     stride *= ZC;
   }
-  k_reduce_z<<<dim3(bx, 1), 256, 0, s>>>(Z, Z, count, stride, part, out, 0, accumulate, fg, fb,
-                                         sb, fK);
+  k_reduce_z<<<dim3(bx, 1), 256, 0, s>>>(Z, Z, count, stride, part, out, 0, accumulate);
   return hipGetLastError();
-}
-
-hipError_t launch_reduce_z(int Z, int64_t count, int64_t stride, float* part, float* out,
-                           int accumulate, hipStream_t s) {
-  return reduce_z(Z, count, stride, part, out, accumulate, nullptr, nullptr, nullptr, 1, s);
-}
-
-hipError_t launch_reduce_wfold(int Z, int N, int K, float* wpart, float* bpart,
-                               const float* gamma, const float* beta, float* grad,
-                               int accumulate, hipStream_t s) {
-  if (Z <= 0 || N <= 0 || K <= 0) return hipSuccess;
-  // the bias sums first, into the first partial row of bpart (in place), which the folded
-  // weight sums then read
-  hipError_t e = reduce_z(Z, N, N, bpart, bpart, 0, nullptr, nullptr, nullptr, 1, s);
-  if (e != hipSuccess) return e;
-  return reduce_z(Z, (int64_t)N * K, (int64_t)N * K, wpart, grad, accumulate, gamma, beta, bpart,
-                  K, s);
 }
 
 }  // namespace tfm
