@@ -99,11 +99,6 @@ WOff weight_offsets(int E, int H);
 struct WFold {
   const float *g1, *be1, *bqkv_i, *g2, *be2, *b1;
 };
-// w: the six matrices in packed order (the fold applied to Wqkv_i and W1 when given, and the
-// folded biases written at fb); wt: each matrix transposed, never folded
-hipError_t launch_weight_prep(const float* params, int E, int H, bf16* w, bf16* wt,
-                              const WFold* fold, hipStream_t s);
-
 // Writes 0 to every element (elt bytes each) of the native tensor that lies in an inactive cell.
 hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStream_t s);
 
@@ -166,7 +161,7 @@ hipError_t launch_ln_out_bwd(const Geo& g, const bf16* dY, const bf16* xhat, con
 
 // The MLP half of the post-norm block, forward, in one kernel (csrc/mlp.hip): item
 // out-projection + residual + LN2, MLP up-projection, GELU and down-projection with the hidden
-// layer in registers, residual + LN3.  Reads the weight stream that launch_mlp_fwd_stream
+// layer in registers, residual + LN3.  Reads the weight stream that launch_setup
 // builds (mlp_fwd_stream_elems(E, H) bf16 elements).
 struct MlpFwdArgs {
   int64_t M;            // active cells
@@ -185,9 +180,9 @@ struct MlpFwdArgs {
   Geo g;
 };
 bool mlp_fused_ok(int E, int H);
-int64_t mlp_fwd_stream_elems(int E, int H);
-hipError_t launch_mlp_fwd_stream(const float* wo, const float* w1, const float* g2,
-                                 const float* w2, int E, int H, bf16* out, hipStream_t s);
+__host__ __device__ inline int64_t mlp_fwd_stream_elems(int E, int H) {
+  return (int64_t)(E / 64 + H / 32) * (E / 8) * 512;
+}
 hipError_t launch_mlp_fwd(const MlpFwdArgs& a, hipStream_t s);
 
 // Backward of the same sub-block in one kernel (csrc/mlp.hip): LN3' from the native dY, the MLP
@@ -211,10 +206,10 @@ struct MlpBwdArgs {
   float* part;          // [mlp_bwd_tiles(M)][4 E]
   Geo g;
 };
-int64_t mlp_bwd_stream_elems(int E, int H);
+__host__ __device__ inline int64_t mlp_bwd_stream_elems(int E, int H) {
+  return (int64_t)(H / 32) * (3 * E / 16) * 512;
+}
 int64_t mlp_bwd_tiles(int64_t M);
-hipError_t launch_mlp_bwd_stream(const float* w1, const float* g2, const float* w2, int E, int H,
-                                 bf16* out, hipStream_t s);
 hipError_t launch_mlp_bwd(const MlpBwdArgs& a, hipStream_t s);
 
 // Floats of one norm's column partials for up to `cells` cells: [64-cell tiles][2 E], which also

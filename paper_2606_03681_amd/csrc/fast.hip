@@ -24,66 +24,6 @@ WOff weight_offsets(int E, int H) {
   return o;
 }
 
-// One thread per weight element: src (fp32, packed parameter order) -> w (same layout, bf16)
-// and wt (each matrix transposed, bf16).
-__global__ void k_weight_prep(const float* __restrict__ p, int E, int H, WOff wo,
-                              bf16* __restrict__ w, bf16* __restrict__ wt, WFold fold,
-                              int folded) {
-  // packed parameter offsets of the six matrices
-  const int64_t E2 = (int64_t)E * E;
-  const int64_t src[6] = {0, 3 * E2 + 3 * E, 4 * E2 + 4 * E, 7 * E2 + 7 * E, 8 * E2 + 8 * E,
-                          8 * E2 + 8 * E + (int64_t)H * E + H};
-  const int64_t dst[6] = {wo.qkv_f, wo.o_f, wo.qkv_i, wo.o_i, wo.w1, wo.w2};
-  const int rows[6] = {3 * E, E, 3 * E, E, H, E};
-  const int cols[6] = {E, E, E, E, E, H};
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int k = 0; k < 6; ++k) {
-    int64_t n = (int64_t)rows[k] * cols[k];
-    if (t < n) {
-      int r = (int)(t / cols[k]), c = (int)(t % cols[k]);
-      const float x = p[src[k] + t];
-      const uint16_t v = f2bf(x);
-      // the fold scales input column c of Wqkv_i by g1[c] and of W1 by g2[c]
-      w[dst[k] + t] = folded && (k == 2 || k == 4) ? f2bf(x * (k == 2 ? fold.g1 : fold.g2)[c]) : v;
-      wt[dst[k] + (int64_t)c * rows[k] + r] = v;
-      return;
-    }
-    t -= n;
-  }
-}
-
-// Folded biases, one wave per output: bqkv_i[n] + sum_k Wqkv_i[n][k] be1[k] for n < 3E, then
-// b1[m] + sum_k W1[m][k] be2[k]; float32, lane l summing k = l, l + 64, ... (a coalesced read of
-// the weight row), then the lanes' sums added in a fixed butterfly.
-__global__ void k_fold_bias(const float* __restrict__ p, int E, int H, WFold fold,
-                            float* __restrict__ fb) {
-  const int n = blockIdx.x * 4 + wave_id();
-  if (n >= 3 * E + H) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t E2 = (int64_t)E * E;
-  const bool q = n < 3 * E;
-  const int m = q ? n : n - 3 * E;
-  const float* row = p + (q ? 4 * E2 + 4 * E : 8 * E2 + 8 * E) + (int64_t)m * E;
-  const float* be = q ? fold.be1 : fold.be2;
-  float acc = 0.f;
-  for (int k = lane; k < E; k += 64) acc = fmaf(row[k], be[k], acc);
-  acc = wave_reduce_sum(acc);
-  if (lane == 0) fb[n] = (q ? fold.bqkv_i : fold.b1)[m] + acc;
-}
-
-hipError_t launch_weight_prep(const float* params, int E, int H, bf16* w, bf16* wt,
-                              const WFold* fold, hipStream_t s) {
-  WOff wo = weight_offsets(E, H);
-  unsigned grid = (unsigned)((wo.fb + 255) / 256);
-  k_weight_prep<<<grid, 256, 0, s>>>(params, E, H, wo, w, wt, fold ? *fold : WFold{}, fold != nullptr);
-  if (fold) {
-    const int n = 3 * E + H;
-    k_fold_bias<<<(n + 3) / 4, 256, 0, s>>>(params, E, H, *fold,
-                                                reinterpret_cast<float*>(w + wo.fb));
-  }
-  return hipGetLastError();
-}
-
 // One wave per native row (b, r): the row's S cells are S * per contiguous 16-byte pieces,
 // written with consecutive lanes on consecutive pieces, zero where the piece's cell is
 // inactive.  Rows of datasets with every cell active leave at once.

@@ -35,7 +35,6 @@ namespace {
 
 // k position of slot j (0..7) of lane group g in a B fragment that two D blocks form:
 // values 4 g .. 4 g + 3 of the first block, then of the second (16 + ...).
-__device__ __forceinline__ int perm_k(int g, int j) { return j < 4 ? 4 * g + j : 16 + 4 * g + (j - 4); }
 
 __device__ __forceinline__ f32x4 unpack4(uint32_t lo, uint32_t hi) {
   f32x4 r;
@@ -56,48 +55,6 @@ __device__ __forceinline__ f32x4 lds4(const float* p) {
 __device__ __forceinline__ float sum4(const f32x4& v) { return (v[0] + v[1]) + (v[2] + v[3]); }
 
 }  // namespace
-
-// ----------------------------------------------------------------------------- weight stream
-// One thread per bf16 element of the stream (see the file comment for the order).
-__global__ void k_mlp_fwd_stream(const float* __restrict__ wo, const float* __restrict__ w1,
-                                 const float* __restrict__ g2, const float* __restrict__ w2,
-                                 int E, int H, bf16* __restrict__ out) {
-  const int NE = E / 16, NK = E / 32, FPS = 2 * NE;  // fragments per stage
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)(NK / 2 + H / 32) * FPS * 512;
-  if (t >= total) return;
-  const int j = (int)(t & 7), lane = (int)((t >> 3) & 63);
-  const int64_t f = t >> 9;  // fragment index in the stream
-  const int st = (int)(f / FPS), fi = (int)(f % FPS);
-  const int g = lane >> 4, r = lane & 15;
-  float v;
-  if (st < NK / 2) {  // Wo_i: rows = output features, k = input features (natural order)
-    const int kk = fi / NE, eb = fi % NE;
-    const int row = eb * 16 + r, k = (2 * st + kk) * 32 + 8 * g + j;
-    v = wo[(int64_t)row * E + k];
-  } else {
-    const int c = st - NK / 2;
-    if (fi < 2 * NK) {  // W1' = W1 diag(g2): rows = hidden units, k = features (permuted)
-      const int hb = fi / NK, ks = fi % NK;
-      const int row = c * 32 + hb * 16 + r, k = ks * 32 + perm_k(g, j);
-      v = w1[(int64_t)row * E + k] * g2[k];
-    } else {  // W2: rows = output features, k = the chunk's hidden units (permuted)
-      const int eb = fi - 2 * NK;
-      const int row = eb * 16 + r, k = c * 32 + perm_k(g, j);
-      v = w2[(int64_t)row * H + k];
-    }
-  }
-  out[t] = f2bf(v);
-}
-
-int64_t mlp_fwd_stream_elems(int E, int H) { return (int64_t)(E / 64 + H / 32) * (E / 8) * 512; }
-
-hipError_t launch_mlp_fwd_stream(const float* wo, const float* w1, const float* g2,
-                                 const float* w2, int E, int H, bf16* out, hipStream_t s) {
-  const int64_t n = mlp_fwd_stream_elems(E, H);
-  k_mlp_fwd_stream<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(wo, w1, g2, w2, E, H, out);
-  return hipGetLastError();
-}
 
 // ----------------------------------------------------------------------------- forward
 // A workgroup: NW waves of CB 16-cell blocks each (every weight fragment read from LDS feeds CB
@@ -323,39 +280,6 @@ __global__ __launch_bounds__(MLP_NW * 64, 2) void k_mlp_fwd(MlpFwdArgs a) {
 // as B fragments and as the per-feature operands of the norms.  Weight stream per 32 hidden
 // units: W1' (units x features), W2^T (units x features), both with permuted feature columns,
 // then W1^T (features x the chunk's units, permuted unit columns).
-__global__ void k_mlp_bwd_stream(const float* __restrict__ w1, const float* __restrict__ g2,
-                                 const float* __restrict__ w2, int E, int H,
-                                 bf16* __restrict__ out) {
-  const int NE = E / 16, NK = E / 32, FPS = 4 * NK + NE;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)(H / 32) * FPS * 512;
-  if (t >= total) return;
-  const int j = (int)(t & 7), lane = (int)((t >> 3) & 63);
-  const int64_t f = t >> 9;
-  const int c = (int)(f / FPS), fi = (int)(f % FPS);
-  const int g = lane >> 4, r = lane & 15;
-  float v;
-  if (fi < 4 * NK) {
-    const int part = fi / (2 * NK), hb = (fi % (2 * NK)) / NK, ks = fi % NK;
-    const int u = c * 32 + hb * 16 + r, k = ks * 32 + perm_k(g, j);
-    v = part == 0 ? w1[(int64_t)u * E + k] * g2[k] : w2[(int64_t)k * H + u];
-  } else {
-    const int eb = fi - 4 * NK;
-    const int e = eb * 16 + r, u = c * 32 + perm_k(g, j);
-    v = w1[(int64_t)u * E + e];
-  }
-  out[t] = f2bf(v);
-}
-
-int64_t mlp_bwd_stream_elems(int E, int H) { return (int64_t)(H / 32) * (3 * E / 16) * 512; }
-
-hipError_t launch_mlp_bwd_stream(const float* w1, const float* g2, const float* w2, int E, int H,
-                                 bf16* out, hipStream_t s) {
-  const int64_t n = mlp_bwd_stream_elems(E, H);
-  k_mlp_bwd_stream<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(w1, g2, w2, E, H, out);
-  return hipGetLastError();
-}
-
 constexpr int MB_NW = 12, MB_TILE = MB_NW * 16;
 
 int64_t mlp_bwd_tiles(int64_t M) { return (M + MB_TILE - 1) / MB_TILE; }

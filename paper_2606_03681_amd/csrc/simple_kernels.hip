@@ -51,40 +51,6 @@ hipError_t launch_upload(const int32_t* host, int64_t count, int32_t* dst, hipSt
   return hipSuccess;
 }
 
-__global__ void k_expand_meta(const int32_t* blob, int B, int R, int S, int W, DsInfo* ds,
-                              int32_t* col_ds, int32_t* col_c, int32_t* colmap,
-                              int64_t* col_cell0, int32_t* col_ntr) {
-  int64_t t = gtid();
-  if (t >= (int64_t)B * S) return;
-  int b = (int)(t / S), c = (int)(t % S);
-  const int32_t* e = blob + (int64_t)b * (3 + W);
-  const uint32_t* bits = (const uint32_t*)(e + 3);
-  if (c == 0) ds[b] = DsInfo{e[0], e[1], e[2], 0};
-  bool on = (bits[c >> 5] >> (c & 31)) & 1u;
-  if (!on) {
-    colmap[t] = -1;
-    return;
-  }
-  int k = 0;
-  for (int w = 0; w < (c >> 5); ++w) k += __popc(bits[w]);
-  k += __popc(bits[c >> 5] & ((1u << (c & 31)) - 1u));
-  int gcol = e[1] + k;
-  col_ds[gcol] = b;
-  col_c[gcol] = c;
-  colmap[t] = gcol;
-  col_cell0[gcol] = (int64_t)b * R * S + c;
-  col_ntr[gcol] = e[0];
-}
-
-hipError_t launch_expand_meta(const int32_t* blob, int B, int R, int S, int words, DsInfo* ds,
-                              int32_t* col_ds, int32_t* col_c, int32_t* colmap,
-                              int64_t* col_cell0, int32_t* col_ntr, hipStream_t s) {
-  k_expand_meta<<<grid_for((int64_t)B * S), TFM_BLOCK, 0, s>>>(blob, B, R, S, words, ds, col_ds,
-                                                                 col_c, colmap, col_cell0,
-                                                                 col_ntr);
-  return hipGetLastError();
-}
-
 // ============================================================================ column sums
 template <class T>
 __global__ void k_colsum(int64_t M, int Nj, const T* __restrict__ A, int64_t lda,

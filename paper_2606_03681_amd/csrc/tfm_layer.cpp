@@ -21,6 +21,7 @@
 #include "fast.h"
 #include "prof.h"
 #include "reduce.h"
+#include "setup.h"
 #include "static_scratch.h"
 
 namespace {
@@ -143,7 +144,7 @@ struct MetaOff {
 
 MetaOff take_meta(const Dims& d, Arena& a) {
   MetaOff L;
-  L.blob = a.take((size_t)d.B * (3 + d.words) * 4);
+  L.blob = a.take((size_t)d.B * (4 + d.words) * 4);
   L.ds = a.take((size_t)d.B * sizeof(tfm::DsInfo));
   L.col_ds = a.take((size_t)d.B * d.S * 4);
   L.col_c = a.take((size_t)d.B * d.S * 4);
@@ -270,7 +271,16 @@ bool aligned(const void* p) { return p && ((uintptr_t)p % 16) == 0; }
 struct Plan {
   int NC = 0;
   int nmax = 0;  // longest train prefix
+  // per dataset: n_train, first active column, active columns, first place in the column order
+  // of the item-attention backward (below), mask words
   std::vector<int32_t> blob;
+  int stride = 0;
+  // Column order of the item-attention backward: the columns of datasets whose train prefix
+  // fits the one-kernel form first (nF of them, longest prefix nmaxF), then the others; within
+  // each group the longer prefixes first, so the largest problems start earliest and the
+  // launches end evenly.  natural: one group, in the order of the columns.
+  int nF = 0, nmaxF = 0;
+  bool natural = true;
 };
 
 // nt_max: the largest allowed n_train (R, or the context rows of a query call).
@@ -278,7 +288,8 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
               int nt_max = -1) {
   if (nt_max < 0) nt_max = d.R;
   if (!n_train || !mask) return fail(TFM_ERR_POINTER, "n_train or cell_mask is null");
-  P.blob.assign((size_t)d.B * (3 + d.words), 0);
+  P.stride = 4 + d.words;
+  P.blob.assign((size_t)d.B * P.stride, 0);
   int col = 0;
   for (int b = 0; b < d.B; ++b) {
     if (n_train[b] < 1 || n_train[b] > nt_max)
@@ -286,21 +297,45 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
     const uint8_t* m = mask + (size_t)b * d.S;
     if (!m[d.C]) return fail(TFM_ERR_MASK, "target cell (index C=%d) of dataset %d inactive",
                              d.C, b);
-    int32_t* e = &P.blob[(size_t)b * (3 + d.words)];
+    int32_t* e = &P.blob[(size_t)b * P.stride];
     int cnt = 0;
     for (int c = 0; c < d.S; ++c)
       if (m[c]) {
         ++cnt;
-        e[3 + (c >> 5)] |= (int32_t)(1u << (c & 31));
+        e[4 + (c >> 5)] |= (int32_t)(1u << (c & 31));
       }
     e[0] = n_train[b];
     if (n_train[b] > P.nmax) P.nmax = n_train[b];
-    e[1] = col;
+    e[1] = e[3] = col;
     e[2] = cnt;
     col += cnt;
   }
   P.NC = col;
   return TFM_OK;
+}
+
+// Orders the columns for the item-attention backward at head width d.
+void order_columns(const Dims& d, Plan& P) {
+  const int fmax = tfm::item_attn_bwd_fused_max_rows(d.d);
+  std::vector<int> order(d.B);
+  std::iota(order.begin(), order.end(), 0);
+  auto rec = [&](int b) { return &P.blob[(size_t)b * P.stride]; };
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+    const bool fx = rec(x)[0] <= fmax, fy = rec(y)[0] <= fmax;
+    return fx != fy ? fx : rec(x)[0] > rec(y)[0];
+  });
+  int place = 0;
+  for (int b : order) {
+    int32_t* e = rec(b);
+    e[3] = place;
+    place += e[2];
+    P.natural = P.natural && e[3] == e[1];
+    if (e[0] <= fmax) {
+      P.nF += e[2];
+      P.nmaxF = std::max(P.nmaxF, e[0]);
+    }
+  }
+  P.natural = P.natural && (P.nF == 0 || P.nF == P.NC);
 }
 
 #define HIPCHK(...)                                                                     \
@@ -330,64 +365,36 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
     if (rc_ != TFM_OK) return rc_;   \
   } while (0)
 
+// Plan and (w not null) weights on the device, in one launch; g describes them.
 int setup_geo(const Dims& d, const Plan& P, char* ws, const MetaOff& W, tfm::Geo& g,
-              hipStream_t s) {
-  int32_t* blob = (int32_t*)(ws + W.blob);
+              const tfm::SetupWeights* w, hipStream_t s) {
   g.B = d.B; g.R = d.R; g.S = d.S; g.E = d.E; g.heads = d.heads; g.d = d.d; g.H = d.H;
   g.NC = P.NC;
   g.nmax = P.nmax;
   g.N = (int64_t)P.NC * d.R;
-  g.ds = (const tfm::DsInfo*)(ws + W.ds);
-  g.col_ds = (const int32_t*)(ws + W.col_ds);
-  g.col_c = (const int32_t*)(ws + W.col_c);
-  g.colmap = (const int32_t*)(ws + W.colmap);
-  g.col_cell0 = (const int64_t*)(ws + W.col_cell0);
-  g.col_ntr = (const int32_t*)(ws + W.col_ntr);
-  HIPCHK(tfm::launch_upload(P.blob.data(), (int64_t)P.blob.size(), blob, s));
-  HIPCHK(tfm::launch_expand_meta(blob, d.B, d.R, d.S, d.words, (tfm::DsInfo*)(ws + W.ds),
-                                 (int32_t*)(ws + W.col_ds), (int32_t*)(ws + W.col_c),
-                                 (int32_t*)(ws + W.colmap), (int64_t*)(ws + W.col_cell0),
-                                 (int32_t*)(ws + W.col_ntr), s));
+  tfm::SetupPlan p{};
+  p.B = d.B; p.R = d.R; p.S = d.S; p.words = d.words; p.blob = P.blob.data();
+  p.dblob = (int32_t*)(ws + W.blob);
+  g.ds = p.ds = (tfm::DsInfo*)(ws + W.ds);
+  g.col_ds = p.col_ds = (int32_t*)(ws + W.col_ds);
+  g.col_c = p.col_c = (int32_t*)(ws + W.col_c);
+  g.colmap = p.colmap = (int32_t*)(ws + W.colmap);
+  g.col_cell0 = p.col_cell0 = (int64_t*)(ws + W.col_cell0);
+  g.col_ntr = p.col_ntr = (int32_t*)(ws + W.col_ntr);
+  p.cord = (int32_t*)(ws + W.cord);
+  STEP("setup/hbm", tfm::launch_setup(p, w, s));
   return TFM_OK;
 }
 
-// Item-attention backward on the MFMA path.  The columns of datasets whose train prefix fits
-// the one-kernel form go through it, the others through the dQ and dK/dV kernels; within each
-// group the columns of longer prefixes come first, so the largest problems start earliest and
-// the launches end evenly.  The column order is uploaded only when it is not the natural one.
+// Item-attention backward on the MFMA path, in the plan's column order: one-kernel columns, then
+// the others through the dQ and dK/dV kernels.
 int item_attn_bwd(const Dims& d, const tfm::Geo& g, const Plan& P, char* ws, const MetaOff& M,
                   const tfm::bf16* qi, const tfm::bf16* ki, const tfm::bf16* vi,
                   const tfm::bf16* oi, const tfm::bf16* doi, const float* lsei, float* Dq,
                   tfm::bf16* dq, tfm::bf16* dk, tfm::bf16* dv, hipStream_t s) {
   using namespace tfm;
-  const int fmax = item_attn_bwd_fused_max_rows(d.d);
-  const int stride = 3 + d.words;
-  std::vector<int> order(d.B);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    return P.blob[(size_t)x * stride] > P.blob[(size_t)y * stride];
-  });
-  std::vector<int32_t> cols;
-  cols.reserve(P.NC);
-  int nF = 0, nmaxF = 0;
-  for (int pass = 0; pass < 2; ++pass)
-    for (int b : order) {
-      const int32_t* e = &P.blob[(size_t)b * stride];
-      const bool fused = e[0] <= fmax;
-      if (fused != (pass == 0)) continue;
-      for (int k = 0; k < e[2]; ++k) cols.push_back(e[1] + k);
-      if (fused) {
-        nF += e[2];
-        nmaxF = std::max(nmaxF, e[0]);
-      }
-    }
-  bool natural = nF == 0 || nF == P.NC;  // a single group in the natural column order
-  for (int i = 0; i < P.NC && natural; ++i) natural = cols[i] == i;
-  int32_t* dcols = nullptr;
-  if (!natural) {
-    dcols = (int32_t*)(ws + M.cord);
-    HIPCHK(launch_upload(cols.data(), P.NC, dcols, s));
-  }
+  const int32_t* dcols = P.natural ? nullptr : (const int32_t*)(ws + M.cord);
+  const int nF = P.nF, nmaxF = P.nmaxF;
   const ColList F{dcols, nF};
   const ColList T{dcols ? dcols + nF : nullptr, P.NC - nF};
   if (nF > 0)
@@ -642,6 +649,31 @@ int feat_fwd(const tfm::Geo& g, const tfm::bf16* x, int xmode, const float* bqkv
   return TFM_OK;
 }
 
+// What the setup of a forward or backward call on the MFMA path prepares: the matrices it reads
+// as stored (forward) or transposed (backward), the LayerNorm folds of the post-norm block, and
+// the fused MLP's weight stream in place of the matrices that are in it.  The fused backward
+// recomputes G with the folded up-projection bias.
+tfm::SetupWeights setup_weights(const Dims& d, const float* prm, const FastWs& f, bool bwd) {
+  const POff o = param_offsets(d.E, d.H, d.block);
+  tfm::SetupWeights w{};
+  w.params = prm; w.E = d.E; w.H = d.H;
+  w.wout = f.w; w.wtout = f.wt;
+  const bool post = d.block == TFM_BLOCK_POSTNORM;
+  const bool fused = post && tfm::mlp_fused_ok(d.E, d.H);
+  if (post) w.f = tfm::WFold{prm + o.g1, prm + o.be1, prm + o.bqkv_i, prm + o.g2, prm + o.be2,
+                             prm + o.b1};
+  if (!bwd) {
+    w.w = fused ? 0x07 : 0x3f;  // Wqkv_f, Wo_f, Wqkv_i; Wo_i, W1, W2 unless in the stream
+    w.fold = post;
+    w.stream = fused ? 1 : 0;
+  } else {
+    w.wt = fused ? 0x0f : 0x3f;
+    w.fold = fused;
+    w.stream = fused ? 2 : 0;
+  }
+  return w;
+}
+
 int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* prm,
              tfm::bf16* Y, const FwdBufs& b, const FastWs& f, hipStream_t s) {
   using namespace tfm;
@@ -649,9 +681,7 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
   const int E = d.E, H = d.H;
   const int64_t N = g.N;
   // H1 and H2 are kept as their x-hat only: the affines of LN1 and LN2 are folded into the
-  // products that read them (weights and biases) and into the residual reads
-  const WFold fold{prm + o.g1, prm + o.be1, prm + o.bqkv_i, prm + o.g2, prm + o.be2, prm + o.b1};
-  STEP("weight_prep/hbm", launch_weight_prep(prm, E, H, f.w, f.wt, &fold, s));
+  // products that read them (weights and biases, by the setup) and into the residual reads
   const float* fb = reinterpret_cast<const float*>(f.w + f.wo.fb);
   // feature Q|K|V from the native cells, and the feature attention
   STEP_ERR(feat_fwd(g, X, ROWS_NATIVE, prm + o.bqkv_f, b, f, s));
@@ -672,8 +702,6 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
   if (mlp_fused_ok(E, H)) {
     // out-projection + LN2, MLP and LN3 in one kernel, the hidden layer in registers
     bf16* ms = f.w + f.wo.ms;
-    STEP("mlp_stream/hbm",
-         launch_mlp_fwd_stream(prm + o.Wo_i, prm + o.W1, prm + o.g2, prm + o.W2, E, H, ms, s));
     MlpFwdArgs m{};
     m.M = N; m.oi = b.oi; m.xh1 = b.h1; m.ws = ms;
     m.bo = prm + o.bo_i; m.g1 = prm + o.g1; m.be1 = prm + o.be1; m.g2 = prm + o.g2;
@@ -764,10 +792,6 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
   const int tiles = (int)tfm::gemm_tiles(tfm::EPI_LN_BWD, E, N);
   FastGrads G(d, g, f, grads);
   const bool fused_mlp = mlp_fused_ok(E, H);
-  // the backward reads the transposed copies only; the fold (x-hat2's affine in W1 and b1)
-  // gives the fused MLP backward the folded up-projection bias it recomputes G with
-  const WFold fold{prm + o.g1, prm + o.be1, prm + o.bqkv_i, prm + o.g2, prm + o.be2, prm + o.b1};
-  STEP("weight_prep/hbm", launch_weight_prep(prm, E, H, f.w, f.wt, fused_mlp ? &fold : nullptr, s));
   T* dz3 = (T*)(ws + W.tb);
   T* dz2 = (T*)(ws + W.te);
   T* dz1 = (T*)(ws + W.tf);
@@ -780,8 +804,6 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
     // LN3 and LN2 weight and bias gradients (each pair adjacent in the packed order)
     T* ub = (T*)(ws + W.th2);
     bf16* ms = f.w + f.wo.ms;
-    STEP("mlp_stream/hbm",
-         launch_mlp_bwd_stream(prm + o.W1, prm + o.g2, prm + o.W2, E, H, ms, s));
     MlpBwdArgs m{};
     m.M = N; m.dy = dY; m.xh3 = (const T*)(sv + S.xh3); m.rs3 = (const float*)(sv + S.rs3);
     m.xh2 = xh2; m.rs2 = (const float*)(sv + S.rs2); m.ws = ms;
@@ -889,7 +911,6 @@ int fwd_pre(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* p
   const POff o = param_offsets(d.E, d.H, d.block);
   const int E = d.E, H = d.H;
   const int64_t N = g.N;
-  STEP("weight_prep/hbm", launch_weight_prep(prm, E, H, f.w, f.wt, nullptr, s));
   // x' = decay X, r1 = RMS1(x')
   STEP("rms_in/hbm", launch_rms_in(g, X, d.decay, prm + o.g1, kRmsEps, b.xs, b.r1, b.rs1, s));
   STEP_ERR(feat_fwd(g, b.r1, ROWS_COMPACT, prm + o.bqkv_f, b, f, s));
@@ -938,7 +959,6 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   const int64_t N = g.N;
   const int tiles = (int)tfm::gemm_tiles(tfm::EPI_RMS_BWD, E, N);
   FastGrads G(d, g, f, grads);
-  STEP("weight_prep/hbm", launch_weight_prep(prm, E, H, f.w, f.wt, nullptr, s));
   T* dh2 = (T*)(ws + W.te);
   T* dh1 = (T*)(ws + W.tf);
   T* dgb = (T*)(ws + W.th1);
@@ -1126,12 +1146,13 @@ int infer_call(const tfm_dims* dims, int ctx_rows, const int32_t* n_train,
   if (rc) return rc;
   char* ws = (char*)workspace;
   tfm::Geo g;
-  rc = setup_geo(d, P, ws, L.meta, g, s);
+  const FastWs f = infer_fast_ws(d, ws, L);
+  const tfm::SetupWeights sw = setup_weights(d, params, f, false);
+  rc = setup_geo(d, P, ws, L.meta, g, &sw, s);
   if (rc) return rc;
   tfm::bf16* kc = (tfm::bf16*)cache;
   tfm::bf16* vc = (tfm::bf16*)((char*)cache + cache_half(dc));
   const FwdBufs b = infer_bufs(d, ws, L, kc, vc, query, query ? ctx_rows : d.R);
-  const FastWs f = infer_fast_ws(d, ws, L);
   if (d.block == TFM_BLOCK_PRENORM)
     return fwd_pre(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y, b, f, s);
   return fwd_fast(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y, b, f, s);
@@ -1198,16 +1219,23 @@ int tfm_layer_fwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* c
   char* ws = (char*)workspace;
   char* sv = (char*)saved;
   tfm::Geo g;
-  rc = setup_geo(d, P, ws, W.meta, g, s);
+  const bool fast = fast_eligible(d);
+  FastWs f{};
+  tfm::SetupWeights sw{};
+  if (fast) {
+    f = fast_ws(d, ws, W);
+    sw = setup_weights(d, params, f, false);
+  }
+  rc = setup_geo(d, P, ws, W.meta, g, fast ? &sw : nullptr, s);
   if (rc) return rc;
   if (d.block == TFM_BLOCK_PRENORM)
     return fwd_pre(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y,
-                   bufs_from_pre_saved(sv, pre_saved_layout(d)), fast_ws(d, ws, W), s);
+                   bufs_from_pre_saved(sv, pre_saved_layout(d)), f, s);
   if (d.dtype == TFM_F32)
     return fwd_simple<float>(d, g, (const float*)X, params, (float*)Y, sv, S, ws, W, s);
-  if (fast_eligible(d))
-    return fwd_fast(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y, bufs_from_saved(sv, S),
-                    fast_ws(d, ws, W), s);
+  if (fast)
+    return fwd_fast(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y, bufs_from_saved(sv, S), f,
+                    s);
   return fwd_simple<tfm::bf16>(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y, sv, S, ws, W,
                                s);
 }
@@ -1237,7 +1265,13 @@ int tfm_layer_bwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* c
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
   tfm::Geo g;
-  rc = setup_geo(d, P, ws, W.meta, g, s);
+  const bool fast = fast_eligible(d);
+  tfm::SetupWeights sw{};
+  if (fast) {
+    order_columns(d, P);
+    sw = setup_weights(d, params, fast_ws(d, ws, W), true);
+  }
+  rc = setup_geo(d, P, ws, W.meta, g, fast ? &sw : nullptr, s);
   if (rc) return rc;
   if (d.block == TFM_BLOCK_PRENORM)
     return bwd_pre(d, g, P, params, (const char*)saved, pre_saved_layout(d),
@@ -1245,7 +1279,7 @@ int tfm_layer_bwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* c
   if (d.dtype == TFM_F32)
     return bwd_simple<float>(d, g, (const float*)X, params, (const char*)saved, S,
                              (const float*)dY, (float*)dX, grads, accumulate, ws, W, s);
-  if (fast_eligible(d))
+  if (fast)
     return bwd_fast(d, g, P, (const tfm::bf16*)X, params, (const char*)saved, S,
                     (const tfm::bf16*)dY, (tfm::bf16*)dX, grads, accumulate, ws, W, s);
   return bwd_simple<tfm::bf16>(d, g, (const tfm::bf16*)X, params, (const char*)saved, S,
@@ -1284,13 +1318,14 @@ int tfm_layer_fwd_noalloc(const tfm_dims* dims, const int32_t* n_train, const ui
   void* base = nullptr;
   HIPCHK(tfm::static_scratch(s, &base));
   char* ws = (char*)base;
-  tfm::Geo g;
-  rc = setup_geo(d, P, ws, M, g, s);
-  if (rc) return rc;
   FastWs f{};
   f.wo = wo;
   f.w = (tfm::bf16*)(ws + w_off);
   f.wt = (tfm::bf16*)(ws + wt_off);
+  const tfm::SetupWeights sw = setup_weights(d, params, f, false);
+  tfm::Geo g;
+  rc = setup_geo(d, P, ws, M, g, &sw, s);
+  if (rc) return rc;
   char* sv = (char*)saved;
   if (d.block == TFM_BLOCK_PRENORM)
     return fwd_pre(d, g, (const tfm::bf16*)X, params, (tfm::bf16*)Y,
@@ -1319,7 +1354,7 @@ static int thinking_setup(const tfm_dims* dims, const int32_t* n_train, const ui
     if (T < 1 || T > n_train[b])
       return fail(TFM_ERR_DIMS, "T=%d thinking rows outside [1, n_train[%d]=%d]", T, b,
                   n_train[b]);
-  return setup_geo(d, P, (char*)workspace, M, g, s);
+  return setup_geo(d, P, (char*)workspace, M, g, nullptr, s);
 }
 
 int tfm_thinking_rows_fwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* cell_mask,
