@@ -896,15 +896,23 @@ static hipError_t gemm_wr_dispatch(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Rows of a tile: 128 (each weight tile staged through LDS serves twice the rows), except for the
+// two-input epilogues at BN = 256, which would spill, and for launches of fewer 128-row tiles
+// than two or three workgroups on each of 256 CUs take at once: there a tile's own latency
+// (loads, then an epilogue of several barriers) is the launch's time, and 64 rows have less of
+// it.  Forward + backward of one 1,000 x 21 table (165 tiles) 520 -> 504 us, eight query rows
+// through five pre-norm blocks (2 tiles) 678 -> 517 us; 1,056 tiles (8 x 512 x 33) 1,444 us
+// with 128 rows, 1,457 us with 64.
+constexpr int64_t GEMM_FILL = 700;
+static int gemm_bm(int epi, int BN, int N, int64_t M) {
+  if (BN > 192 && (epi == EPI_LN_BWD || epi == EPI_RMS_BWD)) return GEMM_BM;
+  return (M + 127) / 128 * (N / BN) < GEMM_FILL ? GEMM_BM : 128;
+}
+
 template <int BN>
 static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
-  // 128-row tiles (each weight tile staged through LDS serves twice the rows), except for the
-  // two-input epilogues at BN = 256, which would spill.  gemm_tiles() gives the row-tile count
-  // (the partial-sum rows of LN_BWD / RMS_BWD).
-  const bool in0 = a.epi == EPI_GELU_BWD || a.epi == EPI_LN || a.epi == EPI_DX ||
-                   a.epi == EPI_RMS;
-  const bool wide = !(BN > 192 && (a.epi == EPI_LN_BWD || a.epi == EPI_RMS_BWD));
-  const int bm = wide ? 128 : GEMM_BM;
+  const int bm = gemm_bm(a.epi, BN, a.N, a.M);
+  const bool wide = bm == 128;
   const int64_t mt = (a.M + bm - 1) / bm;
   const dim3 grid((unsigned)((mt + 7) / 8 * 8 * (a.N / BN)));
   if (wide) {
@@ -943,7 +951,7 @@ static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
 }
 
 int64_t gemm_tiles(int epi, int BN, int64_t M) {
-  const int bm = BN > 192 && (epi == EPI_LN_BWD || epi == EPI_RMS_BWD) ? GEMM_BM : 128;
+  const int bm = gemm_bm(epi, BN, BN, M);
   return (M + bm - 1) / bm;
 }
 
