@@ -108,7 +108,6 @@ hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStrea
 // wgrad_part_floats(Mmax) bounds the floats of all partials of a pass for every M <= Mmax.
 constexpr int WGRAD_CHUNK_MAX = 8192;
 constexpr int WGRAD_CHUNK_MIN = 256;
-constexpr int WGRAD_SLOTS = 512;  // workgroups resident at once: two on each of 256 CUs
 struct WgradSplit {
   int Z;
   int64_t chunk;

@@ -1,4 +1,4 @@
-// Small kernels of the MFMA path: weight casts, strided reductions, zero fill.
+// Small kernels of the MFMA path: zero fill, the norms at the ends of a block, thinking rows.
 #include "fast.h"
 #include "mfma.h"
 
@@ -51,9 +51,12 @@ hipError_t launch_zero_inactive(const Geo& g, void* native, size_t elt, hipStrea
 // time, lane l holding features 8l .. 8l+7 (E <= 256) in 16-byte pieces.  A block covers
 // LN_CELLS consecutive compact cells; half-wave h takes cells h, h + 16, ..., four per batch
 // with all their loads in flight, and keeps running column sums of dY * xhat and dY.
-constexpr int LN_CELLS = 256;
+// LN_CELLS is 256 where that many cells a block still fill the chip, else 64 (one batch a
+// half-wave): at 21,000 cells 82 blocks of 256 left two thirds of the CUs idle (22 us).
 constexpr int LN_BATCH = 4;
+static int ln_cells(int64_t N) { return N >= 256 * 1024 ? 256 : 64; }
 
+template <int LN_CELLS>
 __global__ __launch_bounds__(512) void k_ln_out_bwd(Geo g, const bf16* __restrict__ dY,
                                                     const bf16* __restrict__ xhat,
                                                     const float* __restrict__ rstd,
@@ -143,15 +146,18 @@ __global__ __launch_bounds__(512) void k_ln_out_bwd(Geo g, const bf16* __restric
 hipError_t launch_ln_out_bwd(const Geo& g, const bf16* dY, const bf16* xhat, const float* rstd,
                              const float* gamma, bf16* dz, float* part, int* nblocks,
                              hipStream_t s) {
-  const int64_t nb = (g.N + LN_CELLS - 1) / LN_CELLS;
+  const int cells = ln_cells(g.N);
+  const unsigned nb = (unsigned)((g.N + cells - 1) / cells);
   *nblocks = (int)nb;
-  k_ln_out_bwd<<<(unsigned)nb, 512, 0, s>>>(g, dY, xhat, rstd, gamma, dz, part);
+  if (cells == 64) k_ln_out_bwd<64><<<nb, 512, 0, s>>>(g, dY, xhat, rstd, gamma, dz, part);
+  else k_ln_out_bwd<256><<<nb, 512, 0, s>>>(g, dY, xhat, rstd, gamma, dz, part);
   return hipGetLastError();
 }
 
 // Pre-norm block input: x' = decay * X (native rows) and r = gamma x' / sqrt(mean(x'^2) + eps),
 // both written compact, with rstd.  Same thread layout as the LN3 backward above: a half-wave
 // per cell, lane l holding features 8l .. 8l+7, four cells per half-wave in flight.
+template <int LN_CELLS>
 __global__ __launch_bounds__(512) void k_rms_in(Geo g, const bf16* __restrict__ X, float decay,
                                                 const float* __restrict__ gamma, float eps,
                                                 bf16* __restrict__ xs, bf16* __restrict__ r,
@@ -214,9 +220,11 @@ __global__ __launch_bounds__(512) void k_rms_in(Geo g, const bf16* __restrict__ 
 
 hipError_t launch_rms_in(const Geo& g, const bf16* X, float decay, const float* gamma, float eps,
                          bf16* xs, bf16* r, float* rstd, hipStream_t s) {
-  const int64_t nb = (g.N + LN_CELLS - 1) / LN_CELLS;
+  const int cells = ln_cells(g.N);
+  const unsigned nb = (unsigned)((g.N + cells - 1) / cells);
   if (nb == 0) return hipSuccess;
-  k_rms_in<<<(unsigned)nb, 512, 0, s>>>(g, X, decay, gamma, eps, xs, r, rstd);
+  if (cells == 64) k_rms_in<64><<<nb, 512, 0, s>>>(g, X, decay, gamma, eps, xs, r, rstd);
+  else k_rms_in<256><<<nb, 512, 0, s>>>(g, X, decay, gamma, eps, xs, r, rstd);
   return hipGetLastError();
 }
 

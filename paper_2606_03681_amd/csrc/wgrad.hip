@@ -388,6 +388,12 @@ __global__ __launch_bounds__(256) void k_reduce_z(int Z, int zc, int64_t count, 
 // tiles, whose accumulators fit the registers of a 512-thread workgroup.
 static int wgrad_bn(int E) { return E > 192 ? 128 : E; }
 
+// Workgroups the chip's 256 CUs hold at once: the 192-wide tile's 176 registers leave room for
+// one workgroup of 8 waves on a CU.  With twice that many chunks a 1,000 x 21 table took 488
+// instead of 471 us (forward + backward; more partials to write and add), 16 x 1024 x 101 16.31
+// instead of 16.25 ms.
+static int wgrad_slots(int E) { return wgrad_bn(E) == 192 ? 256 : 512; }
+
 static int wgrad_tiles(int E, int H) {
   const int64_t bn = wgrad_bn(E);
   return (int)((8LL * E * E + 2LL * E * H) / (bn * bn));
@@ -396,11 +402,11 @@ static int wgrad_tiles(int E, int H) {
 // Chunks asked for at M cells; never falls as M grows.
 static int64_t wgrad_want(int64_t M, int E, int H) {
   const int T = wgrad_tiles(E, H);
-  // whole rounds of the WGRAD_SLOTS workgroups the chip holds at once, as few as keep a chunk
-  // within WGRAD_CHUNK_MAX; whole multiples of 8 chunks spread evenly over the XCDs
+  // whole rounds of the workgroups the chip holds at once, as few as keep a chunk within
+  // WGRAD_CHUNK_MAX; whole multiples of 8 chunks spread evenly over the XCDs
   int64_t Z = 8;
   for (int64_t k = 1;; ++k) {
-    Z = WGRAD_SLOTS * k / T / 8 * 8;
+    Z = wgrad_slots(E) * k / T / 8 * 8;
     if (Z >= 8 && (M + Z - 1) / Z <= WGRAD_CHUNK_MAX) break;
   }
   // below WGRAD_CHUNK_MIN cells a chunk's partial tile costs more than its operands
