@@ -72,6 +72,8 @@ struct SgemmArgs {
   int32_t batch;      // kchunk == 0: grid.z runs over `batch` independent products whose A,
   int64_t bsa, bsb;   // B and aux lie bsa, bsb and bsaux floats apart (C zstride apart)
   int64_t bsaux;
+  int32_t sym;        // the product (and aux) is symmetric: tiles on and above the diagonal are
+                      // computed and written to both places
 };
 hipError_t launch_sgemm(const SgemmArgs& a, bool ta, bool tb, int epi, hipStream_t s);
 

@@ -250,6 +250,7 @@ int tfm_muon_step(const tfm_muon* hp, int32_t count, int32_t rows, int32_t cols,
     g1.M = n; g1.N = n; g1.K = m;
     g1.batch = count; g1.bsa = (int64_t)n * m; g1.bsb = (int64_t)n * m;
     g1.zstride = (int64_t)n * n;
+    g1.sym = 1;
     STEP("muon_ns/mfma", tfm::launch_sgemm(g1, false, true, tfm::SG_BIAS, st));
     tfm::SgemmArgs g2{};  // Bm = b A + c A A
     g2.A = A; g2.lda = n; g2.B = A; g2.ldb = n; g2.C = Bm; g2.ldc = n;
@@ -257,6 +258,7 @@ int tfm_muon_step(const tfm_muon* hp, int32_t count, int32_t rows, int32_t cols,
     g2.M = n; g2.N = n; g2.K = n;
     g2.batch = count; g2.bsa = (int64_t)n * n; g2.bsb = (int64_t)n * n;
     g2.bsaux = (int64_t)n * n; g2.zstride = (int64_t)n * n;
+    g2.sym = 1;
     STEP("muon_ns/mfma", tfm::launch_sgemm(g2, false, false, tfm::SG_AXPBY, st));
     tfm::SgemmArgs g3{};  // X' = a X + Bm X
     g3.A = Bm; g3.lda = n; g3.B = X; g3.ldb = m; g3.C = Xn; g3.ldc = m;
