@@ -79,9 +79,10 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // Cells per block tile of the MFMA GEMM; EPI_LN_BWD writes one partial row per tile.
 constexpr int GEMM_BM = 64;
 inline int64_t gemm_row_tiles(int64_t M) { return (M + GEMM_BM - 1) / GEMM_BM; }
-// Row tiles of one launch of epilogue epi at column tile BN (the launch picks 64 or 128 rows);
-// never more than gemm_row_tiles(M).
+// Row tiles of one launch of epilogue epi at column tile BN (the launch picks 32, 64 or 128 rows);
+// never more than gemm_max_tiles(Mmax) for M <= Mmax.
 int64_t gemm_tiles(int epi, int BN, int64_t M);
+int64_t gemm_max_tiles(int64_t Mmax);
 
 // bf16 copies of the six weight matrices of one layer, as stored ([out][in]) and transposed.
 // Offsets (elements) inside w / wt follow the packed parameter order of the weights:
@@ -211,7 +212,7 @@ __host__ __device__ inline int64_t mlp_bwd_stream_elems(int E, int H) {
 int64_t mlp_bwd_tiles(int64_t M);
 hipError_t launch_mlp_bwd(const MlpBwdArgs& a, hipStream_t s);
 
-// Floats of one norm's column partials for up to `cells` cells: [64-cell tiles][2 E], which also
+// Floats of one norm's column partials for up to `cells` cells: [GEMM row tiles][2 E], which also
 // holds the LN3 backward's and (two norms together) the fused MLP backward's.
 int64_t ln_part_floats(int64_t cells, int E);
 

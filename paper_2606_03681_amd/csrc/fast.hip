@@ -282,7 +282,7 @@ template hipError_t launch_thinking_bwd<float>(const Geo&, int, const float*, fl
 template hipError_t launch_thinking_bwd<bf16>(const Geo&, int, const bf16*, float*, int,
                                               hipStream_t);
 
-int64_t ln_part_floats(int64_t cells, int E) { return gemm_row_tiles(cells) * 2 * E; }
+int64_t ln_part_floats(int64_t cells, int E) { return gemm_max_tiles(cells) * 2 * E; }
 
 size_t fast_workspace_bytes(int64_t cells, int E, int H) {
   const WOff wo = weight_offsets(E, H);

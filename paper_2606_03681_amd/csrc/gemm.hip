@@ -51,21 +51,29 @@ __device__ __forceinline__ f32x4 unpack4(uint2 u) {
 // faster per launch.  The GELU epilogue (two outputs, four barriers per half) was 17 % slower
 // that way, and wider tiles (E = 256) would need more registers than three workgroups per CU
 // leave: both keep the full tile.
-template <int EPI, int BN>
+template <int EPI, int BN, int BM>
 constexpr bool gemm_half_tile() {
-  return (EPI == EPI_BIAS || EPI == EPI_ITEM_QKV) && BN <= 192;
+  return (EPI == EPI_BIAS || EPI == EPI_ITEM_QKV) && BN <= 192 && BM >= 64;
+}
+// Stages of the LDS ring.  At 32 rows (launches of at most one workgroup a CU) eight, so that a
+// K = E <= 256 product has all of its loads in flight at once and waits for memory once.  Not at
+// 64 rows: six stages there cost a workgroup per CU (1,000 x 21 table: 468 -> 556 us).
+template <int EPI, int BN, int BM>
+constexpr int gemm_stages() {
+  return gemm_half_tile<EPI, BN, BM>() ? 2 : (BM == 32 ? 8 : 3);
 }
 
 template <int BN, int EPI, int BM>
-__global__ __launch_bounds__(256, (gemm_half_tile<EPI, BN>() ? 3 : 2)) void k_gemm(GemmArgs a) {
+__global__ __launch_bounds__(256, (BM == 32 ? 1 : (gemm_half_tile<EPI, BN, BM>() ? 3 : 2))) void
+k_gemm(GemmArgs a) {
   constexpr int MI = BM / 32;          // 16-row blocks per wave (2 x 2 waves, each BM/2 rows)
-  constexpr int NBA = BM / 64;         // 1 KB blocks of A per wave and stage
+  constexpr int NBA = BM < 64 ? 1 : BM / 64;  // 1 KB blocks of A per wave and stage
   constexpr int NB = BN / 32;          // 16-wide column blocks per wave
   constexpr int TS = BN + 8;           // epilogue tile row stride (elements)
-  constexpr bool HALF = gemm_half_tile<EPI, BN>();
+  constexpr bool HALF = gemm_half_tile<EPI, BN, BM>();
   // pipeline stages in the LDS ring (60 KB at E = 192 and 128 rows: 2 workgroups per CU; 40 KB
   // with two stages)
-  constexpr int S = HALF ? 2 : 3;
+  constexpr int S = gemm_stages<EPI, BN, BM>();
   constexpr int A_EL = BM * BK;        // elements of one stage's A rows
   constexpr int STAGE_EL = (BM + BN) * BK;
   constexpr int NBB = BN / 64;         // 1 KB blocks of B per wave and stage
@@ -121,7 +129,8 @@ __global__ __launch_bounds__(256, (gemm_half_tile<EPI, BN>() ? 3 : 2)) void k_ge
   // [k0, k0+32), straight from memory into the stage's LDS slot (global_load_lds: lane L of a
   // wave fills bytes 16L..16L+15 of the wave's 1 KB block).  LDS position p (16-byte units)
   // holds row p / 4, k chunk kslot^-1(p % 4); this lane's A position is wave*64 + lane.
-  // This lane's A positions: block t covers rows 16 (wave + 4 t) .. + 15.
+  // This lane's A positions: block t covers rows 16 (wave + 4 t) .. + 15 (at 32 rows the waves 2
+  // and 3 repeat the blocks of 0 and 1, so that every wave counts the same loads).
   const bf16* zero = reinterpret_cast<const bf16*>(&kZeroChunk);
   int akc[NBA];
   bool arow_ok[NBA];
@@ -130,7 +139,7 @@ __global__ __launch_bounds__(256, (gemm_half_tile<EPI, BN>() ? 3 : 2)) void k_ge
   int hr[NBA], hntr[NBA];
 #pragma unroll
   for (int t = 0; t < NBA; ++t) {
-    const int ar = ((wave + 4 * t) * 64 + lane) >> 2;
+    const int ar = (((wave + 4 * t) % (BM / 16)) * 64 + lane) >> 2;
     akc[t] = kslot(ar, lane & 3);
     const int64_t am = m0 + ar;
     arow_ok[t] = am < a.M;
@@ -173,7 +182,7 @@ __global__ __launch_bounds__(256, (gemm_half_tile<EPI, BN>() ? 3 : 2)) void k_ge
                   ? base + ((hcol[t] * g.heads + head) * g.R + hr[t]) * (int64_t)g.d + jj
                   : zero;
       }
-      lds_dma16(src, sa + (wave + 4 * t) * 512);
+      lds_dma16(src, sa + ((wave + 4 * t) % (BM / 16)) * 512);
     }
 #pragma unroll
     for (int t = 0; t < NBB; ++t) lds_dma16(bptr[t] + k0, sa + A_EL + (wave + 4 * t) * 512);
@@ -202,8 +211,8 @@ __global__ __launch_bounds__(256, (gemm_half_tile<EPI, BN>() ? 3 : 2)) void k_ge
   // Input tiles are prefetched at 64 rows; at 128 rows the second one (and at BN = 256 the
   // first too) is loaded when the main loop ends: prefetched, they would not fit in registers
   // next to the accumulators.
-  constexpr bool IN0_PRE = IN0 && (BM == 64 || BN <= 192);
-  constexpr bool IN1_PRE = IN1 && BM == 64;
+  constexpr bool IN0_PRE = IN0 && (BM <= 64 || BN <= 192);
+  constexpr bool IN1_PRE = IN1 && BM <= 64;
   uint4 pin0[IN0 ? NCH : 1], pin1[IN1 ? NCH : 1];
   if (IN0) {
     if (tid < BM) {
@@ -878,8 +887,12 @@ __global__ __launch_bounds__(512, 1) void k_gemm_wr(GemmArgs a) {
 
 // The weight-resident kernel applies to K = E = BN <= 192 products with the bias or item
 // Q|K|V epilogue, A rows compact or native (at BN = 256 the weight slice leaves too few
-// registers); grid: one workgroup per CU.
+// registers), of at least GEMM_WR_MIN tiles: its 256 persistent workgroups pay for the weights
+// they load with the tiles that follow the first two or three (1,000 x 21 table, 165 and 495
+// tiles: 468 us, 455 us with the staged kernel).
+constexpr int64_t GEMM_WR_MIN = 600;
 static bool gemm_wr_ok(const GemmArgs& a) {
+  if ((a.M + 127) / 128 * (a.N / a.BN) < GEMM_WR_MIN) return false;
   const bool epi = a.epi == EPI_BIAS || a.epi == EPI_ITEM_QKV;
   const bool mode = a.amode == ROWS_COMPACT || a.amode == ROWS_NATIVE;
   return epi && mode && a.K == a.BN && a.N % a.BN == 0 && a.N / a.BN <= 32 &&
@@ -903,51 +916,52 @@ static hipError_t gemm_wr_dispatch(const GemmArgs& a, hipStream_t s) {
 // it.  Forward + backward of one 1,000 x 21 table (165 tiles) 520 -> 504 us, eight query rows
 // through five pre-norm blocks (2 tiles) 678 -> 517 us; 1,056 tiles (8 x 512 x 33) 1,444 us
 // with 128 rows, 1,457 us with 64.
-constexpr int64_t GEMM_FILL = 700;
+// Launches that 32-row tiles keep within one workgroup a CU take those: eight query rows 480 ->
+// 452 us.
+constexpr int64_t GEMM_FILL = 700, GEMM_DEEP = 256;
 static int gemm_bm(int epi, int BN, int N, int64_t M) {
+  if ((M + 31) / 32 * (N / BN) <= GEMM_DEEP) return 32;
   if (BN > 192 && (epi == EPI_LN_BWD || epi == EPI_RMS_BWD)) return GEMM_BM;
   return (M + 127) / 128 * (N / BN) < GEMM_FILL ? GEMM_BM : 128;
 }
 
-template <int BN>
-static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
-  const int bm = gemm_bm(a.epi, BN, a.N, a.M);
-  const bool wide = bm == 128;
-  const int64_t mt = (a.M + bm - 1) / bm;
+// Row tiles (partial rows of LN_BWD / RMS_BWD) of any M <= Mmax.
+int64_t gemm_max_tiles(int64_t Mmax) {
+  const int64_t deep = (Mmax + 31) / 32 < GEMM_DEEP ? (Mmax + 31) / 32 : GEMM_DEEP;
+  return gemm_row_tiles(Mmax) > deep ? gemm_row_tiles(Mmax) : deep;
+}
+
+template <int BN, int BM>
+static hipError_t gemm_epi(const GemmArgs& a, hipStream_t s) {
+  const int64_t mt = (a.M + BM - 1) / BM;
   const dim3 grid((unsigned)((mt + 7) / 8 * 8 * (a.N / BN)));
-  if (wide) {
-    switch (a.epi) {
-      case EPI_BIAS: k_gemm<BN, EPI_BIAS, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_GELU_FWD: k_gemm<BN, EPI_GELU_FWD, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_ITEM_QKV: k_gemm<BN, EPI_ITEM_QKV, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_GELU_BWD: k_gemm<BN, EPI_GELU_BWD, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_LN: k_gemm<BN, EPI_LN, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_DX: k_gemm<BN, EPI_DX, 128><<<grid, 256, 0, s>>>(a); break;
-      case EPI_RMS: k_gemm<BN, EPI_RMS, 128><<<grid, 256, 0, s>>>(a); break;
-      default:
-        if constexpr (BN <= 192) {
-          if (a.epi == EPI_LN_BWD) k_gemm<BN, EPI_LN_BWD, 128><<<grid, 256, 0, s>>>(a);
-          else if (a.epi == EPI_RMS_BWD) k_gemm<BN, EPI_RMS_BWD, 128><<<grid, 256, 0, s>>>(a);
-          else return hipErrorInvalidValue;
-        } else {
-          return hipErrorInvalidValue;
-        }
-    }
-    return hipGetLastError();
-  }
   switch (a.epi) {
-    case EPI_BIAS: k_gemm<BN, EPI_BIAS, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_GELU_FWD: k_gemm<BN, EPI_GELU_FWD, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_GELU_BWD: k_gemm<BN, EPI_GELU_BWD, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_ITEM_QKV: k_gemm<BN, EPI_ITEM_QKV, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_LN: k_gemm<BN, EPI_LN, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_LN_BWD: k_gemm<BN, EPI_LN_BWD, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_DX: k_gemm<BN, EPI_DX, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_RMS: k_gemm<BN, EPI_RMS, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_RMS_BWD: k_gemm<BN, EPI_RMS_BWD, GEMM_BM><<<grid, 256, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
+    case EPI_BIAS: k_gemm<BN, EPI_BIAS, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_GELU_FWD: k_gemm<BN, EPI_GELU_FWD, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_GELU_BWD: k_gemm<BN, EPI_GELU_BWD, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_ITEM_QKV: k_gemm<BN, EPI_ITEM_QKV, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_LN: k_gemm<BN, EPI_LN, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_DX: k_gemm<BN, EPI_DX, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_RMS: k_gemm<BN, EPI_RMS, BM><<<grid, 256, 0, s>>>(a); break;
+    default:
+      if constexpr (BM < 128 || BN <= 192) {
+        if (a.epi == EPI_LN_BWD) k_gemm<BN, EPI_LN_BWD, BM><<<grid, 256, 0, s>>>(a);
+        else if (a.epi == EPI_RMS_BWD) k_gemm<BN, EPI_RMS_BWD, BM><<<grid, 256, 0, s>>>(a);
+        else return hipErrorInvalidValue;
+      } else {
+        return hipErrorInvalidValue;
+      }
   }
   return hipGetLastError();
+}
+
+template <int BN>
+static hipError_t gemm_dispatch(const GemmArgs& a, hipStream_t s) {
+  switch (gemm_bm(a.epi, BN, a.N, a.M)) {
+    case 32: return gemm_epi<BN, 32>(a, s);
+    case GEMM_BM: return gemm_epi<BN, GEMM_BM>(a, s);
+    default: return gemm_epi<BN, 128>(a, s);
+  }
 }
 
 int64_t gemm_tiles(int epi, int BN, int64_t M) {
