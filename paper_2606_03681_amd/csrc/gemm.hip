@@ -29,8 +29,17 @@ __device__ __attribute__((aligned(16))) const uint4 kZeroChunk = {0u, 0u, 0u, 0u
 // instead costs about 3 conflict cycles per read).
 __device__ __forceinline__ int kslot(int r, int kc) { return kc ^ ((r >> 1) & 3); }
 
+// Column and row of active cell m (m < 2^26, so 32-bit division).
+__device__ __forceinline__ uint32_t cell_col(const Geo& g, int64_t m, int* r) {
+  const uint32_t col = (uint32_t)m / (uint32_t)g.R;
+  *r = (int)((uint32_t)m - col * (uint32_t)g.R);
+  return col;
+}
 __device__ __forceinline__ int64_t row_addr(const Geo& g, int mode, int64_t m, int64_t ld) {
-  return mode == ROWS_NATIVE ? native_cell(g, m) * g.E : m * ld;
+  if (mode != ROWS_NATIVE) return m * ld;
+  int r;
+  const uint32_t col = cell_col(g, m, &r);
+  return (g.col_cell0[col] + (int64_t)r * g.S) * g.E;
 }
 
 __device__ __forceinline__ f32x4 unpack4(uint2 u) {
@@ -63,12 +72,36 @@ constexpr int gemm_stages() {
   return gemm_half_tile<EPI, BN, BM>() ? 2 : (BM == 32 ? 8 : 3);
 }
 
+// Waves of a tile, two along the rows, the others along the columns.  At 32 rows BN / 16, so that
+// a wave's share of the tile, and with it the straight run of instructions (loads, products,
+// epilogue) that such a launch's time consists of, is small; eight at 64 rows of BN = 256, whose
+// LDS leaves room for two workgroups a CU (four waves a SIMD instead of two).  Otherwise four: the
+// LDS holds three or more workgroups there, and more waves measured slower (1,000 x 21 table, E =
+// 192: 454 us, 463 us with twelve at 64 rows).
+template <int BN, int BM>
+constexpr int gemm_waves() {
+  return BM == 32 ? BN / 16 : (BM == 64 && BN == 256 ? 8 : 4);
+}
+
+// Waves per SIMD asked for: as many as the LDS ring leaves room for workgroups.
 template <int BN, int EPI, int BM>
-__global__ __launch_bounds__(256, (BM == 32 ? 1 : (gemm_half_tile<EPI, BN, BM>() ? 3 : 2))) void
+constexpr int gemm_occupancy() {
+  return BM == 32 ? 1
+         : BM == 64 ? (BN == 256 ? 4 : 3)
+                    : (gemm_half_tile<EPI, BN, BM>() ? 3 : 2);
+}
+
+template <int BN, int EPI, int BM>
+__global__ __launch_bounds__((64 * gemm_waves<BN, BM>()), (gemm_occupancy<BN, EPI, BM>())) void
 k_gemm(GemmArgs a) {
-  constexpr int MI = BM / 32;          // 16-row blocks per wave (2 x 2 waves, each BM/2 rows)
-  constexpr int NBA = BM < 64 ? 1 : BM / 64;  // 1 KB blocks of A per wave and stage
-  constexpr int NB = BN / 32;          // 16-wide column blocks per wave
+  constexpr int NW = gemm_waves<BN, BM>(), NT = 64 * NW;
+  constexpr int WC = NW / 2;           // column waves
+  constexpr int MI = BM / 32;          // 16-row blocks per wave (2 row waves, each BM/2 rows)
+  constexpr int NB = BN / 16 / WC;     // 16-wide column blocks per wave
+  // 1 KB blocks (16 rows) of A and B per wave and stage; where they do not divide among the
+  // waves some repeat others' blocks, so that every wave counts the same loads
+  constexpr int AB = BM / 16, BB = BN / 16;
+  constexpr int NBA = (AB + NW - 1) / NW, NBB = (BB + NW - 1) / NW;
   constexpr int TS = BN + 8;           // epilogue tile row stride (elements)
   constexpr bool HALF = gemm_half_tile<EPI, BN, BM>();
   // pipeline stages in the LDS ring (60 KB at E = 192 and 128 rows: 2 workgroups per CU; 40 KB
@@ -76,25 +109,27 @@ k_gemm(GemmArgs a) {
   constexpr int S = gemm_stages<EPI, BN, BM>();
   constexpr int A_EL = BM * BK;        // elements of one stage's A rows
   constexpr int STAGE_EL = (BM + BN) * BK;
-  constexpr int NBB = BN / 64;         // 1 KB blocks of B per wave and stage
   constexpr int RING_BYTES = S * STAGE_EL * 2;
   constexpr int TILE_BYTES = (HALF ? BM / 2 : BM) * TS * 2;
   // The epilogue's tile and its row / column reduction arrays reuse the ring once it drains.
-  constexpr int RED_BYTES = 2 * BM * 4, CRED_BYTES = 4 * BN * 4;
+  constexpr int RED_BYTES = BN / 32 * BM * 4, CRED_BYTES =
+      EPI == EPI_LN_BWD || EPI == EPI_RMS_BWD ? 4 * BN * 4 : 0;
   constexpr int EPI_BYTES = TILE_BYTES + RED_BYTES + CRED_BYTES;
   __shared__ __attribute__((aligned(16))) char smem[RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES];
   bf16* ring = reinterpret_cast<bf16*>(smem);  // stage slot s: A at s*STAGE_EL, B after A
   bf16* tile = reinterpret_cast<bf16*>(smem);  // epilogue: [BM][TS], after the main loop
-  float (*red)[BM] = reinterpret_cast<float (*)[BM]>(smem + TILE_BYTES);          // [2][BM]
+  float (*red)[BM] = reinterpret_cast<float (*)[BM]>(smem + TILE_BYTES);          // [BN/32][BM]
   float (*cred)[2][BN] =
       reinterpret_cast<float (*)[2][BN]>(smem + TILE_BYTES + RED_BYTES);        // [2][2][BN]
   // bias, gamma, beta of the tile; residual affine (EPI_LN)
-  __shared__ __attribute__((aligned(16))) float cpar[5][BN];
-  __shared__ int64_t rbase[BM];  // epilogue: per-row element offset for the current mode
+  __shared__ __attribute__((aligned(16))) float cpar[EPI == EPI_LN ? 5 : 2][BN];
+  // per-row element offsets of the first epilogue input (rows past M: the last row's) and of the
+  // output (-1 where nothing is stored)
+  __shared__ int64_t rin[BM], rout[BM];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = wave_id();
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / WC, wn = wave % WC;
   const int lr = lane & 15, lg = lane >> 4;
   // Workgroup -> (row tile bx, column tile by).  The hardware deals consecutive workgroups
   // round-robin over the 8 XCDs; all column tiles of a row tile are given consecutive slots
@@ -116,30 +151,61 @@ k_gemm(GemmArgs a) {
   if (EPI == EPI_ITEM_QKV && part > 0) {
     // K and V exist for train rows only: skip tiles made of test rows alone
     int64_t last = m0 + BM - 1 < a.M ? m0 + BM - 1 : a.M - 1;
-    int64_t c0 = m0 / g.R, c1 = last / g.R;
+    int rlo, rhi;
+    const uint32_t c0 = cell_col(g, m0, &rlo), c1 = cell_col(g, last, &rhi);
     bool any = false;
-    for (int64_t c = c0; c <= c1 && !any; ++c) {
-      int64_t rlo = c == c0 ? m0 - c0 * g.R : 0;
+    for (uint32_t c = c0; c <= c1 && !any; ++c) {
       any = rlo < g.col_ntr[c];
+      rlo = 0;
     }
     if (!any) return;
+  }
+
+  constexpr bool IN0 = EPI == EPI_GELU_BWD || EPI == EPI_DX || EPI == EPI_LN ||
+                      EPI == EPI_LN_BWD || EPI == EPI_RMS || EPI == EPI_RMS_BWD;
+  constexpr bool IN1 = EPI == EPI_LN_BWD || EPI == EPI_RMS_BWD;
+  constexpr bool QKV = EPI == EPI_ITEM_QKV;
+  constexpr bool GAMMA =
+      EPI == EPI_LN || EPI == EPI_LN_BWD || EPI == EPI_RMS || EPI == EPI_RMS_BWD;
+  // ---- what a tile reads once (its rows' places, its columns' parameters) is requested before
+  // the first stages and put away after them, so that one memory latency covers both.
+  const bool onat = EPI == EPI_DX || ((EPI == EPI_LN || EPI == EPI_RMS_BWD) && a.omode == ROWS_NATIVE);
+  const bool inat = GAMMA && EPI != EPI_LN_BWD && a.rmode == ROWS_NATIVE;
+  const int dsh = 31 - __builtin_clz(g.d);  // d is a power of two
+  int64_t row_nat = 0;
+  int row_r = 0, row_ntr = 0;
+  uint32_t row_col = 0;
+  const int64_t row_m = m0 + tid < a.M ? m0 + tid : a.M - 1;
+  float par[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  if (tid < BM && (QKV || onat || inat)) {
+    row_col = cell_col(g, row_m, &row_r);
+    if (QKV) row_ntr = g.col_ntr[row_col];
+    else row_nat = g.col_cell0[row_col];
+  }
+  if (tid < BN) {
+    if (a.bias) par[0] = a.bias[n0 + tid];
+    if (GAMMA) par[1] = a.gamma[tid];
+    if (EPI == EPI_LN) par[2] = a.beta[tid];
+    if (EPI == EPI_LN && a.rgamma) {
+      par[3] = a.rgamma[tid];
+      par[4] = a.rbeta[tid];
+    }
   }
 
   // ---- operand streaming.  Every stage moves A rows [m0, m0+64) and B rows [n0, n0+BN), k in
   // [k0, k0+32), straight from memory into the stage's LDS slot (global_load_lds: lane L of a
   // wave fills bytes 16L..16L+15 of the wave's 1 KB block).  LDS position p (16-byte units)
-  // holds row p / 4, k chunk kslot^-1(p % 4); this lane's A position is wave*64 + lane.
-  // This lane's A positions: block t covers rows 16 (wave + 4 t) .. + 15 (at 32 rows the waves 2
-  // and 3 repeat the blocks of 0 and 1, so that every wave counts the same loads).
+  // holds row p / 4, k chunk kslot^-1(p % 4); this lane's A positions are below.
+  // This lane's A positions: block t covers rows 16 ((wave + NW t) % AB) .. + 15.
   const bf16* zero = reinterpret_cast<const bf16*>(&kZeroChunk);
   int akc[NBA];
   bool arow_ok[NBA];
   const bf16* aptr[NBA];  // row address + chunk, for compact / native rows
-  int64_t hcol[NBA];
+  uint32_t hcol[NBA];
   int hr[NBA], hntr[NBA];
 #pragma unroll
   for (int t = 0; t < NBA; ++t) {
-    const int ar = (((wave + 4 * t) % (BM / 16)) * 64 + lane) >> 2;
+    const int ar = (((wave + NW * t) % AB) * 64 + lane) >> 2;
     akc[t] = kslot(ar, lane & 3);
     const int64_t am = m0 + ar;
     arow_ok[t] = am < a.M;
@@ -149,8 +215,7 @@ k_gemm(GemmArgs a) {
     hntr[t] = 0;
     if (a.amode == ROWS_ITEM_HM) {
       if (arow_ok[t]) {
-        hcol[t] = am / g.R;
-        hr[t] = (int)(am - hcol[t] * g.R);
+        hcol[t] = cell_col(g, am, &hr[t]);
         hntr[t] = g.col_ntr[hcol[t]];
       }
     } else if (arow_ok[t]) {
@@ -160,7 +225,7 @@ k_gemm(GemmArgs a) {
   const bf16* bptr[NBB];
 #pragma unroll
   for (int t = 0; t < NBB; ++t) {
-    const int p = (wave + 4 * t) * 64 + lane;
+    const int p = ((wave + NW * t) % BB) * 64 + lane;
     const int n = p >> 2;
     bptr[t] = a.Bt + (int64_t)(n0 + n) * a.K + kslot(n, p & 3) * 8;
   }
@@ -176,71 +241,79 @@ k_gemm(GemmArgs a) {
         // alone and the base pointer is chosen by a scalar branch.
         const int part = k0 / BN;
         const int within = k0 - part * BN + akc[t] * 8;
-        const int head = within / g.d, jj = within - head * g.d;
+        const int head = within >> dsh, jj = within & (g.d - 1);
         const bf16* base = part == 0 ? a.A : (part == 1 ? a.A2 : a.A3);
         src = arow_ok[t] && (part == 0 || hr[t] < hntr[t])
-                  ? base + ((hcol[t] * g.heads + head) * g.R + hr[t]) * (int64_t)g.d + jj
+                  ? base + (((int64_t)hcol[t] * g.heads + head) * g.R + hr[t]) * g.d + jj
                   : zero;
       }
-      lds_dma16(src, sa + ((wave + 4 * t) % (BM / 16)) * 512);
+      lds_dma16(src, sa + ((wave + NW * t) % AB) * 512);
     }
 #pragma unroll
-    for (int t = 0; t < NBB; ++t) lds_dma16(bptr[t] + k0, sa + A_EL + (wave + 4 * t) * 512);
+    for (int t = 0; t < NBB; ++t) lds_dma16(bptr[t] + k0, sa + A_EL + ((wave + NW * t) % BB) * 512);
   };
 
-  // per-column epilogue parameters of this column tile, staged once
+  const int KT = a.K / BK;
+#pragma unroll
+  for (int st = 0; st < S - 1; ++st)
+    if (st < KT) issue(st);
+
   if (tid < BN) {
-    cpar[0][tid] = a.bias ? a.bias[n0 + tid] : 0.f;
-    if (EPI == EPI_LN || EPI == EPI_LN_BWD || EPI == EPI_RMS || EPI == EPI_RMS_BWD)
-      cpar[1][tid] = a.gamma[tid];
-    if (EPI == EPI_LN) cpar[2][tid] = a.beta[tid];
-    if (EPI == EPI_LN && a.rgamma) {
-      cpar[3][tid] = a.rgamma[tid];
-      cpar[4][tid] = a.rbeta[tid];
+    cpar[0][tid] = par[0];
+    if (GAMMA) cpar[1][tid] = par[1];
+    if (EPI == EPI_LN) {
+      cpar[2][tid] = par[2];
+      cpar[3][tid] = par[3];
+      cpar[4][tid] = par[4];
     }
   }
+  if (tid < BM) {
+    const int64_t nat = (row_nat + (int64_t)row_r * g.S) * g.E;
+    if (IN0) rin[tid] = inat ? nat : row_m * (EPI == EPI_GELU_BWD ? a.ldo : BN);
+    int64_t off;
+    if (QKV)
+      off = part == 0 || row_r < row_ntr
+                ? ((int64_t)row_col * g.heads * g.R + row_r) * (int64_t)g.d
+                : -1;
+    else if (EPI == EPI_BIAS || EPI == EPI_GELU_FWD || EPI == EPI_GELU_BWD)
+      off = row_m * a.ldo;
+    else
+      off = onat ? nat : row_m * BN;
+    rout[tid] = m0 + tid < a.M ? off : -1;
+  }
+  lds_barrier();
 
   // ---- epilogue inputs (residual, x-hat, pre-activation) do not depend on the product: their
   // rows are fetched into registers now, so that they travel with the first stages instead of
-  // costing a memory round trip after the main loop.
+  // costing a memory round trip after the main loop.  Every load is issued (rows past M read the
+  // last row), because the waits below count them.
   constexpr int CPRW = BN / 8;              // 16-byte chunks per tile row
-  constexpr int NCH = BM * CPRW / 256;      // chunks per thread of one tile
-  constexpr bool IN0 = EPI == EPI_GELU_BWD || EPI == EPI_DX || EPI == EPI_LN ||
-                      EPI == EPI_LN_BWD || EPI == EPI_RMS || EPI == EPI_RMS_BWD;
-  constexpr bool IN1 = EPI == EPI_LN_BWD || EPI == EPI_RMS_BWD;
+  constexpr int NCH = BM * CPRW / NT;      // chunks per thread of one tile
   // Input tiles are prefetched at 64 rows; at 128 rows the second one (and at BN = 256 the
   // first too) is loaded when the main loop ends: prefetched, they would not fit in registers
   // next to the accumulators.
   constexpr bool IN0_PRE = IN0 && (BM <= 64 || BN <= 192);
   constexpr bool IN1_PRE = IN1 && BM <= 64;
+  constexpr int NPIN = (IN0_PRE ? NCH : 0) + (IN1_PRE ? NCH : 0);
   uint4 pin0[IN0 ? NCH : 1], pin1[IN1 ? NCH : 1];
-  if (IN0) {
-    if (tid < BM) {
-      const int64_t m = m0 + tid;
-      int64_t off = -1;
-      if (m < a.M) {
-        if (EPI == EPI_GELU_BWD) off = m * a.ldo;
-        else if (EPI == EPI_LN || EPI == EPI_RMS || EPI == EPI_RMS_BWD)
-          off = row_addr(g, a.rmode, m, BN);
-        else off = m * BN;
-      }
-      rbase[tid] = off;
-    }
-    lds_barrier();
+  auto load_in0 = [&]() __attribute__((always_inline)) {
     const bf16* src0 = EPI == EPI_GELU_BWD ? a.aux + n0 : a.resid;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int ch = tid + 256 * c;
-      const int64_t off = rbase[ch / CPRW];
-      const int cc = (ch % CPRW) * 8;
-      if (IN0_PRE) pin0[c] = off >= 0 ? ldu4(src0 + off + cc) : make_uint4(0, 0, 0, 0);
-      // The second input is always compact rows (x-hat, or h).  Rows past M read row M - 1
-      // instead of zeros (no select on the loaded value): their accumulators and first input
-      // are zero, so they add nothing to the column sums and are never stored.
-      const int64_t m1 = m0 + ch / CPRW < a.M ? m0 + ch / CPRW : a.M - 1;
-      if (IN1_PRE) pin1[c] = ldu4(a.aux + m1 * BN + cc);
+      const int ch = tid + NT * c;
+      pin0[c] = ldu4(src0 + rin[ch / CPRW] + (ch % CPRW) * 8);
     }
-  }
+  };
+  auto load_in1 = [&]() __attribute__((always_inline)) {  // always compact rows (x-hat, or h)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int ch = tid + NT * c;
+      const int64_t m1 = m0 + ch / CPRW < a.M ? m0 + ch / CPRW : a.M - 1;
+      pin1[c] = ldu4(a.aux + m1 * BN + (ch % CPRW) * 8);
+    }
+  };
+  if (IN0_PRE) load_in0();
+  if (IN1_PRE) load_in1();
 
   f32x4 acc[MI][NB];
 #pragma unroll
@@ -249,16 +322,17 @@ k_gemm(GemmArgs a) {
     for (int j = 0; j < NB; ++j) acc[i][j] = zero4();
 
   // Stage kt is consumed at iteration kt; S - 1 stages are in flight ahead of it.  Each wave
-  // waits for its own loads of stage kt (vmcnt counts in issue order; a stage is 1 + NBB
-  // loads), then the barrier makes every wave's part visible and frees the slot of stage
-  // kt - 1, which stage kt + S - 1 refills.
-  const int KT = a.K / BK;
-#pragma unroll
-  for (int st = 0; st < S - 1; ++st)
-    if (st < KT) issue(st);
+  // waits for its own loads of stage kt (vmcnt counts in issue order; a stage is NBA + NBB
+  // loads, and the NPIN loads above follow the first S - 1 stages), then the barrier makes every
+  // wave's part visible and frees the slot of stage kt - 1, which stage kt + S - 1 refills.
   for (int kt = 0; kt < KT; ++kt) {
+    constexpr int AHEAD = (S - 2) * (NBA + NBB);
+    static_assert(AHEAD + NPIN < 64, "vmcnt");
     if (kt + S - 2 < KT) {
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((S - 2) * (NBA + NBB)) : "memory");
+      if (kt < S - 1)
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AHEAD + NPIN) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AHEAD) : "memory");
     } else {
       asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     }
@@ -273,7 +347,7 @@ k_gemm(GemmArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int n = wn * (BN / 2) + j * 16 + lr;
+      const int n = wn * (BN / WC) + j * 16 + lr;
       bfr[j] = ld8(&sb[n * BK + kslot(n, lg) * 8]);
     }
 #pragma unroll
@@ -282,65 +356,43 @@ k_gemm(GemmArgs a) {
       for (int j = 0; j < NB; ++j) acc[i][j] = mfma16(bfr[j], af[i], acc[i][j]);
   }
   lds_barrier();  // every wave is done with the ring before the epilogue tile reuses it
-  if ((IN0 && !IN0_PRE) || (IN1 && !IN1_PRE)) {
-    const bf16* src0 = EPI == EPI_GELU_BWD ? a.aux + n0 : a.resid;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int ch = tid + 256 * c;
-      const int64_t off = rbase[ch / CPRW];
-      const int cc = (ch % CPRW) * 8;
-      if (IN0 && !IN0_PRE) pin0[c] = off >= 0 ? ldu4(src0 + off + cc) : make_uint4(0, 0, 0, 0);
-      const int64_t m1 = m0 + ch / CPRW < a.M ? m0 + ch / CPRW : a.M - 1;  // (as above)
-      if (IN1 && !IN1_PRE) pin1[c] = ldu4(a.aux + m1 * BN + cc);
-    }
-  }
+  if (IN0 && !IN0_PRE) load_in0();
+  if (IN1 && !IN1_PRE) load_in1();
 
   // ---- epilogues.  acc[i][j][q] is C[row, col] with
-  //   row = m0 + wm*BM/2 + i*16 + lr,  col = n0 + wn*BN/2 + j*16 + lg*4 + q
+  //   row = m0 + wm*BM/2 + i*16 + lr,  col = n0 + wn*BN/WC + j*16 + lg*4 + q
   // Global traffic goes through the LDS tile [BM][TS] in 16-byte row chunks: residual / x-hat
   // inputs are loaded into it, outputs are written into it and copied out row by row.
-  const int cb0 = wn * (BN / 2) + lg * 4;  // tile column of q = 0 for j = 0
+  const int cb0 = wn * (BN / WC) + lg * 4;  // tile column of q = 0 for j = 0
   auto rloc = [&](int i) { return wm * (BM / 2) + i * 16 + lr; };
 
-  // per-row element offsets: ROWS_COMPACT with leading dimension ld, ROWS_NATIVE, or the
-  // head-major item layout (offset of row m's (head 0, dim 0); -1 where K/V do not exist)
-  auto set_rows = [&](int mode, int64_t ld, int hm_part) {
-    if (tid < BM) {
-      const int64_t m = m0 + tid;
-      int64_t off = -1;
-      if (m < a.M) {
-        if (hm_part >= 0) {
-          const int64_t col = m / g.R;
-          const int r = (int)(m - col * g.R);
-          if (hm_part == 0 || r < g.col_ntr[col])
-            off = (col * g.heads * g.R + r) * (int64_t)g.d;
-        } else {
-          off = mode == ROWS_NATIVE ? native_cell(g, m) * g.E : m * ld;
-        }
-      }
-      rbase[tid] = off;
-    }
-  };
   // tile <- prefetched rows
   auto fill_tile = [&](const uint4* pin) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int ch = tid + 256 * c;
+      const int ch = tid + NT * c;
       stu4(&tile[(ch / CPRW) * TS + (ch % CPRW) * 8], pin[c]);
     }
   };
-  // rows of dst <- tile (columns [c0, c0 + BN)); head-major destinations when hm is set
-  auto store_tile = [&](bf16* dst, int c0, bool hm) {
-    for (int ch = tid; ch < BM * CPRW; ch += 256) {
+  // head-major offset of tile column cc within its part
+  auto hm_col = [&](int cc) -> int64_t {
+    const int k = pc0 + cc;
+    return (int64_t)(k >> dsh) * g.R * g.d + (k & (g.d - 1));
+  };
+  // rows of dst at rout <- tile (columns [c0, c0 + BN)); head-major columns for Q|K|V
+  auto store_tile = [&](bf16* dst, int c0) {
+    for (int ch = tid; ch < BM * CPRW; ch += NT) {
       const int row = ch / CPRW, cc = (ch % CPRW) * 8;
-      const int64_t off = rbase[row];
+      const int64_t off = rout[row];
       if (off < 0) continue;
-      int64_t o = off + c0 + cc;
-      if (hm) {
-        const int head = (pc0 + cc) / g.d, jj = pc0 + cc - head * g.d;
-        o = off + (int64_t)head * g.R * g.d + jj;
-      }
-      stu4(dst + o, ldu4(&tile[row * TS + cc]));
+      stu4(dst + off + (QKV ? hm_col(cc) : (int64_t)(c0 + cc)), ldu4(&tile[row * TS + cc]));
+    }
+  };
+  // compact rows of dst <- tile
+  auto store_compact = [&](bf16* dst) {
+    for (int ch = tid; ch < BM * CPRW; ch += NT) {
+      const int row = ch / CPRW, cc = (ch % CPRW) * 8;
+      if (m0 + row < a.M) stu4(dst + (m0 + row) * BN + cc, ldu4(&tile[row * TS + cc]));
     }
   };
   // the lane's 4 consecutive tile elements of block (i, j), and the matching parameters
@@ -359,10 +411,6 @@ k_gemm(GemmArgs a) {
   };
 
   if (HALF) {
-    if (EPI == EPI_ITEM_QKV)
-      set_rows(ROWS_COMPACT, 0, part);
-    else
-      set_rows(ROWS_COMPACT, a.ldo, -1);
     // item K is stored pre-multiplied by log2(e)/sqrt(d) (in fp32, before the bf16 rounding):
     // the attention kernels then get scores in the exp2 domain straight from the MFMA
     const float ksc =
@@ -384,26 +432,17 @@ k_gemm(GemmArgs a) {
         }
       }
       lds_barrier();
-      for (int ch = tid; ch < (BM / 2) * CPRW; ch += 256) {
+      for (int ch = tid; ch < (BM / 2) * CPRW; ch += NT) {
         const int rl = ch / CPRW, cc = (ch % CPRW) * 8;
-        const int64_t off = rbase[h * (BM / 2) + rl];
+        const int64_t off = rout[h * (BM / 2) + rl];
         if (off < 0) continue;
-        int64_t o = off + (EPI == EPI_ITEM_QKV ? 0 : n0) + cc;
-        if (EPI == EPI_ITEM_QKV) {
-          const int head = (pc0 + cc) / g.d, jj = pc0 + cc - head * g.d;
-          o = off + (int64_t)head * g.R * g.d + jj;
-        }
-        stu4(dst + o, ldu4(&tile[rl * TS + cc]));
+        stu4(dst + off + (QKV ? hm_col(cc) : (int64_t)(n0 + cc)), ldu4(&tile[rl * TS + cc]));
       }
       lds_barrier();  // the next half overwrites the tile
     }
     return;
   }
   if (EPI == EPI_BIAS || EPI == EPI_GELU_FWD || EPI == EPI_ITEM_QKV) {
-    if (EPI == EPI_ITEM_QKV)
-      set_rows(ROWS_COMPACT, 0, part);
-    else
-      set_rows(ROWS_COMPACT, a.ldo, -1);
     // item K is stored pre-multiplied by log2(e)/sqrt(d) (in fp32, before the bf16 rounding):
     // the attention kernels then get scores in the exp2 domain straight from the MFMA
     const float ksc =
@@ -417,11 +456,11 @@ k_gemm(GemmArgs a) {
     lds_barrier();
     if (EPI == EPI_ITEM_QKV) {
       bf16* dst = part == 0 ? a.out : (part == 1 ? a.out2 : a.out3);
-      store_tile(dst, 0, true);
+      store_tile(dst, 0);
       return;
     }
     // the GELU epilogue may skip the pre-activation store (out == nullptr: forward-only calls)
-    if (EPI != EPI_GELU_FWD || a.out) store_tile(a.out, n0, false);
+    if (EPI != EPI_GELU_FWD || a.out) store_tile(a.out, n0);
     if (EPI == EPI_GELU_FWD) {
       // U = GELU of the stored (bf16) pre-activation, computed in place of the accumulators
 #pragma unroll
@@ -438,13 +477,13 @@ k_gemm(GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < NB; ++j) put4(i, j, acc[i][j]);
       lds_barrier();
-      store_tile(a.out2, n0, false);
+      store_tile(a.out2, n0);
     }
     return;
   }
 
   if (EPI == EPI_GELU_BWD) {
-    fill_tile(pin0);  // rbase still holds the compact rows (leading dimension ldo)
+    fill_tile(pin0);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -460,7 +499,7 @@ k_gemm(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, acc[i][j]);
     lds_barrier();
-    store_tile(a.out, n0, false);
+    store_tile(a.out, n0);
     return;
   }
 
@@ -476,35 +515,48 @@ k_gemm(GemmArgs a) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, acc[i][j]);
-    set_rows(ROWS_NATIVE, 0, -1);
     lds_barrier();
-    store_tile(a.out, 0, false);
+    store_tile(a.out, 0);
     return;
   }
 
   // ---- LayerNorm epilogues (BN == E, n0 == 0): row statistics across the lane groups of a
   // wave and the two column waves.  The accumulators are overwritten in place.
   auto& val = acc;
-  // sum over the row's BN columns of f(i, j) (a 4-vector per block) -> per-row value
-  auto row_sum = [&](auto f, float* out) {
+  // mean over the row's BN columns of f(i, j) (a 4-vector per block) -> per-row value.  The sum is
+  // formed per 32 columns (two blocks of one wave), and those are added in order, so that a row's
+  // statistics do not depend on the tile's shape or its number of waves: the forward-only calls
+  // give the training forward's rows bit for bit.
+  // The forward norms leave no product to be fused at the compiler's choice, which differs
+  // between tile shapes (contract(off), explicit fmaf).
+  auto add4 = [](const f32x4& v) { return (v[0] + v[1]) + (v[2] + v[3]); };
+  auto sq4 = [](const f32x4& v) {
+#pragma clang fp contract(off)
+    return fmaf(v[0], v[0], v[1] * v[1]) + fmaf(v[2], v[2], v[3] * v[3]);
+  };
+  auto row_sum = [&](auto f, auto sum, float* out) {
+#pragma clang fp contract(off)
+    static_assert(!GAMMA || NB % 2 == 0, "32-column units");
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      float sm = 0.f;
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x4 v = f(i, j);
-        sm += (v[0] + v[1]) + (v[2] + v[3]);
+      for (int u = 0; u < NB / 2; ++u) {
+        const float sm = rows4_sum(sum(f(i, 2 * u)) + sum(f(i, 2 * u + 1)));
+        if (lg == 0) red[wn * (NB / 2) + u][rloc(i)] = sm;
       }
-      sm = rows4_sum(sm);
-      if (lg == 0) red[wn][rloc(i)] = sm;
-    }
     lds_barrier();
 #pragma unroll
-    for (int i = 0; i < MI; ++i) out[i] = (red[0][rloc(i)] + red[1][rloc(i)]) * (1.0f / BN);
+    for (int i = 0; i < MI; ++i) {
+      float sm = red[0][rloc(i)];
+#pragma unroll
+      for (int x = 1; x < BN / 32; ++x) sm += red[x][rloc(i)];
+      out[i] = sm * (1.0f / BN);
+    }
     lds_barrier();
   };
 
   if (EPI == EPI_LN) {
+#pragma clang fp contract(off)
     fill_tile(pin0);
     lds_barrier();
     if (a.rgamma) {  // the residual arrives as x-hat of the previous norm: rgamma x-hat + rbeta
@@ -523,11 +575,8 @@ k_gemm(GemmArgs a) {
       }
     }
     float mean[MI], var[MI];
-    row_sum([&](int i, int j) { return val[i][j]; }, mean);
-    row_sum([&](int i, int j) {
-      const f32x4 dv = val[i][j] - mean[i];
-      return dv * dv;
-    }, var);
+    row_sum([&](int i, int j) { return val[i][j]; }, add4, mean);
+    row_sum([&](int i, int j) { return val[i][j] - mean[i]; }, sq4, var);
     // x-hat in place of val; rstd per row
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -551,30 +600,36 @@ k_gemm(GemmArgs a) {
         for (int i = 0; i < MI; ++i) put4(i, j, gm * val[i][j] + bt);
       }
     }
-    set_rows(a.omode, BN, -1);
     lds_barrier();
-    store_tile(a.out, 0, false);
+    store_tile(a.out, 0);
     if (!a.xhat) return;
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, val[i][j]);
-    set_rows(ROWS_COMPACT, BN, -1);
     lds_barrier();
-    store_tile(a.xhat, 0, false);
+    store_compact(a.xhat);
     return;
   }
 
   if (EPI == EPI_LN_BWD) {
     // dh = acc + resid; du = rstd * (g - mean(g) - xhat * mean(g * xhat)), g = dh * gamma;
     // column partial sums of dh * xhat (dgamma) and dh (dbeta) per workgroup
-    fill_tile(pin0);  // rbase still holds the compact rows
+    fill_tile(pin0);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) val[i][j] = acc[i][j] + tile4(i, j);
+    if (m0 + BM > a.M) {  // rows past M hold the last row's residual: nothing for column sums
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+        if (m0 + rloc(i) >= a.M) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) val[i][j] = zero4();
+        }
+    }
     lds_barrier();
     fill_tile(pin1);  // x-hat stays in the tile for the rest of the epilogue
     lds_barrier();
@@ -597,13 +652,13 @@ k_gemm(GemmArgs a) {
       }
     }
     float m1[MI], m2[MI];
-    row_sum([&](int i, int j) { return val[i][j] * par4(1, j); }, m1);
+    row_sum([&](int i, int j) { return val[i][j] * par4(1, j); }, add4, m1);
     if (tid < BN) {
       float* pg = a.part + bx * 2 * BN;
       pg[tid] = cred[0][0][tid] + cred[0][1][tid];
       pg[BN + tid] = cred[1][0][tid] + cred[1][1][tid];
     }
-    row_sum([&](int i, int j) { return val[i][j] * par4(1, j) * tile4(i, j); }, m2);
+    row_sum([&](int i, int j) { return val[i][j] * par4(1, j) * tile4(i, j); }, add4, m2);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const float rs = m0 + rloc(i) < a.M ? a.rstd_in[m0 + rloc(i)] : 0.f;
@@ -617,12 +672,13 @@ k_gemm(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, val[i][j]);
     lds_barrier();
-    store_tile(a.out, 0, false);
+    store_tile(a.out, 0);
     return;
   }
 
   // ---- pre-norm RMSNorm epilogues (BN == E, n0 == 0)
   if (EPI == EPI_RMS) {
+#pragma clang fp contract(off)
     // h = C + bias + rscale * resid -> out; r = gamma h / sqrt(mean(h^2) + eps) -> out2
     fill_tile(pin0);
     lds_barrier();
@@ -633,14 +689,13 @@ k_gemm(GemmArgs a) {
       for (int i = 0; i < MI; ++i) val[i][j] = acc[i][j] + b + a.rscale * tile4(i, j);
     }
     float ms[MI];
-    row_sum([&](int i, int j) { return val[i][j] * val[i][j]; }, ms);
+    row_sum([&](int i, int j) { return val[i][j]; }, sq4, ms);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, val[i][j]);
-    set_rows(ROWS_COMPACT, BN, -1);
     lds_barrier();
-    store_tile(a.out, 0, false);
+    store_tile(a.out, 0);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -650,7 +705,7 @@ k_gemm(GemmArgs a) {
       for (int j = 0; j < NB; ++j) put4(i, j, par4(1, j) * val[i][j] * rs);
     }
     lds_barrier();
-    store_tile(a.out2, 0, false);
+    store_tile(a.out2, 0);
     return;
   }
 
@@ -674,7 +729,7 @@ k_gemm(GemmArgs a) {
       }
     }
     float m1[MI];
-    row_sum([&](int i, int j) { return par4(1, j) * acc[i][j] * tile4(i, j) * rsi[i]; }, m1);
+    row_sum([&](int i, int j) { return par4(1, j) * acc[i][j] * tile4(i, j) * rsi[i]; }, add4, m1);
     if (tid < BN) a.part[bx * BN + tid] = cred[0][0][tid] + cred[0][1][tid];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -693,9 +748,8 @@ k_gemm(GemmArgs a) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) put4(i, j, val[i][j]);
-    set_rows(a.omode, BN, -1);
     lds_barrier();
-    store_tile(a.out, 0, false);
+    store_tile(a.out, 0);
     return;
   }
 }
@@ -764,6 +818,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_wr(GemmArgs a) {
   const int64_t nst = ntile * KT;
   const int part = EPI == EPI_ITEM_QKV ? n0 / g.E : 0;
   const int pc0 = n0 - part * g.E;
+  const int dsh = 31 - __builtin_clz(g.d);  // d is a power of two
 
   // this wave's weight slice: output columns n0 + wn * BN / WN + j * 16 + lr, k 8 lg (+ 32 ks)
   bf16x8 bfr[KT][NB];
@@ -841,8 +896,8 @@ __global__ __launch_bounds__(512, 1) void k_gemm_wr(GemmArgs a) {
       int64_t off = -1;
       if (m < a.M) {
         if (EPI == EPI_ITEM_QKV) {
-          const int64_t col = m / g.R;
-          const int r = (int)(m - col * g.R);
+          int r;
+          const int64_t col = cell_col(g, m, &r);
           if (part == 0 || r < g.col_ntr[col]) off = (col * g.heads * g.R + r) * (int64_t)g.d;
         } else {
           off = m * a.ldo + n0;
@@ -872,8 +927,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_wr(GemmArgs a) {
       if (off < 0) continue;
       int64_t o = off + cc;
       if (EPI == EPI_ITEM_QKV) {
-        const int head = (pc0 + cc) / g.d, jd = pc0 + cc - head * g.d;
-        o = off + (int64_t)head * g.R * g.d + jd;
+        o = off + (int64_t)((pc0 + cc) >> dsh) * g.R * g.d + ((pc0 + cc) & (g.d - 1));
       }
       // saved tensors read only by later kernels (the Q|K|V projections) stream past the caches;
       // the single-tile products' outputs, which the next kernel reads, do not
@@ -917,7 +971,7 @@ static hipError_t gemm_wr_dispatch(const GemmArgs& a, hipStream_t s) {
 // through five pre-norm blocks (2 tiles) 678 -> 517 us; 1,056 tiles (8 x 512 x 33) 1,444 us
 // with 128 rows, 1,457 us with 64.
 // Launches that 32-row tiles keep within one workgroup a CU take those: eight query rows 480 ->
-// 452 us.
+// 440 us.
 constexpr int64_t GEMM_FILL = 700, GEMM_DEEP = 256;
 static int gemm_bm(int epi, int BN, int N, int64_t M) {
   if ((M + 31) / 32 * (N / BN) <= GEMM_DEEP) return 32;
@@ -936,17 +990,17 @@ static hipError_t gemm_epi(const GemmArgs& a, hipStream_t s) {
   const int64_t mt = (a.M + BM - 1) / BM;
   const dim3 grid((unsigned)((mt + 7) / 8 * 8 * (a.N / BN)));
   switch (a.epi) {
-    case EPI_BIAS: k_gemm<BN, EPI_BIAS, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_GELU_FWD: k_gemm<BN, EPI_GELU_FWD, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_GELU_BWD: k_gemm<BN, EPI_GELU_BWD, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_ITEM_QKV: k_gemm<BN, EPI_ITEM_QKV, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_LN: k_gemm<BN, EPI_LN, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_DX: k_gemm<BN, EPI_DX, BM><<<grid, 256, 0, s>>>(a); break;
-    case EPI_RMS: k_gemm<BN, EPI_RMS, BM><<<grid, 256, 0, s>>>(a); break;
+    case EPI_BIAS: k_gemm<BN, EPI_BIAS, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_GELU_FWD: k_gemm<BN, EPI_GELU_FWD, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_GELU_BWD: k_gemm<BN, EPI_GELU_BWD, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_ITEM_QKV: k_gemm<BN, EPI_ITEM_QKV, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_LN: k_gemm<BN, EPI_LN, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_DX: k_gemm<BN, EPI_DX, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
+    case EPI_RMS: k_gemm<BN, EPI_RMS, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a); break;
     default:
       if constexpr (BM < 128 || BN <= 192) {
-        if (a.epi == EPI_LN_BWD) k_gemm<BN, EPI_LN_BWD, BM><<<grid, 256, 0, s>>>(a);
-        else if (a.epi == EPI_RMS_BWD) k_gemm<BN, EPI_RMS_BWD, BM><<<grid, 256, 0, s>>>(a);
+        if (a.epi == EPI_LN_BWD) k_gemm<BN, EPI_LN_BWD, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a);
+        else if (a.epi == EPI_RMS_BWD) k_gemm<BN, EPI_RMS_BWD, BM><<<grid, 64 * (gemm_waves<BN, BM>()), 0, s>>>(a);
         else return hipErrorInvalidValue;
       } else {
         return hipErrorInvalidValue;

@@ -1,0 +1,42 @@
+"""The forward-only calls give the training forward's rows bit for bit although their GEMM launches
+take other tile shapes: a training forward of 97,200 cells runs 128-row tiles, its context call the
+same, and query chunks of 81 to 3,240 cells run 32- and 64-row tiles."""
+
+import numpy as np
+import pytest
+
+from paper_2606_03681_amd import workloads as wl
+
+from _harness import storage_of
+
+pytestmark = pytest.mark.gpu
+
+# block, E, heads, H
+CASES = [("post", 192, 6, 768), ("post", 64, 2, 128), ("pre", 256, 4, 768), ("pre", 128, 2, 384)]
+
+
+@pytest.mark.parametrize("block,E,heads,H", CASES)
+def test_rows_do_not_depend_on_tile_shape(monkeypatch, block, E, heads, H):
+    import torch
+    from paper_2606_03681_amd import tfm
+    from paper_2606_03681_amd.stack import InferStack, Stack, to_device
+    R, n, C = 1200, 500, 80
+    cfg = dict(name="shape", dtype="bf16", B=1, R=R, n_train=n, C=C, E=E, heads=heads, H=H,
+               layers=1, cells="normal", weights="xavier_bias", block=block)
+    monkeypatch.setitem(wl.TEST_CONFIGS, "shape", cfg)
+    w = wl.make_workload("shape", with_dY=False)
+
+    def dims(rows):
+        return tfm.make_dims(1, rows, C, E, heads, H, "bf16", block)
+
+    full = storage_of(Stack(dims(R), w.n_train, w.cell_mask, w.params).forward(
+        to_device(w.X, "bf16")), "bf16")
+    cuts = [1159, 1160, 1165, 1200]                     # query chunks of 1, 5 and 35 rows
+    inf = InferStack(dims(cuts[0]), w.n_train, w.cell_mask, w.params, max_query_rows=40)
+    got = [storage_of(inf.context(to_device(np.ascontiguousarray(w.X[:, :cuts[0]]), "bf16")),
+                      "bf16")]
+    for a, b in zip(cuts, cuts[1:]):
+        got.append(storage_of(inf.query(to_device(np.ascontiguousarray(w.X[:, a:b]), "bf16")),
+                              "bf16"))
+    torch.cuda.synchronize()
+    assert np.array_equal(np.concatenate(got, axis=1), full)
