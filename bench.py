@@ -294,7 +294,8 @@ def main():
     steps_out = {}
     if prof:
         mfma_path = w.dtype == "bf16"
-        fl = step_flops(w, tfm.prof_item_bwd_fused_rows(cfg["E"] // cfg["heads"]) if mfma_path
+        one_kernel = mfma_path and any(k.startswith("item_attn_bwd/") for k in prof)
+        fl = step_flops(w, tfm.prof_item_bwd_fused_rows(cfg["E"] // cfg["heads"]) if one_kernel
                         else 0)
         for name, (n, ms) in sorted(prof.items(), key=lambda kv: -kv[1][1]):
             steps_out[name] = {"launches": n, "avg_ms": round(ms / n, 5),

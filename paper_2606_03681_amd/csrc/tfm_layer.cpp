@@ -394,7 +394,8 @@ int item_attn_bwd(const Dims& d, const tfm::Geo& g, const Plan& P, char* ws, con
                   tfm::bf16* dq, tfm::bf16* dk, tfm::bf16* dv, hipStream_t s) {
   using namespace tfm;
   const int32_t* dcols = P.natural ? nullptr : (const int32_t*)(ws + M.cord);
-  const int nF = P.nF, nmaxF = P.nmaxF;
+  const int nmaxF = P.nmaxF;
+  const int nF = item_attn_bwd_fused_pays(d.d, (int64_t)P.nF * d.heads, d.R, nmaxF) ? P.nF : 0;
   const ColList F{dcols, nF};
   const ColList T{dcols ? dcols + nF : nullptr, P.NC - nF};
   if (nF > 0)
