@@ -47,14 +47,15 @@ __device__ __forceinline__ int64_t native32(const Geo& g, int64_t p) {
 }
 
 // ---- weight gradients -------------------------------------------------------------------------
-// Contraction over cells: a workgroup sums one chunk of cells into a 64 x 64 tile of one weight
-// gradient, four waves of 32 x 32, 32 cells per step through two LDS buffers with the next
-// step's rows already in flight.  Both operands are read as rows of features (the contraction
-// index is the slow one), row stride 68 floats: the four lane groups of a fragment read take
-// cells 4 apart, 16 banks apart.  All products of a backward pass are one launch: on a table of
+// Contraction over cells: a workgroup sums one chunk of cells into a TS x TS tile of one weight
+// gradient, four waves of TS/2 x TS/2, 32 cells per step through two LDS buffers with the next
+// step's rows already in flight.  TS is 96 where E is a multiple of it (24 instead of 16 products
+// for every float read: 21,000 cells, E = 192, H = 768 in 340 instead of 379 us), else 64.
+// Both operands are read as rows of features (the contraction index is the slow one), row stride
+// TS + 4 floats: the four lane groups of a fragment read take cells 4 apart, 16 banks apart.  All products of a backward pass are one launch: on a table of
 // a few thousand cells no single one of them has enough tiles to fill the chip.
 constexpr int WM = 32;   // cells per step
-constexpr int WLS = 68;  // LDS row stride (floats)
+int f32_tile(int E) { return E % 96 == 0 ? 96 : 64; }
 
 template <class T>
 __device__ __forceinline__ float4 wg_load(const Geo& g, const T* p0, const T* p1, const T* p2,
@@ -70,8 +71,9 @@ __device__ __forceinline__ float4 wg_load(const Geo& g, const T* p0, const T* p1
   return ld4((part == 0 ? p0 : (part == 1 ? p1 : p2)) + off);
 }
 
-template <class T>
+template <class T, int TS>
 __global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
+  constexpr int WLS = TS + 4, NB = TS / 32, CH = TS / 4, NI = WM * CH / 256;
   __shared__ __attribute__((aligned(16))) float Ys[2][WM * WLS];
   __shared__ __attribute__((aligned(16))) float Xs[2][WM * WLS];
   // the tiles of one chunk sit on one XCD next to each other: its rows come from memory once
@@ -84,34 +86,36 @@ __global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
   while (ji + 1 < a.n && tl >= a.j[ji + 1].tile0) ++ji;
   const F32WgradJob<T>& J = a.j[ji];
   const int t = tl - J.tile0;
-  const int n0 = (t % J.ntn) * 64, k0 = (t / J.ntn) * 64;
+  const int n0 = (t % J.ntn) * TS, k0 = (t / J.ntn) * TS;
   const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
   const int lg = lane >> 4, c = lane & 15;
-  const int wn = (w >> 1) * 32, wk = (w & 1) * 32;
-  const int sc = tid & 15, sr = tid >> 4;  // staging: 4 features from 4 sc of cells sr, sr + 16
-  float4 y[2], x[2];
+  const int wn = (w >> 1) * (TS / 2), wk = (w & 1) * (TS / 2);
+  // staging: piece p of a step is 4 features from 4 (p % CH) of cell p / CH
+  float4 y[NI], x[NI];
   auto gload = [&](int64_t m0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int64_t m = m0 + sr + 16 * i;
-      y[i] = wg_load<T>(a.g, J.Y, J.Y2, J.Y3, J.ymode, m, me, n0 + 4 * sc, J.N);
-      x[i] = wg_load<T>(a.g, J.X, nullptr, nullptr, J.xmode, m, me, k0 + 4 * sc, J.K);
+    for (int i = 0; i < NI; ++i) {
+      const int p = tid + 256 * i, f = 4 * (p % CH);
+      const int64_t m = m0 + p / CH;
+      y[i] = wg_load<T>(a.g, J.Y, J.Y2, J.Y3, J.ymode, m, me, n0 + f, J.N);
+      x[i] = wg_load<T>(a.g, J.X, nullptr, nullptr, J.xmode, m, me, k0 + f, J.K);
     }
   };
   auto sstore = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      st4(&Ys[b][(sr + 16 * i) * WLS + 4 * sc], y[i]);
-      st4(&Xs[b][(sr + 16 * i) * WLS + 4 * sc], x[i]);
+    for (int i = 0; i < NI; ++i) {
+      const int p = tid + 256 * i, at = (p / CH) * WLS + 4 * (p % CH);
+      st4(&Ys[b][at], y[i]);
+      st4(&Xs[b][at], x[i]);
     }
   };
-  f32x4 acc[2][2];
+  f32x4 acc[NB][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = zero4();
+    for (int j = 0; j < NB; ++j) acc[i][j] = zero4();
   const bool bias = k0 == 0;  // this tile also sums its columns of Y, 8 cells a wave and step
-  float bs = 0.f;
+  float bs[2] = {0.f, 0.f};  // columns lane and 64 + lane
   gload(mb);
   sstore(0);
   __syncthreads();
@@ -122,30 +126,33 @@ __global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
 #pragma unroll
     for (int s = 0; s < WM / 4; ++s) {
       const int row = 4 * lg + (s & 3) + 16 * (s >> 2);
-      float av[2], bv[2];
+      float av[NB], bv[NB];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < NB; ++i) {
         av[i] = Ys[b][row * WLS + wn + 16 * i + c];
         bv[i] = Xs[b][row * WLS + wk + 16 * i + c];
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(av[i], bv[j], acc[i][j]);
+        for (int j = 0; j < NB; ++j) acc[i][j] = mfma32(av[i], bv[j], acc[i][j]);
     }
     if (bias) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) bs += Ys[b][(8 * w + r) * WLS + lane];
+      for (int r = 0; r < 8; ++r) {
+        bs[0] += Ys[b][(8 * w + r) * WLS + lane];
+        if (TS > 64 && lane < TS - 64) bs[1] += Ys[b][(8 * w + r) * WLS + 64 + lane];
+      }
     }
     if (more) sstore(b ^ 1);
     __syncthreads();
   }
   float* out = J.part + (int64_t)z * J.N * J.K;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < NB; ++i) {
     const int n = n0 + wn + 16 * i + 4 * lg;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NB; ++j) {
       const int k = k0 + wk + 16 * j;
       if (n >= J.N || k >= J.K) continue;
 #pragma unroll
@@ -153,11 +160,13 @@ __global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
     }
   }
   if (bias) {
-    Ys[0][tid] = bs;
+    float* R = Ys[0];
+    R[w * 128 + lane] = bs[0];
+    R[w * 128 + 64 + lane] = bs[1];
     __syncthreads();
-    if (tid < 64 && n0 + tid < J.N)
+    if (tid < TS && n0 + tid < J.N)
       J.bpart[(int64_t)z * J.N + n0 + tid] =
-          (Ys[0][tid] + Ys[0][64 + tid]) + (Ys[0][128 + tid] + Ys[0][192 + tid]);
+          (R[tid] + R[128 + tid]) + (R[256 + tid] + R[384 + tid]);
   }
 }
 
@@ -429,20 +438,27 @@ __global__ __launch_bounds__(256) void k_f32_linear(F32LinArgs<T> a) {
   }
 }
 
-int f32_tiles(int N, int K) { return ((N + 63) / 64) * ((K + 63) / 64); }
+int f32_tiles(int ts, int N, int K) { return ((N + ts - 1) / ts) * ((K + ts - 1) / ts); }
+int f32_all_tiles(int E, int H) {
+  const int ts = f32_tile(E);
+  return 2 * (f32_tiles(ts, 3 * E, E) + f32_tiles(ts, E, E) + f32_tiles(ts, H, E));
+}
+// Chunks asked for; never falls as N grows.
+int64_t f32_want(int64_t N, int E, int H) {
+  // enough workgroups for the chip, at least 64 cells and at most 2,048 in a chunk: a chunk's
+  // partial tile (written and read once) is then no more than its operands' traffic, and no chain
+  // of sums is longer
+  const int tiles = f32_all_tiles(E, H);
+  const int64_t fill = (2048 + tiles - 1) / tiles;
+  return std::max<int64_t>(
+      1, std::min<int64_t>((N + 63) / 64, std::max<int64_t>(fill, (N + 2047) / 2048)));
+}
 
 }  // namespace
 
 F32Split f32_split(int64_t N, int E, int H) {
-  const int tiles = 2 * (f32_tiles(3 * E, E) + f32_tiles(E, E) + f32_tiles(H, E));
-  // enough workgroups for the chip, at least 64 cells and at most 2,048 in a chunk: a chunk's
-  // partial tile (16 KB, written and read once) is then no more than its operands' traffic, and
-  // no chain of sums is longer
-  const int64_t fill = (2048 + tiles - 1) / tiles;
-  int64_t Z = std::min<int64_t>((N + 63) / 64, std::max<int64_t>(fill, (N + 2047) / 2048));
-  if (Z < 1) Z = 1;
-  int64_t chunk = (N + Z - 1) / Z;
-  chunk = std::max<int64_t>((chunk + WM - 1) / WM * WM, WM);
+  const int64_t Z = f32_want(N, E, H);
+  const int64_t chunk = std::max<int64_t>(((N + Z - 1) / Z + WM - 1) / WM * WM, WM);
   return F32Split{(int)std::max<int64_t>((N + chunk - 1) / chunk, 1), chunk};
 }
 
@@ -452,11 +468,8 @@ int f32_ln_rows(int64_t N) {
 
 size_t f32_wpart_floats(int64_t Nmax, int E, int H) {
   // chunk rounding may leave fewer chunks than asked for, never more
-  const int tiles = 2 * (f32_tiles(3 * E, E) + f32_tiles(E, E) + f32_tiles(H, E));
-  const int64_t fill = (2048 + tiles - 1) / tiles;
-  const int64_t Z = std::max<int64_t>(
-      1, std::min<int64_t>((Nmax + 63) / 64, std::max<int64_t>(fill, (Nmax + 2047) / 2048)));
-  return (size_t)Z * (8 * (size_t)E * E + 2 * (size_t)E * H + 9 * (size_t)E + H);
+  return (size_t)f32_want(Nmax, E, H) *
+         (8 * (size_t)E * E + 2 * (size_t)E * H + 9 * (size_t)E + H);
 }
 
 size_t f32_lnpart_floats(int64_t Nmax, int E) { return (size_t)f32_ln_rows(Nmax) * 2 * E * 3; }
@@ -468,12 +481,15 @@ hipError_t launch_f32_wgrads(F32WgradArgs<T>& a, const F32Split& sp, hipStream_t
   a.Z = sp.Z;
   a.chunk = sp.chunk;
   a.tiles = 0;
+  const int ts = f32_tile(a.g.E);
   for (int i = 0; i < a.n; ++i) {
     a.j[i].tile0 = a.tiles;
-    a.j[i].ntn = (a.j[i].N + 63) / 64;
-    a.tiles += f32_tiles(a.j[i].N, a.j[i].K);
+    a.j[i].ntn = (a.j[i].N + ts - 1) / ts;
+    a.tiles += f32_tiles(ts, a.j[i].N, a.j[i].K);
   }
-  k_f32_wgrads<T><<<(unsigned)((sp.Z + 7) / 8 * 8 * a.tiles), 256, 0, s>>>(a);
+  const unsigned grid = (unsigned)((sp.Z + 7) / 8 * 8 * a.tiles);
+  if (ts == 96) k_f32_wgrads<T, 96><<<grid, 256, 0, s>>>(a);
+  else k_f32_wgrads<T, 64><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 

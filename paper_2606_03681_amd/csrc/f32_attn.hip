@@ -43,6 +43,9 @@ __device__ __forceinline__ float el(const float4& v, int j) {
 __device__ __forceinline__ float dot4(const float4& a, const float4& b) {
   return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, a.w * b.w)));
 }
+// Queries (keys, on the key side) are scaled by log2(e) / sqrt(d) as they are loaded, so that
+// scores are exponents of 2 for v_exp_f32; log-sum-exps are kept in the natural base.
+constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.69314718055994531f;
 __device__ __forceinline__ float4 scale4(const float4& a, float f) {
   return make_float4(a.x * f, a.y * f, a.z * f, a.w * f);
 }
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
   const float tau = 1.0f / sqrtf((float)D);
   Row<D> qf = ld_row<D>(q + (base + r) * D, rok, lg);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) qf.v[i] = scale4(qf.v[i], tau);
+  for (int i = 0; i < NB; ++i) qf.v[i] = scale4(qf.v[i], tau * LOG2E);
   f32x4 acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) acc[i] = zero4();
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
       }
     }
     const float mn = fmaxf(mx, rows4_max(tm));  // finite: every tile holds a key below n
-    const float al = expf(mx - mn);
+    const float al = exp2_hw(mx - mn);
     mx = mn;
     sum *= al;
 #pragma unroll
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float p = expf(s[kb][x] - mx);
+        const float p = exp2_hw(s[kb][x] - mx);
         sum += p;
         const float* vr = &Vs[b][(16 * kb + 4 * lg + x) * LS + c];
 #pragma unroll
@@ -188,7 +191,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
 #pragma unroll
   for (int i = 0; i < NB; ++i)
     st4(o + (P.col * g.R + r) * g.E + P.head * D + 16 * i + 4 * lg, acc[i] * inv);
-  if (lg == 0) lse[base + r] = mx + logf(sum);
+  if (lg == 0) lse[base + r] = fmaf(mx, LN2, logf(sum));
 }
 
 template <class T, int D>
@@ -215,11 +218,11 @@ __global__ __launch_bounds__(256) void k_f32_item_dq(Geo g, const T* __restrict_
   float Dr = 0.f;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    qf.v[i] = scale4(qf.v[i], tau);
+    qf.v[i] = scale4(qf.v[i], tau * LOG2E);
     Dr += dot4(df.v[i], of.v[i]);
   }
   Dr = rows4_sum(Dr);
-  const float L = rok ? lse[base + r] : 0.f;
+  const float L = rok ? lse[base + r] * LOG2E : 0.f;
   if (rok && lg == 0) Dbuf[base + r] = Dr;
   f32x4 acc[NB];
 #pragma unroll
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dq(Geo g, const T* __restrict_
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const bool in = k0 + 16 * kb + 4 * lg + x < n;
-        const float ds = in ? expf(s[x] - L) * (dp[x] - Dr) : 0.f;
+        const float ds = in ? exp2_hw(s[x] - L) * (dp[x] - Dr) : 0.f;
         const float* kr = &Ks[b][(16 * kb + 4 * lg + x) * LS + c];
 #pragma unroll
         for (int i = 0; i < NB; ++i) acc[i] = mfma32(kr[16 * i], ds, acc[i]);
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
   Row<D> kf = ld_row<D>(k + (base + t) * D, tok, lg);
   const Row<D> vf = ld_row<D>(v + (base + t) * D, tok, lg);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau);
+  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau * LOG2E);
   f32x4 ak[NB], av[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) ak[i] = av[i] = zero4();
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
     st.load(q + base * D, D, od, g.E, r0, g.R);
     // rows past the end: zero dO, L and D give P = 1 against zero rows
     const bool ok = tid < TK && r0 + tid < g.R;
-    sl = ok ? lse[base + r0 + tid] : 0.f;
+    sl = ok ? lse[base + r0 + tid] * LOG2E : 0.f;
     sd = ok ? Dbuf[base + r0 + tid] : 0.f;
   };
   auto store = [&](int b) __attribute__((always_inline)) {
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const int row = 16 * qb + 4 * lg + x;
-        const float p = expf(s[x] - Ls[b][row]);
+        const float p = exp2_hw(s[x] - Ls[b][row]);
         const float ds = p * (dp[x] - Ds[b][row]);
         const float* qr = &Qs[b][row * LS + c];
         const float* orow = &Os[b][row * LS + c];
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_fwd(Geo g, const T* __restrict
   const int64_t pq = qok ? cell(kq) : 0;
   Row<D> qf = ld_row<D>(qkv + pq * E3 + hd, qok, lg);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) qf.v[i] = scale4(qf.v[i], tau);
+  for (int i = 0; i < NB; ++i) qf.v[i] = scale4(qf.v[i], tau * LOG2E);
   f32x4 acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) acc[i] = zero4();
@@ -402,14 +405,14 @@ __global__ __launch_bounds__(256) void k_f32_feat_fwd(Geo g, const T* __restrict
       tm = fmaxf(tm, s[x]);
     }
     const float mn = fmaxf(mx, rows4_max(tm));
-    const float al = expf(mx - mn);
+    const float al = exp2_hw(mx - mn);
     mx = mn;
     sum *= al;
 #pragma unroll
     for (int i = 0; i < NB; ++i) acc[i] *= al;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      const float p = expf(s[x] - mx);
+      const float p = exp2_hw(s[x] - mx);
       sum += p;
 #pragma unroll
       for (int i = 0; i < NB; ++i) acc[i] = mfma32(vv[x][i], p, acc[i]);
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_fwd(Geo g, const T* __restrict
   const float inv = 1.0f / sum;
 #pragma unroll
   for (int i = 0; i < NB; ++i) st4(o + pq * E + hd + 16 * i + 4 * lg, acc[i] * inv);
-  if (lg == 0) lse[pq * g.heads + F.head] = mx + logf(sum);
+  if (lg == 0) lse[pq * g.heads + F.head] = fmaf(mx, LN2, logf(sum));
 }
 
 // The wave's 16 cells first as queries (dQ, over every key), then as keys (dK, dV, over every
@@ -446,11 +449,11 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
     Row<D> qf = ld_row<D>(qkv + pc * E3 + hd, own, lg);
     const Row<D> df = ld_row<D>(dout + pc * E + hd, own, lg);
     const Row<D> of = ld_row<D>(o + pc * E + hd, own, lg);
-    const float L = own ? lse[pc * g.heads + F.head] : 0.f;
+    const float L = own ? lse[pc * g.heads + F.head] * LOG2E : 0.f;
     float Dr = 0.f;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      qf.v[i] = scale4(qf.v[i], tau);
+      qf.v[i] = scale4(qf.v[i], tau * LOG2E);
       Dr += dot4(df.v[i], of.v[i]);
     }
     Dr = rows4_sum(Dr);
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
       const f32x4 s = rows_dot<D>(kf, qf), dp = rows_dot<D>(vf, df);
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float ds = k0 + 4 * lg + x < F.S ? expf(s[x] - L) * (dp[x] - Dr) : 0.f;
+        const float ds = k0 + 4 * lg + x < F.S ? exp2_hw(s[x] - L) * (dp[x] - Dr) : 0.f;
 #pragma unroll
         for (int i = 0; i < NB; ++i) acc[i] = mfma32(kt[x][i], ds, acc[i]);
       }
@@ -486,7 +489,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
   Row<D> kf = ld_row<D>(qkv + pc * E3 + E + hd, own, lg);
   const Row<D> vf = ld_row<D>(qkv + pc * E3 + 2 * E + hd, own, lg);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau);
+  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau * LOG2E);
   f32x4 ak[NB], av[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) ak[i] = av[i] = zero4();
@@ -502,7 +505,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
       const int qq = q0 + 4 * lg + x;
       const bool ok = qq < F.S;
       const int64_t px = cell(qq);
-      Lx[x] = ok ? lse[px * g.heads + F.head] : 0.f;
+      Lx[x] = ok ? lse[px * g.heads + F.head] * LOG2E : 0.f;
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         qt[x][i] = ok ? ld(qkv + px * E3 + hd + c + 16 * i) : 0.f;
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
     for (int x = 0; x < 4; ++x) {
       const float Dx = __shfl(Dr, 4 * lg + x, 64);
       // a query past the end has zero rows: P = 1 adds zeros
-      const float pr = expf(s[x] - Lx[x]);
+      const float pr = exp2_hw(s[x] - Lx[x]);
       const float ds = pr * (dp[x] - Dx);
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
