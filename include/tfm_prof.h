@@ -29,8 +29,8 @@ int tfm_prof_step(int i, const char** name, long long* launches, double* total_m
 
 /* Attribution of the item-attention backward to steps, for tools that price each step: on the
  * bfloat16 MFMA path the columns whose train prefix has at most this many rows run in the
- * one-kernel backward (step "item_attn_bwd"); longer prefixes run in the two-kernel form
- * (steps "item_attn_dq" and "item_attn_dkdv").  Returns 0 when head_dim has no one-kernel form.
+ * one-kernel backward (step "item_attn_bwd") where their number fills it, else with the longer
+ * prefixes in the two-kernel form (steps "item_attn_dq" and "item_attn_dkdv").  Returns 0 when head_dim has no one-kernel form.
  * Pure host function: no device, no side effects. */
 int tfm_prof_item_bwd_fused_rows(int head_dim);
 

@@ -31,9 +31,6 @@ hipError_t launch_item_attn_dkdv(const Geo& g, const ColList& cl, const bf16* q,
 // among those columns.
 bool item_attn_bwd_fused_ok(const Geo& g, int nmax);
 int item_attn_bwd_fused_max_rows(int d);
-// Whether `problems` (column, head) problems of R rows and at most nmax keys that fit the
-// one-kernel form should take it.
-bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax);
 hipError_t launch_item_attn_bwd_fused(const Geo& g, const ColList& cl, int nmax, const bf16* q,
                                       const bf16* k, const bf16* v, const bf16* o,
                                       const bf16* dout, const float* lse, bf16* dq, bf16* dk,

@@ -673,25 +673,6 @@ static int fused_nkb(int d, int nmax) {
 
 bool item_attn_bwd_fused_ok(const Geo& g, int nmax) { return fused_nkb(g.d, nmax) > 0; }
 
-// The one-kernel form runs a problem per CU and pays for whole rounds of 256 and for whole
-// thirds of its 768 keys; the two kernels compute each probability twice but spread over rows and
-// keys.  Microseconds as measured over d in {16, 32}, 64 to 768 keys (R = 4/3 of them) and 84 to
-// 3,936 problems: a 32-row chunk of a round costs 1.7 / 2.1 / 2.57 (d = 16: 1.75, two problems a
-// CU / 1.95 / 2.27) for up to 256 / 512 / 768 keys; the two kernels 20 a call, 0.01 a problem and
-// 4.9e-7 (3.9e-7) a score of whole 128 x 128 tiles.  One against two, d = 32: 768 keys 83 / 75 us
-// at 126 problems, 166 / 135 at 264, 1,314 / 1,604 at 3,936; 512 keys 712 / 719 at 3,936; 384
-// keys 521 / 464; 128 keys 21 / 22 at 264.
-bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax) {
-  const int third = nmax <= 256 ? 0 : (nmax <= 512 ? 1 : 2);
-  const double c32[3] = {1.7, 2.1, 2.57}, c16[3] = {1.75, 1.95, 2.27};
-  const int64_t slots = d == 16 && third == 0 ? 512 : 256;
-  const double one = (double)((problems + slots - 1) / slots) * ((R + 31) / 32) *
-                     (d == 16 ? c16 : c32)[third];
-  const double tile = (double)((R + 127) / 128 * 128) * ((nmax + 127) / 128 * 128);
-  const double two = 20.0 + (double)problems * (0.01 + tile * (d == 16 ? 3.9e-7 : 4.9e-7));
-  return one <= 1.05 * two;
-}
-
 int item_attn_bwd_fused_max_rows(int d) { return fused_nkb(d, 1) > 0 ? 768 : 0; }
 
 template <int D>

@@ -1,10 +1,9 @@
 // Internal declarations shared by the host library and the HIP kernels.
 //
 // Internal cell order.  Each dataset b keeps only its S_b active cell columns.  Active
-// columns of all datasets are numbered globally, dataset-major: column g belongs to dataset
-// col_ds[g] and is native cell column col_c[g].  Active cell p is (column g = p / R, row
-// r = p % R), so every column is R consecutive cells — the item axis reads contiguous rows —
-// and the cells of row (b, r) are p = (col0[b] + k) * R + r, k in [0, S_b).
+// columns of all datasets are numbered globally, dataset-major.  Active cell p is (column
+// g = p / R, row r = p % R), so every column is R consecutive cells — the item axis reads
+// contiguous rows — and the cells of row (b, r) are p = (col0[b] + k) * R + r, k in [0, S_b).
 //
 // Item-axis Q/K/V are stored head-major per column: [g][head][R][d].
 #pragma once
@@ -28,12 +27,9 @@ struct Geo {
   int32_t NC;              // total active columns
   int64_t N;               // total active cells = NC * R
   const DsInfo* ds;        // [B]
-  const int32_t* col_ds;   // [NC] dataset of each active column
-  const int32_t* col_c;    // [NC] native cell column of each active column
   const int32_t* colmap;   // [B*S] native (b, c) -> global active column, or -1
-  // Per-column copies of the above that a kernel reads with one load instead of a dependent
-  // pair: the native cell index of the column's row 0, (col_ds * R) * S + col_c, and the
-  // train-prefix length of the column's dataset.
+  // Per active column: the native cell index of its row 0 (dataset b, cell column c: b R S + c)
+  // and the train-prefix length of its dataset.
   const int64_t* col_cell0;  // [NC]
   const int32_t* col_ntr;    // [NC]
   int32_t nmax;              // longest train prefix over the datasets

@@ -2,12 +2,12 @@
 //
 //   C[m, n] = sum_k A[m, k] * Bt[n, k]        (A: cells x K, Bt: [N][K] bf16 weights)
 //
-// Block tile 64 x BN (BN = E, the embedding width, so that one block owns whole cell rows and
-// LayerNorm can run in the epilogue), K streamed through LDS in steps of 32 with double
-// buffering.  Four waves in a 2 x 2 arrangement; each wave owns a 32 x BN/2 sub-tile held as
-// 2 x (BN/32) accumulators of v_mfma_f32_16x16x32_bf16, computed as C^T blocks (weights as
-// the A operand) so that a lane holds 4 consecutive output features of one cell: epilogue
-// tiles then move through LDS in 8-byte pieces.
+// Block tile BM x BN (BN = E, the embedding width, so that one block owns whole cell rows and
+// LayerNorm can run in the epilogue; BM = 128, 64 or 32 by the number of tiles), K streamed
+// through a ring of LDS stages of 32.  The waves tile the block as accumulators of
+// v_mfma_f32_16x16x32_bf16, computed as C^T blocks (weights as the A operand) so that a lane
+// holds 4 consecutive output features of one cell: epilogue tiles then move through LDS in
+// 8-byte pieces.
 #include <math.h>
 
 #include "fast.h"

@@ -14,7 +14,7 @@ struct SetupPlan {
   // per dataset: n_train, first active column, active columns, its first place in cord, mask words
   const int32_t* blob;  // host, B * (4 + words)
   DsInfo* ds;
-  int32_t *dblob, *col_ds, *col_c, *colmap, *col_ntr, *cord;
+  int32_t *dblob, *colmap, *col_ntr, *cord;
   int64_t* col_cell0;
 };
 

@@ -39,8 +39,6 @@ __device__ __forceinline__ void expand_column(const Plan& P, int t) {
   int k = __popc(word & ((1u << (c & 31)) - 1u));
   for (int w = 0; w < (c >> 5); ++w) k += __popc((uint32_t)e[4 + w]);
   const int col = e[1] + k;
-  p.col_ds[col] = b;
-  p.col_c[col] = c;
   p.colmap[t] = col;
   p.col_cell0[col] = (int64_t)b * p.R * p.S + c;
   p.col_ntr[col] = e[0];

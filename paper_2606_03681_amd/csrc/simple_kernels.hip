@@ -1,32 +1,7 @@
-// Straightforward HIP kernels of the layer: fp32 arithmetic on VALU, any storage type.
-// They serve the float32 mode, whose 1e-4 parity needs true fp32 products, and they are the
-// baseline that the MFMA kernels of the bfloat16 mode are measured against.
-#include <math.h>
-
+// Small kernels shared by every path: uploads through kernel arguments and column sums.
 #include "kernels.h"
 
 namespace tfm {
-
-namespace {
-
-inline unsigned grid_for(int64_t n, int per_block = TFM_BLOCK) {
-  int64_t g = (n + per_block - 1) / per_block;
-  if (g < 1) g = 1;
-  return (unsigned)g;
-}
-
-__device__ __forceinline__ int64_t gtid() {
-  return (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-}
-__device__ __forceinline__ int64_t gstride() { return (int64_t)gridDim.x * blockDim.x; }
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-}  // namespace
 
 // ============================================================================ metadata
 struct UploadChunk {

@@ -139,15 +139,13 @@ struct Arena {
 
 // Offsets of the device copy of the plan inside a workspace.
 struct MetaOff {
-  size_t blob, ds, col_ds, col_c, colmap, col_cell0, col_ntr, cord;
+  size_t blob, ds, colmap, col_cell0, col_ntr, cord;
 };
 
 MetaOff take_meta(const Dims& d, Arena& a) {
   MetaOff L;
   L.blob = a.take((size_t)d.B * (4 + d.words) * 4);
   L.ds = a.take((size_t)d.B * sizeof(tfm::DsInfo));
-  L.col_ds = a.take((size_t)d.B * d.S * 4);
-  L.col_c = a.take((size_t)d.B * d.S * 4);
   L.colmap = a.take((size_t)d.B * d.S * 4);
   L.col_cell0 = a.take((size_t)d.B * d.S * 8);
   L.col_ntr = a.take((size_t)d.B * d.S * 4);
@@ -232,7 +230,7 @@ size_t saved_total(const Dims& d) {
 
 struct WsLayout {
   MetaOff meta;
-  size_t xc, ta, tb, tc, td, te, tf, th1, th2, tq, tk, tv, tqkv, D;
+  size_t ta, tb, tc, te, tf, th1, th2, tq, tk, tv, tqkv, D;
   size_t part, lnpart;  // float32 mode: weight / bias partials, norm partials
   size_t fast;          // region owned by the MFMA path
   size_t total;
@@ -243,11 +241,9 @@ WsLayout ws_layout(const Dims& d) {
   Arena a;
   const size_t N = (size_t)d.Nmax, t = d.tsz, E = d.E;
   L.meta = take_meta(d, a);
-  L.xc = a.take(N * E * t);
   L.ta = a.take(N * E * t);
   L.tb = a.take(N * E * t);
   L.tc = a.take(N * E * t);
-  L.td = a.take(N * E * t);
   L.te = a.take(N * E * t);
   L.tf = a.take(N * E * t);
   L.th1 = a.take(N * d.H * t);
@@ -376,14 +372,33 @@ int setup_geo(const Dims& d, const Plan& P, char* ws, const MetaOff& W, tfm::Geo
   p.B = d.B; p.R = d.R; p.S = d.S; p.words = d.words; p.blob = P.blob.data();
   p.dblob = (int32_t*)(ws + W.blob);
   g.ds = p.ds = (tfm::DsInfo*)(ws + W.ds);
-  g.col_ds = p.col_ds = (int32_t*)(ws + W.col_ds);
-  g.col_c = p.col_c = (int32_t*)(ws + W.col_c);
   g.colmap = p.colmap = (int32_t*)(ws + W.colmap);
   g.col_cell0 = p.col_cell0 = (int64_t*)(ws + W.col_cell0);
   g.col_ntr = p.col_ntr = (int32_t*)(ws + W.col_ntr);
   p.cord = (int32_t*)(ws + W.cord);
   STEP("setup/hbm", tfm::launch_setup(p, w, s));
   return TFM_OK;
+}
+
+// Whether `problems` (column, head) problems of R rows and at most nmax keys that fit the one-kernel
+// item-attention backward should take it.
+// The one-kernel form runs a problem per CU and pays for whole rounds of 256 and for whole
+// thirds of its 768 keys; the two kernels compute each probability twice but spread over rows and
+// keys.  Microseconds as measured over d in {16, 32}, 64 to 768 keys (R = 4/3 of them) and 84 to
+// 3,936 problems: a 32-row chunk of a round costs 1.7 / 2.1 / 2.57 (d = 16: 1.75, two problems a
+// CU / 1.95 / 2.27) for up to 256 / 512 / 768 keys; the two kernels 20 a call, 0.01 a problem and
+// 4.9e-7 (3.9e-7) a score of whole 128 x 128 tiles.  One against two, d = 32: 768 keys 83 / 75 us
+// at 126 problems, 166 / 135 at 264, 1,314 / 1,604 at 3,936; 512 keys 712 / 719 at 3,936; 384
+// keys 521 / 464; 128 keys 21 / 22 at 264.
+bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax) {
+  const int third = nmax <= 256 ? 0 : (nmax <= 512 ? 1 : 2);
+  const double c32[3] = {1.7, 2.1, 2.57}, c16[3] = {1.75, 1.95, 2.27};
+  const int64_t slots = d == 16 && third == 0 ? 512 : 256;
+  const double one = (double)((problems + slots - 1) / slots) * ((R + 31) / 32) *
+                     (d == 16 ? c16 : c32)[third];
+  const double tile = (double)((R + 127) / 128 * 128) * ((nmax + 127) / 128 * 128);
+  const double two = 20.0 + (double)problems * (0.01 + tile * (d == 16 ? 3.9e-7 : 4.9e-7));
+  return one <= 1.05 * two;
 }
 
 // Item-attention backward on the MFMA path, in the plan's column order: one-kernel columns, then
@@ -537,12 +552,8 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
        launch_f32_linear(f32_linear_dx<T>(g, dz1, E, prm + o.Wo_f, E, F32_BIAS, dof), s));
   STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
-  a = f32_linear_dx<T>(g, dqkv, 3 * E, prm + o.Wqkv_f, E, F32_DX, dX);
-  a.aux = dz1;
-  STEP("feat_qkv_dx/mfma", launch_f32_linear(a, s));
-  ZERO_INACTIVE(g, dX);
-  // every weight and bias gradient in one launch (their operands are all still there), and the
-  // sums of all partials in another
+  // every weight and bias gradient in one launch (their operands are all still there; before dX
+  // is written, which may share memory with X), and the sums of all partials in another
   const F32Split sp = f32_split(N, E, H);
   F32WgradArgs<T> wa{};
   ReduceList rl;
@@ -567,6 +578,10 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
   const size_t og[3] = {o.g1, o.g2, o.g3};
   for (int i = 0; i < 3; ++i) rl.add(lnp[i], 2 * E, lnr, 2 * E, grads + og[i]);
   STEP("wgrad/mfma", launch_f32_wgrads<T>(wa, sp, s));
+  a = f32_linear_dx<T>(g, dqkv, 3 * E, prm + o.Wqkv_f, E, F32_DX, dX);
+  a.aux = dz1;
+  STEP("feat_qkv_dx/mfma", launch_f32_linear(a, s));
+  ZERO_INACTIVE(g, dX);
   STEP("reduce/hbm", launch_reduce_list(rl, accumulate, s));
   return TFM_OK;
 }
@@ -739,8 +754,8 @@ int fwd_fast(const Dims& d, const tfm::Geo& g, const tfm::bf16* X, const float* 
 }
 
 // Weight, bias and norm gradients of one backward pass on the MFMA path: the passes note them
-// as their operands become final (every operand keeps its buffer to the end of the call), and
-// finish() forms all products in one launch and adds all partials in another.
+// as their operands become final (every operand keeps its buffer until then), products() forms
+// all products in one launch and sums() adds all partials in another.
 struct FastGrads {
   float* wpart;
   float* grads;
@@ -773,8 +788,12 @@ struct FastGrads {
   void norm(const float* part, int64_t stride, int rows, int64_t count, size_t off) {
     rl.add(part, stride, rows, count, grads + off);
   }
-  int finish(int accumulate, hipStream_t s) {
+  // Every product; called before dX is written, which may share memory with X or dY.
+  int products(hipStream_t s) {
     STEP("wgrad/mfma", tfm::launch_wgrads(wa, sp, s));
+    return TFM_OK;
+  }
+  int sums(int accumulate, hipStream_t s) {
     STEP("reduce/hbm", tfm::launch_reduce_list(rl, accumulate, s));
     return TFM_OK;
   }
@@ -882,12 +901,13 @@ int bwd_fast(const Dims& d, const tfm::Geo& g, const Plan& P, const tfm::bf16* X
     STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
   G.linear(dqkv, 3 * E, X, E, ROWS_NATIVE, o.Wqkv_f, o.bqkv_f);
+  CHK(G.products(s));
   // dX = dZ1 + dQKV_f Wqkv_f, native layout
   a = gemm_base(g, N, E, 3 * E, EPI_DX);
   a.A = dqkv; a.lda = 3 * E; a.Bt = f.wt + f.wo.qkv_f; a.resid = dz1; a.out = dX;
   STEP("feat_qkv_dx/mfma", launch_gemm(a, s));
   ZERO_INACTIVE(g, dX);
-  return G.finish(accumulate, s);
+  return G.sums(accumulate, s);
 }
 
 // ---- pre-norm RMSNorm block (bfloat16, MFMA path) --------------------------------------------
@@ -1020,6 +1040,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
     STEP("feat_attn_bwd/mfma", launch_f32_feat_bwd<T>(g, (const T*)(sv + S.qkvf), (const T*)(sv + S.of), dof,
                                         (const float*)(sv + S.lsef), dqkv, s));
   G.linear(dqkv, 3 * E, (const T*)(sv + S.r1), E, ROWS_COMPACT, o.Wqkv_f, o.bqkv_f);
+  CHK(G.products(s));
   // dX = decay (dh1 + RMS1'(dQKV_f Wqkv_f)), native
   a = gemm_base(g, N, E, 3 * E, EPI_RMS_BWD);
   a.A = dqkv; a.lda = 3 * E; a.Bt = f.wt + f.wo.qkv_f; a.resid = dh1;
@@ -1028,7 +1049,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
   STEP("feat_qkv_dx_rms1/mfma", launch_gemm(a, s));
   G.norm(f.lnpart[0], E, tiles, E, o.g1);
   ZERO_INACTIVE(g, dX);
-  return G.finish(accumulate, s);
+  return G.sums(accumulate, s);
 }
 
 // ---- forward-only calls ----------------------------------------------------------------------

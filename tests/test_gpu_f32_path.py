@@ -23,6 +23,7 @@ CASES = [
     ("f32", 1, 130, 129, 2, None, 256, 4, 1024),     # the widest block, head width 64
     ("f32", 3, 900, (1, 900), 15, (3, 15), 32, 1, 64),  # several cells per chunk and tile
     ("f32", 4, 20, (1, 20), 150, (130, 150), 32, 2, 32),  # rows of more than 128 cells
+    ("f32", 110, 3, (1, 3), 2, (0, 2), 32, 2, 32),   # a plan too long for kernel arguments
     ("bf16", 3, 70, (1, 70), 5, (0, 5), 96, 3, 96),  # bfloat16 widths without a bf16 path
     ("bf16", 2, 31, 30, 3, None, 192, 6, 96),        # H not a multiple of E
 ]
@@ -37,3 +38,28 @@ def test_f32_path_edges(monkeypatch, dtype, B, R, n, C, active, E, heads, H):
     monkeypatch.setitem(wl.TEST_CONFIGS, "edge", cfg)
     w = wl.make_workload("edge")
     compare_all(w, gpu_stack(w), oracle_stack(w))
+
+
+@pytest.mark.parametrize("name", ["d64-f32", "d64-bf16", "prenorm-small-bf16"])
+@pytest.mark.parametrize("shared", ["X", "dY"])
+def test_dX_may_share_memory_with_an_input(name, shared):
+    """The backward of one layer with dX written over X (post-norm) or dY gives the gradients of
+    the call with a buffer of its own, bit for bit."""
+    import torch
+    from paper_2606_03681_amd import tfm
+    from paper_2606_03681_amd.stack import Stack, to_device
+    w = wl.make_workload(name)
+    dims = tfm.make_dims(dtype=w.dtype, block=w.block,
+                         **{k: v for k, v in w.dims.items() if k != "dtype"})
+    got = []
+    for inplace in (False, True):
+        st = Stack(dims, w.n_train, w.cell_mask, w.params[:1])
+        X, dY = to_device(w.X, w.dtype), to_device(w.dY, w.dtype)
+        st.forward(X)
+        out = st.dxs[0] if not inplace else (X if shared == "X" else dY)
+        tfm.layer_bwd(st.layer_dims[0], st.n_train, st.cell_mask, X, st.params[0], st.saved[0],
+                      dY, out, st.grads[0], False, st.workspace)
+        torch.cuda.synchronize()
+        got.append((out.clone(), st.grads[0].clone()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
