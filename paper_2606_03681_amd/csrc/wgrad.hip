@@ -75,6 +75,20 @@ __device__ __forceinline__ uint4 cur_load(const Cursor& c, const bf16* p0, const
   return ldu4(base + (v ? c.addr : 0));
 }
 
+// The cursor `rows` cells further on in the compact layout.
+__device__ __forceinline__ Cursor cur_ahead(Cursor c, int rows, int64_t ld) {
+  c.rem -= rows;
+  c.addr += rows * ld;
+  return c;
+}
+
+// What a cursor of the same features, some rows away, need not keep in registers of its own.
+__device__ __forceinline__ void cur_share(Cursor& c, const Cursor& c0, int rem) {
+  c.rem = rem;
+  c.part = c0.part;
+  c.hmo = c0.hmo;
+}
+
 // cell0 / ntr: the column metadata (entry col - lo for column col); the workgroup's own copy
 // in LDS where it has one, so that crossing into the next column costs no global load (whose
 // wait would also wait for every data load in flight).
@@ -161,6 +175,10 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob& a, const Geo& g, int6
   const bool opa = __builtin_amdgcn_readfirstlane(w) < 4;
   const int st = tid & 255;
   constexpr int CPM = CPA > CPB ? CPA : CPB;
+  // where whole slice rows lie between a thread's chunks, one cursor serves them all in the
+  // compact layout (RS rows apart, the same features)
+  constexpr bool ONE = 2048 % BN == 0 && 2048 % BK == 0;
+  constexpr int RS = 2048 / BN;
   Cursor cu[CPM];  // one array for both roles (a select between two arrays would not stay in
                    // registers)
 #pragma unroll
@@ -179,11 +197,18 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob& a, const Geo& g, int6
                             "two role branches with non-constant indices (scratch arrays)");
   auto gload = [&](uint4* r, uint32_t& okm) __attribute__((always_inline)) {
     okm = 0u;
+    const int rem0 = cu[0].rem;
     if (opa) {
 #pragma unroll
       for (int i = 0; i < CPA; ++i) {
         const int ch = st + 256 * i;
         bool ok;
+        if (ONE && YM == ROWS_COMPACT) {
+          r[i] = cur_load<YM>(cur_ahead(cu[0], RS * i, a.N), a.dY, a.dY2, a.dY3, &ok);
+          okm |= ok ? 1u << i : 0u;
+          continue;
+        }
+        if (ONE) cur_share(cu[i], cu[0], rem0 - RS * i);
         r[i] = cur_load<YM>(cu[i], a.dY, a.dY2, a.dY3, &ok);
         okm |= ok ? 1u << i : 0u;
         cur_advance<YM>(cu[i], g, a.N, n0 + (ch % (BN / 8)) * 8, cell0, ntrp, lo);
@@ -193,11 +218,19 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob& a, const Geo& g, int6
       for (int i = 0; i < CPB; ++i) {
         const int ch = st + 256 * i;
         bool ok;
+        if (ONE && XM == ROWS_COMPACT) {
+          r[i] = cur_load<XM>(cur_ahead(cu[0], RS * i, a.K), a.X, nullptr, nullptr, &ok);
+          okm |= ok ? 1u << i : 0u;
+          continue;
+        }
+        if (ONE) cur_share(cu[i], cu[0], rem0 - RS * i);
         r[i] = cur_load<XM>(cu[i], a.X, nullptr, nullptr, &ok);
         okm |= ok ? 1u << i : 0u;
         cur_advance<XM>(cu[i], g, a.K, k0 + (ch % (BK / 8)) * 8, cell0, ntrp, lo);
       }
     }
+    if (ONE && YM == ROWS_COMPACT && opa) cur_advance<YM>(cu[0], g, a.N, 0, cell0, ntrp, lo);
+    if (ONE && XM == ROWS_COMPACT && !opa) cur_advance<XM>(cu[0], g, a.K, 0, cell0, ntrp, lo);
   };
   const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
   auto sstore = [&](const uint4* r, uint32_t okm, int b) __attribute__((always_inline)) {
@@ -384,29 +417,32 @@ __global__ __launch_bounds__(256) void k_reduce_z(int Z, int zc, int64_t count, 
   }
 }
 
-// Square tiles (the two staging roles then move equal chunk counts); E = 256 takes 128 x 128
-// tiles, whose accumulators fit the registers of a 512-thread workgroup.
-static int wgrad_bn(int E) { return E > 192 ? 128 : E; }
+// Square tiles as wide as E (the two staging roles then move equal chunk counts).  At E = 256 a
+// 256 x 256 tile reads half of what 128 x 128 tiles read through L2 (14 against 29 KB a cell, what
+// bounded them: 10 TB/s), but its partials need more cells to pay: forward + backward at H = 768
+// 6,162 against 5,992 us at 344,000 cells, 1,379 / 1,341 at 80,000, 568 / 562 at 21,500, and 247
+// / 252 at 12,000.
+constexpr int64_t WGRAD_WIDE_MIN = 20000;
+static int wgrad_bn(int E, int64_t M) { return E > 192 && M < WGRAD_WIDE_MIN ? 128 : E; }
 
-// Workgroups the chip's 256 CUs hold at once: the 192-wide tile's 176 registers leave room for
-// one workgroup of 8 waves on a CU.  With twice that many chunks a 1,000 x 21 table took 488
-// instead of 471 us (forward + backward; more partials to write and add), 16 x 1024 x 101 16.31
-// instead of 16.25 ms.
-static int wgrad_slots(int E) { return wgrad_bn(E) == 192 ? 256 : 512; }
+// Workgroups the chip's 256 CUs hold at once: the 176 and 252 registers of the 192- and 256-wide
+// tiles leave room for one workgroup of 8 waves on a CU.  With twice that many chunks a 1,000 x 21
+// table took 488 instead of 471 us (forward + backward; more partials to write and add), 16 x 1024
+// x 101 16.31 instead of 16.25 ms; 80,000 cells at E = 256 1,367 instead of 1,341 us.
+static int wgrad_slots(int BN) { return BN >= 192 ? 256 : 512; }
 
-static int wgrad_tiles(int E, int H) {
-  const int64_t bn = wgrad_bn(E);
-  return (int)((8LL * E * E + 2LL * E * H) / (bn * bn));
+static int wgrad_tiles(int BN, int E, int H) {
+  return (int)((8LL * E * E + 2LL * E * H) / ((int64_t)BN * BN));
 }
 
-// Chunks asked for at M cells; never falls as M grows.
+// Chunks asked for at M cells; never falls as M grows at one tile width.
 static int64_t wgrad_want(int64_t M, int E, int H) {
-  const int T = wgrad_tiles(E, H);
+  const int BN = wgrad_bn(E, M), T = wgrad_tiles(BN, E, H);
   // whole rounds of the workgroups the chip holds at once, as few as keep a chunk within
   // WGRAD_CHUNK_MAX; whole multiples of 8 chunks spread evenly over the XCDs
   int64_t Z = 8;
   for (int64_t k = 1;; ++k) {
-    Z = wgrad_slots(E) * k / T / 8 * 8;
+    Z = wgrad_slots(BN) * k / T / 8 * 8;
     if (Z >= 8 && (M + Z - 1) / Z <= WGRAD_CHUNK_MAX) break;
   }
   // below WGRAD_CHUNK_MIN cells a chunk's partial tile costs more than its operands
@@ -425,12 +461,17 @@ WgradSplit wgrad_split(int64_t M, int E, int H) {
 }
 
 size_t wgrad_part_floats(int64_t Mmax, int E, int H) {
-  return (size_t)wgrad_want(Mmax, E, H) *
+  int64_t Z = wgrad_want(Mmax, E, H);
+  if (Mmax >= WGRAD_WIDE_MIN) {
+    const int64_t narrow = wgrad_want(WGRAD_WIDE_MIN - 1, E, H);
+    Z = Z > narrow ? Z : narrow;
+  }
+  return (size_t)Z *
          (8 * (size_t)E * E + 2 * (size_t)E * H + 9 * (size_t)E + H);
 }
 
 hipError_t launch_wgrads(WgradArgs& a, const WgradSplit& sp, hipStream_t s) {
-  const int BN = wgrad_bn(a.g.E);
+  const int BN = wgrad_bn(a.g.E, a.g.N);
   a.M = a.g.N;
   a.chunk = sp.chunk;
   a.tiles = 0;
@@ -455,6 +496,10 @@ hipError_t launch_wgrads(WgradArgs& a, const WgradSplit& sp, hipStream_t s) {
     case 192:
       if (tbl) k_wgrads<192, true><<<grid, 512, 0, s>>>(a);
       else k_wgrads<192, false><<<grid, 512, 0, s>>>(a);
+      break;
+    case 256:
+      if (tbl) k_wgrads<256, true><<<grid, 512, 0, s>>>(a);
+      else k_wgrads<256, false><<<grid, 512, 0, s>>>(a);
       break;
     default: return hipErrorInvalidValue;
   }

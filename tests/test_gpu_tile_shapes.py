@@ -1,13 +1,15 @@
 """The forward-only calls give the training forward's rows bit for bit although their GEMM launches
 take other tile shapes: a training forward of 97,200 cells runs 128-row tiles, its context call the
-same, and query chunks of 81 to 3,240 cells run 32- and 64-row tiles."""
+same, and query chunks of 81 to 3,240 cells run 32- and 64-row tiles.  The weight gradients at
+E = 256 agree with the float64 oracle on both sides of the cell count from which their tiles are
+256 wide, within the parity tests' bfloat16 tolerance (2e-2 of each tensor's largest value)."""
 
 import numpy as np
 import pytest
 
 from paper_2606_03681_amd import workloads as wl
 
-from _harness import storage_of
+from _harness import compare_all, gpu_stack, oracle_stack, storage_of
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,20 @@ def test_rows_do_not_depend_on_tile_shape(monkeypatch, block, E, heads, H):
                               "bf16"))
     torch.cuda.synchronize()
     assert np.array_equal(np.concatenate(got, axis=1), full)
+
+
+# block, B, R, n_train, C, active, H: 20,000 cells (one column spans less than a slice of the
+# contraction), 19,980 and ragged tables of more than 21,000
+WIDE = [("post", 100, 20, (1, 20), 9, None, 256), ("post", 2, 999, 700, 9, None, 512),
+        ("pre", 2, 703, (1, 703), 21, (16, 21), 768)]
+
+
+@pytest.mark.parametrize("block,B,R,n,C,active,H", WIDE)
+def test_weight_gradients_at_width_256(monkeypatch, block, B, R, n, C, active, H):
+    cfg = dict(name="wide", dtype="bf16", B=B, R=R, n_train=n, C=C, E=256, heads=8, H=H, layers=1,
+               cells="normal", weights="xavier_bias", block=block)
+    if active:
+        cfg.update(active=active, mask="random")
+    monkeypatch.setitem(wl.TEST_CONFIGS, "wide", cfg)
+    w = wl.make_workload("wide")
+    compare_all(w, gpu_stack(w), oracle_stack(w))
