@@ -42,6 +42,40 @@ struct ColList {
   int32_t count;
 };
 
+// Threads of one launch: a grid of 2^32 or more is started modulo 2^32, without an error.  Kernels
+// with a wave or a workgroup for each row or (column, head) problem reach that inside the supported
+// envelope (many tables of a few rows or cells) and go in pieces, launches over some of the columns
+// or datasets.
+constexpr int64_t MAX_THREADS = (int64_t(1) << 32) - 1;
+
+// fn(columns, c0) for successive pieces of the active columns: a Geo whose columns start at column
+// c0 of g, of which per-column arrays (not cells of native tensors) are addressed from c0 on.
+// threads: of one (column, head) problem; launches round their number up to a multiple of 8.
+template <class F>
+void by_columns(const Geo& g, int64_t threads, F fn) {
+  const int64_t per = (MAX_THREADS / threads - 8) / g.heads;  // >= 1: R * E <= 715,827,882
+  for (int64_t c0 = 0; c0 < g.NC; c0 += per) {
+    Geo p = g;
+    p.NC = (int32_t)(g.NC - c0 < per ? g.NC - c0 : per);
+    p.N = (int64_t)p.NC * g.R;
+    p.col_cell0 = g.col_cell0 + c0;
+    p.col_ntr = g.col_ntr + c0;
+    fn(p, c0);
+  }
+}
+// fn(datasets) for successive pieces of the datasets: a Geo with some of them, whose columns and
+// cells keep their numbers in g.  threads: of one row.
+template <class F>
+void by_datasets(const Geo& g, int64_t threads, F fn) {
+  const int64_t per = (MAX_THREADS - 1024) / (threads * g.R);  // >= 1 as above
+  for (int64_t b0 = 0; b0 < g.B; b0 += per) {
+    Geo p = g;
+    p.B = (int32_t)(g.B - b0 < per ? g.B - b0 : per);
+    p.ds = g.ds + b0;
+    fn(p);
+  }
+}
+
 __host__ __device__ inline int64_t native_cell(const Geo& g, int64_t p) {
   int64_t col = p / g.R;
   int64_t r = p - col * g.R;

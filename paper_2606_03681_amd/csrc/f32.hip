@@ -171,9 +171,11 @@ __global__ __launch_bounds__(256) void k_f32_wgrads(F32WgradArgs<T> a) {
 }
 
 // ---- LayerNorm --------------------------------------------------------------------------------
-// One wave per cell, lane l holding features 4l .. 4l+3 (E <= 256) in 16-byte pieces.
+// One wave per cell from cell p0 up, lane l holding features 4l .. 4l+3 (E <= 256) in 16-byte
+// pieces.
 template <class T>
-__global__ __launch_bounds__(256) void k_f32_add_ln(Geo g, const T* __restrict__ a, int amode,
+__global__ __launch_bounds__(256) void k_f32_add_ln(Geo g, int64_t p0, const T* __restrict__ a,
+                                                    int amode,
                                                     const T* __restrict__ b,
                                                     const float* __restrict__ gamma,
                                                     const float* __restrict__ beta,
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(256) void k_f32_add_ln(Geo g, const T* __restrict__
                                                     T* __restrict__ xhat,
                                                     float* __restrict__ rstd) {
   const int lane = threadIdx.x & 63, E = g.E;
-  const int64_t p = (int64_t)blockIdx.x * 4 + wave_id();
+  const int64_t p = p0 + (int64_t)blockIdx.x * 4 + wave_id();
   if (p >= g.N) return;
   const bool act = 4 * lane < E;
   const int64_t nat = amode == ROWS_NATIVE || hmode == ROWS_NATIVE ? native32(g, p) : 0;
@@ -497,9 +499,11 @@ template <class T>
 hipError_t launch_f32_add_ln(const Geo& g, const T* a, int amode, const T* b, const float* gamma,
                              const float* beta, T* h, int hmode, T* xhat, float* rstd,
                              hipStream_t s) {
-  if (g.N <= 0) return hipSuccess;
-  k_f32_add_ln<T><<<(unsigned)((g.N + 3) / 4), 256, 0, s>>>(g, a, amode, b, gamma, beta, h, hmode,
-                                                            xhat, rstd);
+  constexpr int64_t per = MAX_THREADS / 256;  // workgroups of one launch
+  const int64_t nb = (g.N + 3) / 4;
+  for (int64_t b0 = 0; b0 < nb; b0 += per)
+    k_f32_add_ln<T><<<(unsigned)std::min(nb - b0, per), 256, 0, s>>>(
+        g, 4 * b0, a, amode, b, gamma, beta, h, hmode, xhat, rstd);
   return hipGetLastError();
 }
 

@@ -538,10 +538,12 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
   }
 }
 
+int64_t item_threads(int rows) { return (int64_t)((rows + 63) / 64) * 256; }  // of a problem
 unsigned item_grid(const Geo& g, int rows) {
   const int64_t np = ((int64_t)g.NC * g.heads + 7) / 8 * 8;
   return (unsigned)(np * ((rows + 63) / 64));
 }
+int64_t feat_threads(const Geo& g) { return (int64_t)g.heads * ((g.S + 15) / 16) * 64; }  // a row's
 unsigned feat_grid(const Geo& g) {
   return (unsigned)(((int64_t)g.B * g.R * g.heads * ((g.S + 15) / 16) + 3) / 4);
 }
@@ -560,7 +562,12 @@ unsigned feat_grid(const Geo& g) {
 template <class T>
 hipError_t launch_f32_item_fwd(const Geo& g, const T* q, const T* k, const T* v, T* o, float* lse,
                                hipStream_t s) {
-#define CALL(D) k_f32_item_fwd<T, D><<<item_grid(g, g.R), 256, 0, s>>>(g, q, k, v, o, lse)
+#define CALL(D)                                                                              \
+  by_columns(g, item_threads(g.R), [&](const Geo& p, int64_t c0) {                           \
+    const int64_t h = c0 * g.heads * g.R;                                                    \
+    k_f32_item_fwd<T, D><<<item_grid(p, g.R), 256, 0, s>>>(                                  \
+        p, q + h * D, k + h * D, v + h * D, o + c0 * g.R * g.E, lse + h);                    \
+  })
   BY_D(CALL);
 #undef CALL
 }
@@ -569,16 +576,26 @@ template <class T>
 hipError_t launch_f32_item_bwd(const Geo& g, const T* q, const T* k, const T* v, const T* o,
                                const T* dout, const float* lse, float* Dbuf, T* dq, T* dk, T* dv,
                                hipStream_t s) {
-#define CALL(D)                                                                                  \
-  k_f32_item_dq<T, D><<<item_grid(g, g.R), 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dq);     \
-  k_f32_item_dkv<T, D><<<item_grid(g, g.nmax), 256, 0, s>>>(g, q, k, v, dout, lse, Dbuf, dk, dv)
+#define CALL(D)                                                                              \
+  by_columns(g, item_threads(g.R), [&](const Geo& p, int64_t c0) {                           \
+    const int64_t h = c0 * g.heads * g.R, x = c0 * g.R * g.E;                                \
+    k_f32_item_dq<T, D><<<item_grid(p, g.R), 256, 0, s>>>(p, q + h * D, k + h * D,           \
+                                                          v + h * D, o + x, dout + x,        \
+                                                          lse + h, Dbuf + h, dq + h * D);    \
+    k_f32_item_dkv<T, D><<<item_grid(p, g.nmax), 256, 0, s>>>(                               \
+        p, q + h * D, k + h * D, v + h * D, dout + x, lse + h, Dbuf + h, dk + h * D,         \
+        dv + h * D);                                                                         \
+  })
   BY_D(CALL);
 #undef CALL
 }
 
 template <class T>
 hipError_t launch_f32_feat_fwd(const Geo& g, const T* qkv, T* o, float* lse, hipStream_t s) {
-#define CALL(D) k_f32_feat_fwd<T, D><<<feat_grid(g), 256, 0, s>>>(g, qkv, o, lse)
+#define CALL(D)                                                              \
+  by_datasets(g, feat_threads(g), [&](const Geo& p) {                        \
+    k_f32_feat_fwd<T, D><<<feat_grid(p), 256, 0, s>>>(p, qkv, o, lse);       \
+  })
   BY_D(CALL);
 #undef CALL
 }
@@ -586,7 +603,10 @@ hipError_t launch_f32_feat_fwd(const Geo& g, const T* qkv, T* o, float* lse, hip
 template <class T>
 hipError_t launch_f32_feat_bwd(const Geo& g, const T* qkv, const T* o, const T* dout,
                                const float* lse, T* dqkv, hipStream_t s) {
-#define CALL(D) k_f32_feat_bwd<T, D><<<feat_grid(g), 256, 0, s>>>(g, qkv, o, dout, lse, dqkv)
+#define CALL(D)                                                                          \
+  by_datasets(g, feat_threads(g), [&](const Geo& p) {                                    \
+    k_f32_feat_bwd<T, D><<<feat_grid(p), 256, 0, s>>>(p, qkv, o, dout, lse, dqkv);       \
+  })
   BY_D(CALL);
 #undef CALL
 }
