@@ -379,51 +379,45 @@ bool feat_attn_mfma_ok(const Geo& g) {
 }
 
 template <int D>
-static hipError_t feat_fwd_d(const Geo& g, unsigned grid, const bf16* qkv, bf16* o, float* lse,
+static hipError_t feat_fwd_d(const Geo& g, const bf16* qkv, bf16* o, float* lse,
                              hipStream_t s) {
-  if (g.S <= 32)
-    k_feat_attn_fwd<D, 32><<<grid, 256, 0, s>>>(g, qkv, o, lse);
-  else if (g.S <= 64)
-    k_feat_attn_fwd<D, 64><<<grid, 256, 0, s>>>(g, qkv, o, lse);
-  else if (D < 64)
-    k_feat_attn_fwd<D, (D < 64 ? 128 : 64)><<<grid, 256, 0, s>>>(g, qkv, o, lse);
-  else
-    return hipErrorInvalidValue;
+  if (D == 64 && g.S > 64) return hipErrorInvalidValue;
+  by_datasets(g, (int64_t)g.heads * 64, [&](const Geo& p) {
+    const unsigned grid = (unsigned)(((int64_t)p.B * p.R * p.heads + 3) / 4);
+    if (g.S <= 32) k_feat_attn_fwd<D, 32><<<grid, 256, 0, s>>>(p, qkv, o, lse);
+    else if (g.S <= 64) k_feat_attn_fwd<D, 64><<<grid, 256, 0, s>>>(p, qkv, o, lse);
+    else k_feat_attn_fwd<D, (D < 64 ? 128 : 64)><<<grid, 256, 0, s>>>(p, qkv, o, lse);
+  });
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t feat_bwd_d(const Geo& g, unsigned grid, const bf16* qkv, const bf16* o,
+static hipError_t feat_bwd_d(const Geo& g, const bf16* qkv, const bf16* o,
                              const bf16* dout, const float* lse, bf16* dqkv, hipStream_t s) {
-  if (g.S <= 32)
-    k_feat_attn_bwd<D, 32><<<grid, 256, 0, s>>>(g, qkv, o, dout, lse, dqkv);
-  else if (g.S <= 64)
-    k_feat_attn_bwd<D, 64><<<grid, 256, 0, s>>>(g, qkv, o, dout, lse, dqkv);
-  else if (D < 64)
-    k_feat_attn_bwd<D, (D < 64 ? 128 : 64)><<<grid, 256, 0, s>>>(g, qkv, o, dout, lse, dqkv);
-  else
-    return hipErrorInvalidValue;
+  if (D == 64 && g.S > 64) return hipErrorInvalidValue;
+  by_datasets(g, (int64_t)g.heads * 64, [&](const Geo& p) {
+    const unsigned grid = (unsigned)(((int64_t)p.B * p.R * p.heads + 3) / 4);
+    if (g.S <= 32) k_feat_attn_bwd<D, 32><<<grid, 256, 0, s>>>(p, qkv, o, dout, lse, dqkv);
+    else if (g.S <= 64) k_feat_attn_bwd<D, 64><<<grid, 256, 0, s>>>(p, qkv, o, dout, lse, dqkv);
+    else k_feat_attn_bwd<D, (D < 64 ? 128 : 64)><<<grid, 256, 0, s>>>(p, qkv, o, dout, lse, dqkv);
+  });
   return hipGetLastError();
 }
 
 hipError_t launch_feat_attn_fwd(const Geo& g, const bf16* qkv, bf16* o, float* lse,
                                 hipStream_t s) {
   if (!feat_attn_mfma_ok(g)) return hipErrorInvalidValue;
-  const int64_t pairs = (int64_t)g.B * g.R * g.heads;
-  const unsigned grid = (unsigned)((pairs + 3) / 4);
-  if (g.d == 16) return feat_fwd_d<16>(g, grid, qkv, o, lse, s);
-  if (g.d == 32) return feat_fwd_d<32>(g, grid, qkv, o, lse, s);
-  return feat_fwd_d<64>(g, grid, qkv, o, lse, s);
+  if (g.d == 16) return feat_fwd_d<16>(g, qkv, o, lse, s);
+  if (g.d == 32) return feat_fwd_d<32>(g, qkv, o, lse, s);
+  return feat_fwd_d<64>(g, qkv, o, lse, s);
 }
 
 hipError_t launch_feat_attn_bwd(const Geo& g, const bf16* qkv, const bf16* o, const bf16* dout,
                                 const float* lse, bf16* dqkv, hipStream_t s) {
   if (!feat_attn_mfma_ok(g)) return hipErrorInvalidValue;
-  const int64_t pairs = (int64_t)g.B * g.R * g.heads;
-  const unsigned grid = (unsigned)((pairs + 3) / 4);
-  if (g.d == 16) return feat_bwd_d<16>(g, grid, qkv, o, dout, lse, dqkv, s);
-  if (g.d == 32) return feat_bwd_d<32>(g, grid, qkv, o, dout, lse, dqkv, s);
-  return feat_bwd_d<64>(g, grid, qkv, o, dout, lse, dqkv, s);
+  if (g.d == 16) return feat_bwd_d<16>(g, qkv, o, dout, lse, dqkv, s);
+  if (g.d == 32) return feat_bwd_d<32>(g, qkv, o, dout, lse, dqkv, s);
+  return feat_bwd_d<64>(g, qkv, o, dout, lse, dqkv, s);
 }
 
 }  // namespace tfm

@@ -260,24 +260,27 @@ __global__ __launch_bounds__(256, 3) void k_item_attn_fwd(Geo g, const bf16* __r
   }
 }
 
+template <int D>
+static hipError_t item_fwd_d(const Geo& g, const bf16* q, const bf16* k, const bf16* v, bf16* o,
+                             float* lse, int kR, hipStream_t s) {
+  const int QT = (g.R + qgroup<D>() - 1) / qgroup<D>();
+  by_columns(g, (int64_t)QT * 256, [&](const Geo& p, int64_t c0) {
+    const int64_t P = (int64_t)p.NC * g.heads, h = c0 * g.heads * g.R, hk = c0 * g.heads * kR;
+    k_item_attn_fwd<D><<<(unsigned)((P + 7) / 8 * 8 * QT), 256, 0, s>>>(
+        p, q + h * D, k + hk * D, v + hk * D, o + c0 * g.R * g.E, lse + h, QT, kR);
+  });
+  return hipGetLastError();
+}
+
 hipError_t launch_item_attn_fwd(const Geo& g, const bf16* q, const bf16* k, const bf16* v,
                                 bf16* o, float* lse, hipStream_t s, int kR) {
   if (kR <= 0) kR = g.R;
-  const int64_t P = (int64_t)g.NC * g.heads;
-  auto grid = [&](int QT) { return (unsigned)((P + 7) / 8 * 8 * QT); };
-  if (g.d == 16) {
-    const int QT = (g.R + qgroup<16>() - 1) / qgroup<16>();
-    k_item_attn_fwd<16><<<grid(QT), 256, 0, s>>>(g, q, k, v, o, lse, QT, kR);
-  } else if (g.d == 32) {
-    const int QT = (g.R + qgroup<32>() - 1) / qgroup<32>();
-    k_item_attn_fwd<32><<<grid(QT), 256, 0, s>>>(g, q, k, v, o, lse, QT, kR);
-  } else if (g.d == 64) {
-    const int QT = (g.R + qgroup<64>() - 1) / qgroup<64>();
-    k_item_attn_fwd<64><<<grid(QT), 256, 0, s>>>(g, q, k, v, o, lse, QT, kR);
-  } else {
-    return hipErrorInvalidValue;
+  switch (g.d) {
+    case 16: return item_fwd_d<16>(g, q, k, v, o, lse, kR, s);
+    case 32: return item_fwd_d<32>(g, q, k, v, o, lse, kR, s);
+    case 64: return item_fwd_d<64>(g, q, k, v, o, lse, kR, s);
+    default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace tfm

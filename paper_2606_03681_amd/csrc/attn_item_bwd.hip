@@ -675,26 +675,34 @@ bool item_attn_bwd_fused_ok(const Geo& g, int nmax) { return fused_nkb(g.d, nmax
 
 int item_attn_bwd_fused_max_rows(int d) { return fused_nkb(d, 1) > 0 ? 768 : 0; }
 
+// fn(geo, list, c0) for pieces of the columns of cl (by_columns): without a list the piece's columns
+// start at column c0, from which per-column arrays are addressed.
+template <class F>
+static void by_list(const Geo& g, const ColList& cl, int64_t threads, F fn) {
+  Geo w = g;
+  w.NC = cl.count;
+  by_columns(w, threads, [&](const Geo& p, int64_t c0) {
+    if (cl.cols) fn(g, ColList{cl.cols + c0, p.NC}, 0);
+    else fn(p, ColList{nullptr, p.NC}, c0);
+  });
+}
+
 template <int D>
-static hipError_t fused_d(const Geo& g, const ColList& cl, int nkb, unsigned grid, int per,
-                          const bf16* q, const bf16* k, const bf16* v, const bf16* o,
-                          const bf16* dout, const float* lse, bf16* dq, bf16* dk, bf16* dv,
-                          hipStream_t s) {
-  switch (nkb) {
-    case 2:
-      k_item_attn_bwd_fused<D, 2><<<grid, 512, 0, s>>>(g, q, k, v, o, dout, lse, dq, dk, dv,
-                                                         per, cl);
-      break;
-    case 4:
-      k_item_attn_bwd_fused<D, 4><<<grid, 512, 0, s>>>(g, q, k, v, o, dout, lse, dq, dk, dv,
-                                                         per, cl);
-      break;
-    case 6:
-      k_item_attn_bwd_fused<D, 6><<<grid, 512, 0, s>>>(g, q, k, v, o, dout, lse, dq, dk, dv,
-                                                         per, cl);
-      break;
-    default: return hipErrorInvalidValue;
-  }
+static hipError_t fused_d(const Geo& g, const ColList& list, int nkb, const bf16* q, const bf16* k,
+                          const bf16* v, const bf16* o, const bf16* dout, const float* lse,
+                          bf16* dq, bf16* dk, bf16* dv, hipStream_t s) {
+  by_list(g, list, 512, [&](const Geo& p, const ColList& cl, int64_t c0) {
+    const int per = (int)(((int64_t)cl.count * g.heads + 7) / 8);
+    const unsigned grid = (unsigned)(8 * per);
+    const int64_t h = c0 * g.heads * g.R, hd = h * D, x = c0 * g.R * g.E;
+#define RUN(NKB)                                                                                \
+  k_item_attn_bwd_fused<D, NKB><<<grid, 512, 0, s>>>(p, q + hd, k + hd, v + hd, o + x, dout + x, \
+                                                     lse + h, dq + hd, dk + hd, dv + hd, per, cl)
+    if (nkb == 2) RUN(2);
+    else if (nkb == 4) RUN(4);
+    else RUN(6);
+#undef RUN
+  });
   return hipGetLastError();
 }
 
@@ -704,29 +712,46 @@ hipError_t launch_item_attn_bwd_fused(const Geo& g, const ColList& cl, int nmax,
                                       bf16* dv, hipStream_t s) {
   const int nkb = fused_nkb(g.d, nmax);
   if (nkb == 0) return hipErrorInvalidValue;
-  const int64_t P = (int64_t)cl.count * g.heads;
-  if (P == 0) return hipSuccess;
-  const int per = (int)((P + 7) / 8);
-  const unsigned grid = (unsigned)(8 * per);
-  if (g.d == 16) return fused_d<16>(g, cl, nkb, grid, per, q, k, v, o, dout, lse, dq, dk, dv, s);
-  return fused_d<32>(g, cl, nkb, grid, per, q, k, v, o, dout, lse, dq, dk, dv, s);
+  if (g.d == 16) return fused_d<16>(g, cl, nkb, q, k, v, o, dout, lse, dq, dk, dv, s);
+  return fused_d<32>(g, cl, nkb, q, k, v, o, dout, lse, dq, dk, dv, s);
+}
+
+template <int D>
+static hipError_t dq_d(const Geo& g, const ColList& list, const bf16* q, const bf16* k,
+                       const bf16* v, const bf16* o, const bf16* dout, const float* lse,
+                       float* Dbuf, bf16* dq, hipStream_t s) {
+  const int QT = (g.R + 127) / 128;
+  by_list(g, list, (int64_t)QT * 256, [&](const Geo& p, const ColList& cl, int64_t c0) {
+    const unsigned grid = (unsigned)(((int64_t)cl.count * g.heads + 7) / 8 * 8 * QT);
+    const int64_t h = c0 * g.heads * g.R, hd = h * D, x = c0 * g.R * g.E;
+    k_item_attn_dq<D><<<grid, 256, 0, s>>>(p, q + hd, k + hd, v + hd, o + x, dout + x, lse + h,
+                                           Dbuf + h, dq + hd, QT, cl);
+  });
+  return hipGetLastError();
 }
 
 hipError_t launch_item_attn_dq(const Geo& g, const ColList& cl, const bf16* q, const bf16* k,
                                const bf16* v, const bf16* o, const bf16* dout, const float* lse,
                                float* Dbuf, bf16* dq, hipStream_t s) {
-  const int64_t P = (int64_t)cl.count * g.heads;
-  if (P == 0) return hipSuccess;
-  const int QT = (g.R + 127) / 128;
-  const unsigned grid = (unsigned)((P + 7) / 8 * 8 * QT);
-  if (g.d == 16)
-    k_item_attn_dq<16><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dq, QT, cl);
-  else if (g.d == 32)
-    k_item_attn_dq<32><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dq, QT, cl);
-  else if (g.d == 64)
-    k_item_attn_dq<64><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dq, QT, cl);
-  else
-    return hipErrorInvalidValue;
+  switch (g.d) {
+    case 16: return dq_d<16>(g, cl, q, k, v, o, dout, lse, Dbuf, dq, s);
+    case 32: return dq_d<32>(g, cl, q, k, v, o, dout, lse, Dbuf, dq, s);
+    case 64: return dq_d<64>(g, cl, q, k, v, o, dout, lse, Dbuf, dq, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int D>
+static hipError_t dkdv_d(const Geo& g, const ColList& list, const bf16* q, const bf16* k,
+                         const bf16* v, const bf16* o, const bf16* dout, const float* lse,
+                         const float* Dbuf, bf16* dk, bf16* dv, hipStream_t s) {
+  const int KT = (g.R + 127) / 128;
+  by_list(g, list, (int64_t)KT * 256, [&](const Geo& p, const ColList& cl, int64_t c0) {
+    const unsigned grid = (unsigned)(((int64_t)cl.count * g.heads + 7) / 8 * 8 * KT);
+    const int64_t h = c0 * g.heads * g.R, hd = h * D, x = c0 * g.R * g.E;
+    k_item_attn_dkdv<D><<<grid, 256, 0, s>>>(p, q + hd, k + hd, v + hd, o + x, dout + x, lse + h,
+                                             Dbuf + h, dk + hd, dv + hd, KT, cl);
+  });
   return hipGetLastError();
 }
 
@@ -734,19 +759,12 @@ hipError_t launch_item_attn_dkdv(const Geo& g, const ColList& cl, const bf16* q,
                                  const bf16* v, const bf16* o, const bf16* dout,
                                  const float* lse, const float* Dbuf, bf16* dk, bf16* dv,
                                  hipStream_t s) {
-  const int64_t P = (int64_t)cl.count * g.heads;
-  if (P == 0) return hipSuccess;
-  const int KT = (g.R + 127) / 128;
-  const unsigned grid = (unsigned)((P + 7) / 8 * 8 * KT);
-  if (g.d == 16)
-    k_item_attn_dkdv<16><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dk, dv, KT, cl);
-  else if (g.d == 32)
-    k_item_attn_dkdv<32><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dk, dv, KT, cl);
-  else if (g.d == 64)
-    k_item_attn_dkdv<64><<<grid, 256, 0, s>>>(g, q, k, v, o, dout, lse, Dbuf, dk, dv, KT, cl);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  switch (g.d) {
+    case 16: return dkdv_d<16>(g, cl, q, k, v, o, dout, lse, Dbuf, dk, dv, s);
+    case 32: return dkdv_d<32>(g, cl, q, k, v, o, dout, lse, Dbuf, dk, dv, s);
+    case 64: return dkdv_d<64>(g, cl, q, k, v, o, dout, lse, Dbuf, dk, dv, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace tfm

@@ -229,10 +229,11 @@ hipError_t launch_rms_in(const Geo& g, const bf16* X, float decay, const float* 
 }
 
 // Thinking rows: rows [0, T) of X get the table (float32 [T][E]) at active cell columns and 0 at
-// inactive ones; one thread per element of those rows.
+// inactive ones; elements [i0, i0 + threads) of those rows, one a thread.
 template <class TT>
-__global__ void k_thinking_fwd(Geo g, int T, const float* __restrict__ table, TT* __restrict__ X) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_thinking_fwd(Geo g, int T, const float* __restrict__ table, TT* __restrict__ X,
+                               int64_t i0) {
+  const int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t per = (int64_t)T * g.S * g.E;
   if (i >= per * g.B) return;
   const int b = (int)(i / per);
@@ -261,8 +262,10 @@ __global__ void k_thinking_bwd(Geo g, int T, const TT* __restrict__ dX, float* _
 template <class TT>
 hipError_t launch_thinking_fwd(const Geo& g, int T, const float* table, TT* X, hipStream_t s) {
   const int64_t n = (int64_t)g.B * T * g.S * g.E;
-  if (n == 0) return hipSuccess;
-  k_thinking_fwd<TT><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(g, T, table, X);
+  constexpr int64_t per = MAX_THREADS / 256 * 256;
+  for (int64_t i = 0; i < n; i += per)
+    k_thinking_fwd<TT><<<(unsigned)(((n - i < per ? n - i : per) + 255) / 256), 256, 0, s>>>(
+        g, T, table, X, i);
   return hipGetLastError();
 }
 

@@ -63,46 +63,3 @@ def test_dX_may_share_memory_with_an_input(name, shared):
         got.append((out.clone(), st.grads[0].clone()))
     for a, b in zip(*got):
         assert torch.equal(a, b)
-
-
-# what is over the size of one launch, dtype, B, R, n_train, C, E, heads, and the datasets to run
-# again alone
-MANY = [("item", "f32", 8193, 2, (1, 2), 255, 128, 8, (0, 4100, 8192)),
-        ("feature", "bf16", 3, 1597831, (1, 9), 0, 224, 14, (0, 2))]
-
-
-@pytest.mark.parametrize("axis,dtype,B,R,n,C,E,heads,picks", MANY)
-def test_more_workgroups_than_one_launch_holds(axis, dtype, B, R, n, C, E, heads, picks):
-    """2^24 and more workgroups of 256 threads: NC * heads * ceil(R / 64) on the item axis, a quarter
-    of B * R * heads * ceil(S / 16) on the feature axis.  One launch of them starts only what is left
-    modulo 2^32 threads.  Every dataset's rows are bit for bit those of a call on that dataset alone,
-    forward and backward."""
-    import numpy as np
-    import torch
-    from paper_2606_03681_amd import tfm
-    from paper_2606_03681_amd.stack import Stack
-    if axis == "item":
-        assert B * (C + 1) * heads * -(-R // 64) >= 1 << 24
-    else:
-        assert B * R * heads * -(-(C + 1) // 16) >= 1 << 26
-    gen = torch.Generator(device="cuda").manual_seed(17)
-    elt = torch.float32 if dtype == "f32" else torch.bfloat16
-    nt = np.random.default_rng(17).integers(n[0], n[1] + 1, B).astype(np.int32)
-    mask = np.ones((B, C + 1), np.uint8)
-
-    def block(b, X, dY, prm):
-        st = Stack(tfm.make_dims(len(nt[b]), R, C, E, heads, 32, dtype), nt[b], mask[b], [prm])
-        return st.forward(X[b]), st.backward(dY[b])
-
-    X = torch.empty((B, R, C + 1, E), device="cuda", dtype=elt).normal_(generator=gen)
-    dY = torch.empty_like(X).normal_(generator=gen)
-    prm = torch.randn(tfm.param_count(tfm.make_dims(B, R, C, E, heads, 32, dtype)), generator=gen,
-                      device="cuda") * 0.1
-    Y, dX = block(slice(None), X, dY, prm)
-    torch.cuda.synchronize()
-    for b in picks:
-        y, dx = block(slice(b, b + 1), X, dY, prm)
-        assert bool(torch.isfinite(y).all()) and bool(torch.isfinite(dx).all())
-        assert torch.equal(y[0], Y[b]) and torch.equal(dx[0], dX[b]), b
-    del X, dY, Y, dX
-    torch.cuda.empty_cache()
