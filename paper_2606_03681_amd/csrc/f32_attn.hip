@@ -46,6 +46,10 @@ __device__ __forceinline__ float dot4(const float4& a, const float4& b) {
 // Queries (keys, on the key side) are scaled by log2(e) / sqrt(d) as they are loaded, so that
 // scores are exponents of 2 for v_exp_f32; log-sum-exps are kept in the natural base.
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.69314718055994531f;
+// What a running softmax subtracts from its scores at running maximum mx: 0 while every score was
+// -infinity (a product that overflowed), whose terms are then 0 and not NaN, as they are to a later
+// finite maximum.  A row of such scores alone ends as 0 / 0.
+__device__ __forceinline__ float exp_ref(float mx) { return mx == -INFINITY ? 0.f : mx; }
 __device__ __forceinline__ float4 scale4(const float4& a, float f) {
   return make_float4(a.x * f, a.y * f, a.z * f, a.w * f);
 }
@@ -166,8 +170,8 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
         tm = fmaxf(tm, s[kb][x]);
       }
     }
-    const float mn = fmaxf(mx, rows4_max(tm));  // finite: every tile holds a key below n
-    const float al = exp2_hw(mx - mn);
+    const float mn = fmaxf(mx, rows4_max(tm)), ref = exp_ref(mn);
+    const float al = exp2_hw(mx - ref);
     mx = mn;
     sum *= al;
 #pragma unroll
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float p = exp2_hw(s[kb][x] - mx);
+        const float p = exp2_hw(s[kb][x] - ref);
         sum += p;
         const float* vr = &Vs[b][(16 * kb + 4 * lg + x) * LS + c];
 #pragma unroll
@@ -404,15 +408,15 @@ __global__ __launch_bounds__(256) void k_f32_feat_fwd(Geo g, const T* __restrict
       if (k0 + 4 * lg + x >= F.S) s[x] = -INFINITY;
       tm = fmaxf(tm, s[x]);
     }
-    const float mn = fmaxf(mx, rows4_max(tm));
-    const float al = exp2_hw(mx - mn);
+    const float mn = fmaxf(mx, rows4_max(tm)), ref = exp_ref(mn);
+    const float al = exp2_hw(mx - ref);
     mx = mn;
     sum *= al;
 #pragma unroll
     for (int i = 0; i < NB; ++i) acc[i] *= al;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      const float p = exp2_hw(s[x] - mx);
+      const float p = exp2_hw(s[x] - ref);
       sum += p;
 #pragma unroll
       for (int i = 0; i < NB; ++i) acc[i] = mfma32(vv[x][i], p, acc[i]);

@@ -63,3 +63,61 @@ def test_dX_may_share_memory_with_an_input(name, shared):
         got.append((out.clone(), st.grads[0].clone()))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def _overflow_inputs(dtype, axis, n, C, E, heads):
+    """One table whose attention along `axis` scores -infinity in float32 (a product of 1e40) against
+    the first half of the keys and 0 against the others: feature 0 of a cell is -1 or 0 (over the
+    others, +-1 in turn), Q holds 1e20 and K 1e20 times that feature of its norm-1 input."""
+    import numpy as np
+    rng = np.random.default_rng(3)
+    R = n + 3
+    prm = wl._draw_params(rng, E, 64, "xavier_bias")
+    at, views = 0, {}
+    for name, shape, _ in wl.param_layout(E, 64):
+        k = int(np.prod(shape))
+        views[name] = prm[at:at + k].reshape(shape)
+        at += k
+    ax = "f" if axis == "feature" else "i"
+    W, b = views["Wqkv_" + ax], views["bqkv_" + ax]
+    W[:2 * E] = 0
+    b[:2 * E] = 0
+    d = E // heads
+    for h in range(heads):
+        b[h * d] = 1e20
+        W[E + h * d, 0] = 1e20
+    if axis == "item":  # the item axis reads LN1(X + 0): no output of the feature axis
+        views["Wo_f"][:] = 0
+        views["bo_f"][:] = 0
+        views["g1"][0], views["be1"][0] = 1, 0
+    X = np.ones((1, R, C + 1, E))
+    X[..., 1::2] = -1
+    X[..., 0], X[..., -1] = 0, 0
+    low = (np.arange(R) < n // 2)[:, None] if axis == "item" else (np.arange(C + 1) < C // 2)[None]
+    X[0, ..., 0] = np.where(low, -1, 0)
+    X[0, ..., -1] = np.where(low, 1, 0)
+    return wl.to_storage(X, dtype), prm, np.array([n], np.int32), R
+
+
+@pytest.mark.parametrize("dtype,axis,n,C,heads", [("f32", "item", 80, 2, 6), ("f32", "item", 70, 1, 3),
+                                                  ("f32", "feature", 5, 70, 3),
+                                                  ("bf16", "feature", 5, 90, 6)])
+def test_first_key_tiles_of_overflowing_scores(dtype, axis, n, C, heads):
+    """Keys whose scores are -infinity have probability 0, also where every key of the first tiles
+    is one: the forward equals the oracle's, in which they are -1e40."""
+    import numpy as np
+    import oracle
+    import torch
+    from _harness import TOL, nerr
+    from paper_2606_03681_amd import tfm
+    from paper_2606_03681_amd.stack import Stack, to_device, to_host
+    E = 96
+    X, prm, nt, R = _overflow_inputs(dtype, axis, n, C, E, heads)
+    mask = np.ones((1, C + 1), np.uint8)
+    P = oracle.unpack_params(prm.astype(np.float64), E, 64)
+    ref, _ = oracle.stack_forward(wl.storage_to_f64(X, dtype), [P], nt, mask, heads)
+    Y = Stack(tfm.make_dims(1, R, C, E, heads, 64, dtype), nt, mask, [prm]).forward(
+        to_device(X, dtype))
+    got = to_host(Y, dtype)
+    torch.cuda.synchronize()
+    assert nerr(got, ref) <= TOL[dtype]
