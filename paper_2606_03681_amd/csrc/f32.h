@@ -80,7 +80,8 @@ hipError_t launch_f32_linear(const F32LinArgs<T>& a, hipStream_t s);
 
 // Item-axis attention (layouts as in attn.h), keys the first n_train rows of the column.  The
 // backward writes dq, dk, dv head-major (dk, dv at train rows only); Dbuf [NC * heads * R] is
-// scratch.
+// scratch.  On both axes lse is the base-2 log-sum-exp of the scores times log2(e), written and read
+// by these kernels only.
 template <class T>
 hipError_t launch_f32_item_fwd(const Geo& g, const T* q, const T* k, const T* v, T* o, float* lse,
                                hipStream_t s);

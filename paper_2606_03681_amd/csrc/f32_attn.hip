@@ -43,8 +43,10 @@ __device__ __forceinline__ float el(const float4& v, int j) {
 __device__ __forceinline__ float dot4(const float4& a, const float4& b) {
   return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, a.w * b.w)));
 }
-// Queries (keys, on the key side) are scaled by log2(e) / sqrt(d) as they are loaded, so that
-// scores are exponents of 2 for v_exp_f32; log-sum-exps are kept in the natural base.
+// Queries are scaled by log2(e) / sqrt(d) as they are loaded, so that scores are exponents of 2 for
+// v_exp_f32, and log-sum-exps are kept in base 2: every kernel forms a score from the same operands in
+// the same order, so a dominant key's score less the log-sum-exp is exact, and its probability 1,
+// however large the scores are.
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.69314718055994531f;
 // What a running softmax subtracts from its scores at running maximum mx: 0 while every score was
 // -infinity (a product that overflowed), whose terms are then 0 and not NaN, as they are to a later
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256) void k_f32_item_fwd(Geo g, const T* __restrict
 #pragma unroll
   for (int i = 0; i < NB; ++i)
     st4(o + (P.col * g.R + r) * g.E + P.head * D + 16 * i + 4 * lg, acc[i] * inv);
-  if (lg == 0) lse[base + r] = fmaf(mx, LN2, logf(sum));
+  if (lg == 0) lse[base + r] = mx + log2f(sum);
 }
 
 template <class T, int D>
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dq(Geo g, const T* __restrict_
     Dr += dot4(df.v[i], of.v[i]);
   }
   Dr = rows4_sum(Dr);
-  const float L = rok ? lse[base + r] * LOG2E : 0.f;
+  const float L = rok ? lse[base + r] : 0.f;
   if (rok && lg == 0) Dbuf[base + r] = Dr;
   f32x4 acc[NB];
 #pragma unroll
@@ -282,10 +284,8 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
   const int64_t base = P.ch * g.R;
   const T* od = dout + P.col * g.R * g.E + P.head * D;
   const float tau = 1.0f / sqrtf((float)D);
-  Row<D> kf = ld_row<D>(k + (base + t) * D, tok, lg);
+  const Row<D> kf = ld_row<D>(k + (base + t) * D, tok, lg);
   const Row<D> vf = ld_row<D>(v + (base + t) * D, tok, lg);
-#pragma unroll
-  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau * LOG2E);
   f32x4 ak[NB], av[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) ak[i] = av[i] = zero4();
@@ -295,10 +295,12 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
     st.load(q + base * D, D, od, g.E, r0, g.R);
     // rows past the end: zero dO, L and D give P = 1 against zero rows
     const bool ok = tid < TK && r0 + tid < g.R;
-    sl = ok ? lse[base + r0 + tid] * LOG2E : 0.f;
+    sl = ok ? lse[base + r0 + tid] : 0.f;
     sd = ok ? Dbuf[base + r0 + tid] : 0.f;
   };
   auto store = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < st.NI; ++i) st.a[i] = scale4(st.a[i], tau * LOG2E);
     st.store(Qs[b], Os[b]);
     if (tid < TK) {
       Ls[b][tid] = sl;
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(256) void k_f32_item_dkv(Geo g, const T* __restrict
   if (!tok) return;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    st4(dk + (base + t) * D + 16 * i + 4 * lg, ak[i] * tau);
+    st4(dk + (base + t) * D + 16 * i + 4 * lg, ak[i] * LN2);  // Q carries tau log2(e)
     st4(dv + (base + t) * D + 16 * i + 4 * lg, av[i]);
   }
 }
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_fwd(Geo g, const T* __restrict
   const float inv = 1.0f / sum;
 #pragma unroll
   for (int i = 0; i < NB; ++i) st4(o + pq * E + hd + 16 * i + 4 * lg, acc[i] * inv);
-  if (lg == 0) lse[pq * g.heads + F.head] = fmaf(mx, LN2, logf(sum));
+  if (lg == 0) lse[pq * g.heads + F.head] = mx + log2f(sum);
 }
 
 // The wave's 16 cells first as queries (dQ, over every key), then as keys (dK, dV, over every
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
     Row<D> qf = ld_row<D>(qkv + pc * E3 + hd, own, lg);
     const Row<D> df = ld_row<D>(dout + pc * E + hd, own, lg);
     const Row<D> of = ld_row<D>(o + pc * E + hd, own, lg);
-    const float L = own ? lse[pc * g.heads + F.head] * LOG2E : 0.f;
+    const float L = own ? lse[pc * g.heads + F.head] : 0.f;
     float Dr = 0.f;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -490,26 +492,26 @@ __global__ __launch_bounds__(256) void k_f32_feat_bwd(Geo g, const T* __restrict
     }
   }
   // as keys
-  Row<D> kf = ld_row<D>(qkv + pc * E3 + E + hd, own, lg);
+  const Row<D> kf = ld_row<D>(qkv + pc * E3 + E + hd, own, lg);
   const Row<D> vf = ld_row<D>(qkv + pc * E3 + 2 * E + hd, own, lg);
-#pragma unroll
-  for (int i = 0; i < NB; ++i) kf.v[i] = scale4(kf.v[i], tau * LOG2E);
   f32x4 ak[NB], av[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) ak[i] = av[i] = zero4();
   for (int q0 = 0; q0 < F.S; q0 += 16) {
     const bool qok = q0 + c < F.S;
     const int64_t p = cell(q0 + c);
-    const Row<D> qf = ld_row<D>(qkv + p * E3 + hd, qok, lg);
+    Row<D> qf = ld_row<D>(qkv + p * E3 + hd, qok, lg);
     const Row<D> df = ld_row<D>(dout + p * E + hd, qok, lg);
     const Row<D> of = ld_row<D>(o + p * E + hd, qok, lg);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) qf.v[i] = scale4(qf.v[i], tau * LOG2E);
     float qt[4][NB], dt[4][NB], Lx[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int qq = q0 + 4 * lg + x;
       const bool ok = qq < F.S;
       const int64_t px = cell(qq);
-      Lx[x] = ok ? lse[px * g.heads + F.head] * LOG2E : 0.f;
+      Lx[x] = ok ? lse[px * g.heads + F.head] : 0.f;
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         qt[x][i] = ok ? ld(qkv + px * E3 + hd + c + 16 * i) : 0.f;

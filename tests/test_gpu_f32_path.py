@@ -121,3 +121,41 @@ def test_first_key_tiles_of_overflowing_scores(dtype, axis, n, C, heads):
     got = to_host(Y, dtype)
     torch.cuda.synchronize()
     assert nerr(got, ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("axis", ["item", "feature"])
+@pytest.mark.parametrize("E,heads", [(32, 2), (96, 3), (128, 2)])
+def test_probabilities_of_large_scores(axis, E, heads):
+    """A key that dominates has probability 1 in the backward too, whatever its score: with one key
+    and scores of some 1e6 the value gradients are those of the oracle.  (A probability from a
+    rounded log-sum-exp is off by the score's rounding, 0.1 there.)"""
+    import numpy as np
+    import torch
+    from _harness import TOL, nerr
+    import oracle
+    from paper_2606_03681_amd import tfm
+    from paper_2606_03681_amd.stack import Stack, to_device
+    rng = np.random.default_rng(11)
+    B, R, H, n = 3, 50, 64, (1 if axis == "item" else 20)
+    C = 0 if axis == "feature" else 2
+    prm = wl._draw_params(rng, E, H, "xavier_bias")
+    at = 0
+    for name, shape, _ in wl.param_layout(E, H):
+        k = int(np.prod(shape))
+        if name == ("bqkv_i" if axis == "item" else "bqkv_f"):
+            prm[at:at + 2 * E] *= 5000
+        at += k
+    X = rng.normal(size=(B, R, C + 1, E)).astype(np.float32)
+    dY = rng.normal(size=X.shape).astype(np.float32)
+    nt, mask = np.full(B, n, np.int32), np.ones((B, C + 1), np.uint8)
+    st = Stack(tfm.make_dims(B, R, C, E, heads, H, "f32"), nt, mask, [prm])
+    st.forward(to_device(X, "f32"))
+    st.backward(to_device(dY, "f32"))
+    torch.cuda.synchronize()
+    got = oracle.unpack_params(st.grads[0].double().cpu().numpy(), E, H)
+    Y, caches = oracle.stack_forward(X.astype(np.float64), [oracle.unpack_params(
+        prm.astype(np.float64), E, H)], nt, mask, heads)
+    _, (want,) = oracle.stack_backward(dY.astype(np.float64), caches)
+    ax = "i" if axis == "item" else "f"
+    for name in ("Wqkv_" + ax, "bqkv_" + ax):
+        assert nerr(got[name][2 * E:], want[name][2 * E:]) <= TOL["f32"], name
