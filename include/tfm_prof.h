@@ -11,6 +11,8 @@
 
 #include <stddef.h>
 
+#include "tfm_layer.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -30,9 +32,17 @@ int tfm_prof_step(int i, const char** name, long long* launches, double* total_m
 /* Attribution of the item-attention backward to steps, for tools that price each step: on the
  * bfloat16 MFMA path the columns whose train prefix has at most this many rows run in the
  * one-kernel backward (step "item_attn_bwd") where their number fills it, else with the longer
- * prefixes in the two-kernel form (steps "item_attn_dq" and "item_attn_dkdv").  Returns 0 when head_dim has no one-kernel form.
- * Pure host function: no device, no side effects. */
+ * prefixes in the two-kernel form (steps "item_attn_dq" and "item_attn_dkdv").  Returns 0 when
+ * head_dim has no one-kernel form.  Pure host function: no device, no side effects. */
 int tfm_prof_item_bwd_fused_rows(int head_dim);
+
+/* The same for one backward call: the number of active columns that run in the one-kernel form
+ * (0 also off the bfloat16 MFMA path), or a negative code of tfm_layer.h.  order (nullable, room
+ * for B * (C + 1) entries) receives every active column, numbered dataset by dataset, in the order
+ * in which they are launched: the one-kernel columns, then the others, within each group the
+ * longer train prefixes first.  Pure host function. */
+int tfm_prof_item_bwd_columns(const tfm_dims* dims, const int32_t* n_train,
+                              const uint8_t* cell_mask, int32_t* order);
 
 #ifdef __cplusplus
 }

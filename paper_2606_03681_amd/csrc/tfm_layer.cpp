@@ -271,10 +271,10 @@ struct Plan {
   // of the item-attention backward (below), mask words
   std::vector<int32_t> blob;
   int stride = 0;
-  // Column order of the item-attention backward: the columns of datasets whose train prefix
-  // fits the one-kernel form first (nF of them, longest prefix nmaxF), then the others; within
-  // each group the longer prefixes first, so the largest problems start earliest and the
-  // launches end evenly.  natural: one group, in the order of the columns.
+  // Column order of the item-attention backward: the columns that run in the one-kernel form first
+  // (nF of them, longest prefix nmaxF), then the others; within each group the longer prefixes
+  // first, so the largest problems start earliest and the launches end evenly.  natural: one
+  // group, in the order of the columns.
   int nF = 0, nmaxF = 0;
   bool natural = true;
 };
@@ -310,14 +310,41 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
   return TFM_OK;
 }
 
-// Orders the columns for the item-attention backward at head width d.
+// Whether `problems` (column, head) problems of R rows and at most nmax keys that fit the one-kernel
+// item-attention backward should take it.
+// The one-kernel form runs a problem per CU and pays for whole rounds of 256 and for whole
+// thirds of its 768 keys; the two kernels compute each probability twice but spread over rows and
+// keys.  Microseconds as measured over d in {16, 32}, 64 to 768 keys (R = 4/3 of them) and 84 to
+// 3,936 problems: a 32-row chunk of a round costs 1.7 / 2.1 / 2.57 (d = 16: 1.75, two problems a
+// CU / 1.95 / 2.27) for up to 256 / 512 / 768 keys; the two kernels 20 a call, 0.01 a problem and
+// 4.9e-7 (3.9e-7) a score of whole 128 x 128 tiles.  One against two, d = 32: 768 keys 83 / 75 us
+// at 126 problems, 166 / 135 at 264, 1,314 / 1,604 at 3,936; 512 keys 712 / 719 at 3,936; 384
+// keys 521 / 464; 128 keys 21 / 22 at 264.
+bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax) {
+  const int third = nmax <= 256 ? 0 : (nmax <= 512 ? 1 : 2);
+  const double c32[3] = {1.7, 2.1, 2.57}, c16[3] = {1.75, 1.95, 2.27};
+  const int64_t slots = d == 16 && third == 0 ? 512 : 256;
+  const double one = (double)((problems + slots - 1) / slots) * ((R + 31) / 32) *
+                     (d == 16 ? c16 : c32)[third];
+  const double tile = (double)((R + 127) / 128 * 128) * ((nmax + 127) / 128 * 128);
+  const double two = 20.0 + (double)problems * (0.01 + tile * (d == 16 ? 3.9e-7 : 4.9e-7));
+  return one <= 1.05 * two;
+}
+
+// Chooses the form of the item-attention backward for each column and orders the columns for it.
 void order_columns(const Dims& d, Plan& P) {
   const int fmax = tfm::item_attn_bwd_fused_max_rows(d.d);
+  auto rec = [&](int b) { return &P.blob[(size_t)b * P.stride]; };
+  for (int b = 0; b < d.B; ++b)
+    if (rec(b)[0] <= fmax) {
+      P.nF += rec(b)[2];
+      P.nmaxF = std::max(P.nmaxF, rec(b)[0]);
+    }
+  if (!item_attn_bwd_fused_pays(d.d, (int64_t)P.nF * d.heads, d.R, P.nmaxF)) P.nF = P.nmaxF = 0;
   std::vector<int> order(d.B);
   std::iota(order.begin(), order.end(), 0);
-  auto rec = [&](int b) { return &P.blob[(size_t)b * P.stride]; };
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    const bool fx = rec(x)[0] <= fmax, fy = rec(y)[0] <= fmax;
+    const bool fx = rec(x)[0] <= P.nmaxF, fy = rec(y)[0] <= P.nmaxF;
     return fx != fy ? fx : rec(x)[0] > rec(y)[0];
   });
   int place = 0;
@@ -326,10 +353,6 @@ void order_columns(const Dims& d, Plan& P) {
     e[3] = place;
     place += e[2];
     P.natural = P.natural && e[3] == e[1];
-    if (e[0] <= fmax) {
-      P.nF += e[2];
-      P.nmaxF = std::max(P.nmaxF, e[0]);
-    }
   }
   P.natural = P.natural && (P.nF == 0 || P.nF == P.NC);
 }
@@ -380,27 +403,6 @@ int setup_geo(const Dims& d, const Plan& P, char* ws, const MetaOff& W, tfm::Geo
   return TFM_OK;
 }
 
-// Whether `problems` (column, head) problems of R rows and at most nmax keys that fit the one-kernel
-// item-attention backward should take it.
-// The one-kernel form runs a problem per CU and pays for whole rounds of 256 and for whole
-// thirds of its 768 keys; the two kernels compute each probability twice but spread over rows and
-// keys.  Microseconds as measured over d in {16, 32}, 64 to 768 keys (R = 4/3 of them) and 84 to
-// 3,936 problems: a 32-row chunk of a round costs 1.7 / 2.1 / 2.57 (d = 16: 1.75, two problems a
-// CU / 1.95 / 2.27) for up to 256 / 512 / 768 keys; the two kernels 20 a call, 0.01 a problem and
-// 4.9e-7 (3.9e-7) a score of whole 128 x 128 tiles.  One against two, d = 32: 768 keys 83 / 75 us
-// at 126 problems, 166 / 135 at 264, 1,314 / 1,604 at 3,936; 512 keys 712 / 719 at 3,936; 384
-// keys 521 / 464; 128 keys 21 / 22 at 264.
-bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax) {
-  const int third = nmax <= 256 ? 0 : (nmax <= 512 ? 1 : 2);
-  const double c32[3] = {1.7, 2.1, 2.57}, c16[3] = {1.75, 1.95, 2.27};
-  const int64_t slots = d == 16 && third == 0 ? 512 : 256;
-  const double one = (double)((problems + slots - 1) / slots) * ((R + 31) / 32) *
-                     (d == 16 ? c16 : c32)[third];
-  const double tile = (double)((R + 127) / 128 * 128) * ((nmax + 127) / 128 * 128);
-  const double two = 20.0 + (double)problems * (0.01 + tile * (d == 16 ? 3.9e-7 : 4.9e-7));
-  return one <= 1.05 * two;
-}
-
 // Item-attention backward on the MFMA path, in the plan's column order: one-kernel columns, then
 // the others through the dQ and dK/dV kernels.
 int item_attn_bwd(const Dims& d, const tfm::Geo& g, const Plan& P, char* ws, const MetaOff& M,
@@ -409,14 +411,12 @@ int item_attn_bwd(const Dims& d, const tfm::Geo& g, const Plan& P, char* ws, con
                   tfm::bf16* dq, tfm::bf16* dk, tfm::bf16* dv, hipStream_t s) {
   using namespace tfm;
   const int32_t* dcols = P.natural ? nullptr : (const int32_t*)(ws + M.cord);
-  const int nmaxF = P.nmaxF;
-  const int nF = item_attn_bwd_fused_pays(d.d, (int64_t)P.nF * d.heads, d.R, nmaxF) ? P.nF : 0;
-  const ColList F{dcols, nF};
-  const ColList T{dcols ? dcols + nF : nullptr, P.NC - nF};
-  if (nF > 0)
+  const ColList F{dcols, P.nF};
+  const ColList T{dcols ? dcols + P.nF : nullptr, P.NC - P.nF};
+  if (P.nF > 0)
     STEP("item_attn_bwd/mfma",
-         launch_item_attn_bwd_fused(g, F, nmaxF, qi, ki, vi, oi, doi, lsei, dq, dk, dv, s));
-  if (nF < P.NC) {
+         launch_item_attn_bwd_fused(g, F, P.nmaxF, qi, ki, vi, oi, doi, lsei, dq, dk, dv, s));
+  if (P.nF < P.NC) {
     STEP("item_attn_dq/mfma", launch_item_attn_dq(g, T, qi, ki, vi, oi, doi, lsei, Dq, dq, s));
     STEP("item_attn_dkdv/mfma",
          launch_item_attn_dkdv(g, T, qi, ki, vi, oi, doi, lsei, Dq, dk, dv, s));
@@ -1215,6 +1215,22 @@ const char* tfm_last_error(void) { return g_err.c_str(); }
 
 int tfm_prof_item_bwd_fused_rows(int head_dim) {
   return tfm::item_attn_bwd_fused_max_rows(head_dim);
+}
+
+int tfm_prof_item_bwd_columns(const tfm_dims* dims, const int32_t* n_train,
+                              const uint8_t* cell_mask, int32_t* order) {
+  Dims d;
+  int rc = check_dims(dims, d);
+  if (rc) return rc;
+  Plan P;
+  rc = make_plan(d, n_train, cell_mask, P);
+  if (rc) return rc;
+  if (fast_eligible(d)) order_columns(d, P);
+  for (int b = 0; b < d.B && order; ++b) {
+    const int32_t* e = &P.blob[(size_t)b * P.stride];
+    for (int k = 0; k < e[2]; ++k) order[e[3] + k] = e[1] + k;
+  }
+  return P.nF;
 }
 
 int tfm_layer_fwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* cell_mask,

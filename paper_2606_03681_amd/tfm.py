@@ -27,7 +27,8 @@ EXPORTS = ("tfm_layer_param_count", "tfm_layer_saved_bytes", "tfm_layer_workspac
            "tfm_thinking_rows_bwd",
            "tfm_infer_workspace_bytes", "tfm_infer_cache_bytes", "tfm_layer_fwd_context",
            "tfm_layer_fwd_query", "tfm_last_error", "tfm_prof_enable", "tfm_prof_collect",
-           "tfm_prof_step", "tfm_prof_item_bwd_fused_rows", "tfm_ends_param_count", "tfm_ends_workspace_bytes", "tfm_encode_fwd",
+           "tfm_prof_step", "tfm_prof_item_bwd_fused_rows", "tfm_prof_item_bwd_columns",
+           "tfm_ends_param_count", "tfm_ends_workspace_bytes", "tfm_encode_fwd",
            "tfm_encode_bwd", "tfm_decode_fwd", "tfm_decode_loss", "tfm_clip_workspace_bytes",
            "tfm_clip_scale", "tfm_sfadamw_step", "tfm_muon_workspace_bytes", "tfm_muon_step")
 
@@ -141,6 +142,8 @@ def lib():
                                     P(ctypes.c_double)]
         L.tfm_prof_item_bwd_fused_rows.restype = i32
         L.tfm_prof_item_bwd_fused_rows.argtypes = [i32]
+        L.tfm_prof_item_bwd_columns.restype = i32
+        L.tfm_prof_item_bwd_columns.argtypes = [P(tfm_dims), vp, vp, vp]
         _lib = L
     return _lib
 
@@ -394,6 +397,19 @@ def prof_item_bwd_fused_rows(head_dim):
     """Longest train prefix whose item-attention backward runs as the one-kernel step
     "item_attn_bwd" at this head dimension (0: never); see tfm_prof.h."""
     return int(lib().tfm_prof_item_bwd_fused_rows(int(head_dim)))
+
+
+def prof_item_bwd_columns(dims, n_train, cell_mask):
+    """(number of columns of the one-kernel item-attention backward, every active column in launch
+    order) for a backward call; see tfm_prof.h."""
+    n = np.ascontiguousarray(n_train, dtype=np.int32)
+    m = np.ascontiguousarray(cell_mask, dtype=np.uint8)
+    order = np.empty(int(np.count_nonzero(m)), np.int32)
+    k = lib().tfm_prof_item_bwd_columns(ctypes.byref(dims), n.ctypes.data, m.ctypes.data,
+                                        order.ctypes.data)
+    if k < 0:
+        raise TfmError(k, last_error())
+    return k, order
 
 
 def prof_collect():

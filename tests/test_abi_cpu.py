@@ -374,3 +374,41 @@ def test_noalloc_forward_limits_rejected_before_launch():
     d = _dims(dtype="bf16")
     rc = tfm.lib().tfm_layer_fwd_noalloc(ctypes.byref(d), None, None, p, p, p, 0, 1 << 40, None)
     assert rc == -5
+
+
+@pytest.mark.parametrize("d,R,few,many", [(16, 1000, 2, 60), (32, 1000, 2, 60), (64, 300, 3, 30),
+                                          (32, 300, 4, 200)])
+def test_item_backward_column_order(d, R, few, many):
+    """The columns of the item-attention backward: the one-kernel columns (prefixes within its
+    limit) and the others are two groups, each with the longer prefixes first; where too few columns
+    fit the one-kernel form to fill it, all columns are one such group."""
+    limit = tfm.prof_item_bwd_fused_rows(d)
+    rng = np.random.default_rng(d + R)
+    E, C = 4 * d if d < 64 else 2 * d, 7
+    forms = set()
+    for B in (1, few, many, few, many):
+        n = rng.integers(1, R + 1, B).astype(np.int32)
+        mask = (rng.random((B, C + 1)) < 0.6).astype(np.uint8)
+        mask[:, C] = 1
+        prefix = np.repeat(n, mask.sum(1, dtype=np.int64))
+        k, order = tfm.prof_item_bwd_columns(
+            tfm.make_dims(B, R, C, E, E // d, E, "bf16"), n, mask)
+        assert sorted(order.tolist()) == list(range(len(prefix)))
+        p = prefix[order]
+        assert np.all(np.diff(p[:k]) <= 0) and np.all(np.diff(p[k:]) <= 0)
+        if k:
+            assert p[:k].max() <= limit and (k == len(p) or p[k:].min() > limit)
+        forms.add("one" if k == len(p) else "mixed" if k else "two")
+    assert "two" in forms if d == 64 else forms & {"one", "mixed"}
+    # float32 calls keep the columns' own order
+    k, order = tfm.prof_item_bwd_columns(tfm.make_dims(B, R, C, E, E // d, E, "f32"), n, mask)
+    assert k == 0 and order.tolist() == list(range(len(prefix)))
+
+
+def test_item_backward_column_order_rejects_bad_calls():
+    d = tfm.make_dims(1, 10, 3, 64, 2, 128, "bf16")
+    mask = np.ones((1, 4), np.uint8)
+    for n, m, code in (([0], mask, -3), ([11], mask, -3), ([5], mask * 0, -4)):
+        with pytest.raises(tfm.TfmError) as e:
+            tfm.prof_item_bwd_columns(d, n, m)
+        assert e.value.code == code
