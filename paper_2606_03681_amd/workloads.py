@@ -107,9 +107,10 @@ TEST_CONFIGS = {
     "tiny-mlp-bf16": dict(name="tiny-mlp-bf16", dtype="bf16", B=2, R=9, n_train=5, C=2, E=192,
                           heads=6, H=384, layers=2, cells="normal", weights="xavier_bias"),
     # train prefixes on both sides of the one-kernel item-attention backward's limit (768
-    # rows): its columns and those of the two-kernel form run in separate launches
-    "mixed-prefix-bf16": dict(name="mixed-prefix-bf16", dtype="bf16", B=5, R=1000,
-                              n_train=(600, 1000), C=6, active=(1, 6), mask="random", E=192,
+    # rows), with enough columns below it to fill that form (30 of 60): its columns and those of
+    # the two-kernel form run in separate launches
+    "mixed-prefix-bf16": dict(name="mixed-prefix-bf16", dtype="bf16", B=10, R=1000,
+                              n_train=(550, 950), C=8, active=(4, 8), mask="random", E=192,
                               heads=6, H=384, layers=1, cells="normal", weights="xavier_bias"),
     # rows wider than the matrix-core feature attention takes (more than 128 cells at d = 32,
     # more than 64 at d = 64): the bfloat16 feature attention runs on the vector kernels
