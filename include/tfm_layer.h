@@ -125,8 +125,9 @@ int tfm_layer_bwd(const tfm_dims* dims, const int32_t* n_train, const uint8_t* c
  * allocating routine.
  *
  * Limits: TFM_BF16 with E in {64, 128, 192, 256} and H a multiple of E (either block); dims whose
- * scratch exceeds TFM_NOALLOC_SCRATCH_BYTES (the bf16 weights, 2 (8E^2 + 2EH) bytes, plus about
- * 24 B (C+1) + 28 + 4 ceil((C+1)/32) bytes per dataset) return TFM_ERR_BUFFER; a stream of another
+ * scratch exceeds TFM_NOALLOC_SCRATCH_BYTES return TFM_ERR_BUFFER (the bf16 weights and folded biases,
+ * 2 (8E^2 + 2EH) + 4 (3E + H) bytes, another 0.6 MB at E = 192, H = 384, plus 20 (C+1) + 32 +
+ * 4 ceil((C+1)/32) bytes per dataset); a stream of another
  * device than the current one returns TFM_ERR_HIP.  The array is shared by every call on one
  * GPU and keeps the last call's contents (nothing in it needs to start at zero: each call
  * rewrites what it reads), so calls that overlap on one GPU (concurrent streams, or threads)

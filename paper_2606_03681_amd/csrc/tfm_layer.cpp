@@ -230,7 +230,10 @@ size_t saved_total(const Dims& d) {
 
 struct WsLayout {
   MetaOff meta;
-  size_t ta, tb, tc, te, tf, th1, th2, tq, tk, tv, tqkv, D;
+  size_t ta;            // float32 mode, forward
+  size_t tb;            // post-norm block
+  size_t tc, te, tf, th1, tq, tk, tv, tqkv, D;
+  size_t th2;           // fused MLP: U for the weight gradient
   size_t part, lnpart;  // float32 mode: weight / bias partials, norm partials
   size_t fast;          // region owned by the MFMA path
   size_t total;
@@ -241,19 +244,19 @@ WsLayout ws_layout(const Dims& d) {
   Arena a;
   const size_t N = (size_t)d.Nmax, t = d.tsz, E = d.E;
   L.meta = take_meta(d, a);
-  L.ta = a.take(N * E * t);
-  L.tb = a.take(N * E * t);
+  const bool f32 = !fast_eligible(d), pre = d.block == TFM_BLOCK_PRENORM;
+  L.ta = a.take(f32 ? N * E * t : 0);
+  L.tb = a.take(pre ? 0 : N * E * t);
   L.tc = a.take(N * E * t);
   L.te = a.take(N * E * t);
   L.tf = a.take(N * E * t);
   L.th1 = a.take(N * d.H * t);
-  L.th2 = a.take(N * d.H * t);
+  L.th2 = a.take(!f32 && !pre && tfm::mlp_fused_ok(d.E, d.H) ? N * d.H * t : 0);
   L.tq = a.take(N * E * t);
   L.tk = a.take(N * E * t);
   L.tv = a.take(N * E * t);
   L.tqkv = a.take(N * 3 * E * t);
   L.D = a.take(N * d.heads * 4);
-  const bool f32 = !fast_eligible(d);
   L.part = a.take(f32 ? tfm::f32_wpart_floats(d.Nmax, d.E, d.H) * 4 : 0);
   L.lnpart = a.take(f32 ? tfm::f32_lnpart_floats(d.Nmax, d.E) * 4 : 0);
   L.fast = a.take(f32 ? 0 : tfm::fast_workspace_bytes(d.Nmax, d.E, d.H));
@@ -589,7 +592,7 @@ int bwd_simple(const Dims& d, const tfm::Geo& g, const T* X, const float* prm, c
 // ---- MFMA path (bfloat16) -------------------------------------------------------------------
 struct FastWs {
   tfm::bf16* w;
-  tfm::bf16* wt;
+  tfm::bf16* wt;     // transposed weights (a backward's; null in forward-only calls)
   float* lnpart[3];  // column partials of norm 1, 2, 3 (2 and 3 adjacent)
   float* wpart;      // weight and bias partials
   tfm::WOff wo;
@@ -1059,7 +1062,7 @@ int bwd_pre(const Dims& d, const tfm::Geo& g, const Plan& P, const float* prm, c
 // p5: x', then h2, and p6: r1, then r2, then r3), one rstd and one log-sum-exp scratch.
 struct InferLayout {
   MetaOff meta;
-  size_t w, wt, p1, p2, p3, p4, p5, p6, rs, lse, total;
+  size_t w, p1, p2, p3, p4, p5, p6, rs, lse, total;
 };
 
 bool infer_eligible(const Dims& d) {
@@ -1074,7 +1077,6 @@ InferLayout infer_layout(const Dims& d) {
   const tfm::WOff wo = tfm::weight_offsets(d.E, d.H);
   L.meta = take_meta(d, a);
   L.w = a.take((size_t)wo.total * 2);
-  L.wt = a.take((size_t)wo.total * 2);
   L.p1 = a.take(N * (3 * E > (size_t)d.H ? 3 * E : (size_t)d.H) * 2);
   L.p2 = a.take(N * E * 2);
   L.p3 = a.take(N * E * 2);
@@ -1127,7 +1129,6 @@ FastWs infer_fast_ws(const Dims& d, char* ws, const InferLayout& L) {
   FastWs f{};
   f.wo = tfm::weight_offsets(d.E, d.H);
   f.w = (tfm::bf16*)(ws + L.w);
-  f.wt = (tfm::bf16*)(ws + L.wt);
   return f;
 }
 
@@ -1341,7 +1342,6 @@ int tfm_layer_fwd_noalloc(const tfm_dims* dims, const int32_t* n_train, const ui
   const MetaOff M = take_meta(d, a);
   const tfm::WOff wo = tfm::weight_offsets(d.E, d.H);
   const size_t w_off = a.take((size_t)wo.total * 2);
-  const size_t wt_off = a.take((size_t)wo.total * 2);
   if (a.off > tfm::kStaticScratchBytes)
     return fail(TFM_ERR_BUFFER, "these dims need %zu bytes of library scratch; the maximum is "
                                 "%zu (TFM_NOALLOC_SCRATCH_BYTES)", a.off,
@@ -1359,7 +1359,6 @@ int tfm_layer_fwd_noalloc(const tfm_dims* dims, const int32_t* n_train, const ui
   FastWs f{};
   f.wo = wo;
   f.w = (tfm::bf16*)(ws + w_off);
-  f.wt = (tfm::bf16*)(ws + wt_off);
   const tfm::SetupWeights sw = setup_weights(d, params, f, false);
   tfm::Geo g;
   rc = setup_geo(d, P, ws, M, g, &sw, s);

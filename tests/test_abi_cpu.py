@@ -376,6 +376,37 @@ def test_noalloc_forward_limits_rejected_before_launch():
     assert rc == -5
 
 
+@pytest.mark.parametrize("dtype,block,E,heads,H,units", [
+    ("f32", "post", 192, 6, 384, (11, 1)), ("bf16", "post", 96, 3, 192, (11, 1)),
+    ("bf16", "post", 192, 6, 384, (10, 2)), ("bf16", "post", 192, 6, 768, (10, 1)),
+    ("bf16", "pre", 256, 4, 768, (9, 1))])
+def test_workspace_holds_what_a_call_uses(dtype, block, E, heads, H, units):
+    """Scratch per cell: units[0] rows of E values and units[1] rows of H values, the row sums of the
+    item attention, and the partial sums of the gradients (at most one set for each 2,048 cells,
+    8,192 on the bfloat16 matrix-core path, and one row of norm partials for each 64 cells)."""
+    B, C = 16, 63
+    ws = [tfm.workspace_bytes(tfm.make_dims(B, R, C, E, heads, H, dtype, block))
+          for R in (2048, 4096)]
+    cells = B * (C + 1) * 2048
+    t = 4 if dtype == "f32" else 2
+    fast = dtype == "bf16" and E in (64, 128, 192, 256)
+    part = 4 * (8 * E * E + 2 * E * H + 9 * E + H) / (8192 if fast else 2048)
+    norm = 3 * 2 * E * 4 / 64 if fast else 0
+    per_cell = (units[0] * E + units[1] * H) * t + 4 * heads + part + norm
+    assert (ws[1] - ws[0]) / cells <= 1.01 * per_cell
+
+
+@pytest.mark.parametrize("block,E,heads,H", [("post", 192, 6, 384), ("pre", 256, 4, 768),
+                                             ("post", 64, 2, 1024)])
+def test_forward_only_scratch_has_one_copy_of_the_weights(block, E, heads, H):
+    """A forward reads the weights as stored: the workspace of a forward-only call on one cell is
+    one bfloat16 copy of them (and the fused MLP's stream, as large as its matrices), not two."""
+    one = 2 * (8 * E * E + 2 * E * H)
+    stream = 2 * (E * E + 3 * E * H) if (E, H) == (192, 384) else 0
+    d = tfm.make_dims(1, 1, 0, E, heads, H, "bf16", block)
+    assert one <= tfm.infer_workspace_bytes(d) <= one + stream + 24 * (E + H) + 8192
+
+
 @pytest.mark.parametrize("d,R,few,many", [(16, 1000, 2, 60), (32, 1000, 2, 60), (64, 300, 3, 30),
                                           (32, 300, 4, 200)])
 def test_item_backward_column_order(d, R, few, many):
