@@ -25,11 +25,10 @@ hipError_t launch_item_attn_dkdv(const Geo& g, const ColList& cl, const bf16* q,
                                  const float* lse, const float* Dbuf, bf16* dk, bf16* dv,
                                  hipStream_t s);
 
-// The same backward in one launch for train prefixes of at most 768 rows at d in {16, 32}
-// (item_attn_bwd_fused_ok): one workgroup per (column, head) problem of the columns in cl
-// computes P and dS once per score and writes dq, dk and dv; nmax is the longest train prefix
-// among those columns.
-bool item_attn_bwd_fused_ok(const Geo& g, int nmax);
+// The same backward in one launch for train prefixes of at most item_attn_bwd_fused_max_rows(d)
+// rows (768 at d in {16, 32}; 0: no such form): one workgroup per (column, head) problem of the
+// columns in cl computes P and dS once per score and writes dq, dk and dv; nmax is the longest
+// train prefix among those columns.
 int item_attn_bwd_fused_max_rows(int d);
 hipError_t launch_item_attn_bwd_fused(const Geo& g, const ColList& cl, int nmax, const bf16* q,
                                       const bf16* k, const bf16* v, const bf16* o,

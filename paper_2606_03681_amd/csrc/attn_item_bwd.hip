@@ -671,8 +671,6 @@ static int fused_nkb(int d, int nmax) {
   return 0;
 }
 
-bool item_attn_bwd_fused_ok(const Geo& g, int nmax) { return fused_nkb(g.d, nmax) > 0; }
-
 int item_attn_bwd_fused_max_rows(int d) { return fused_nkb(d, 1) > 0 ? 768 : 0; }
 
 // fn(geo, list, c0) for pieces of the columns of cl (by_columns): without a list the piece's columns

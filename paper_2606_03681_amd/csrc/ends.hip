@@ -11,6 +11,7 @@
 // Decoder: gather of the decoder input, float32 GEMMs on the MFMA with bias/GELU epilogues, a
 // masked softmax cross entropy per row, and a scatter that writes the whole dY.
 #include "ends.h"
+#include "gelu.h"
 
 #include <hip/hip_runtime.h>
 
@@ -398,14 +399,6 @@ __global__ __launch_bounds__(256) void k_cross_entropy(EndsGeo g, const float* _
 // v_mfma_f32_16x16x4f32), K staged through LDS 16 at a time with zero fill past the edges.
 // Operand lanes: A[i][k] from lane i + 16 k, B[k][j] from lane j + 16 k; result D[i][j] in
 // lane j + 16 (i / 4), element i % 4.
-__device__ __forceinline__ float gelu_exact(float v) {
-  return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_exact_grad(float v) {
-  const float cdf = 0.5f * (1.0f + erff(v * 0.70710678118654752f));
-  return cdf + v * 0.39894228040143268f * expf(-0.5f * v * v);
-}
-
 template <bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256) void k_sgemm(SgemmArgs a) {
   __shared__ float As[16][68];

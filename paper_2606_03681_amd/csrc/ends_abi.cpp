@@ -221,7 +221,7 @@ int row_contraction(const float* A, int64_t lda, const float* B, int64_t ldb, in
 int column_sums(const float* A, int64_t lda, int N, int64_t rows, float* part, float* out,
                 int accumulate, hipStream_t st) {
   const int nz = (int)((rows + kColChunk - 1) / kColChunk);
-  STEP("dec_bgrad/hbm", tfm::launch_colsum<float>(rows, N, A, lda, nullptr, 0, kColChunk, part, st));
+  STEP("dec_bgrad/hbm", tfm::launch_colsum(rows, N, A, lda, kColChunk, part, st));
   STEP("dec_bgrad_reduce/hbm", tfm::launch_reduce_z(nz, N, N, part, out, accumulate, st));
   return TFM_OK;
 }

@@ -1,43 +1,16 @@
 // Kernels of the float32 mode (declarations in f32.h).
 //
-// Every product runs on v_mfma_f32_16x16x4_f32 (float32 operands and accumulators; 157 TFLOP/s,
-// as much as the vector unit's FMAs could reach with every slot filled).  Lane layout, with
-// g = lane / 16 and c = lane % 16:
-//   A (16 x 4): lane holds A[c][g];  B (4 x 16): lane holds B[g][c];
-//   D (16 x 16): lane holds D[4g .. 4g+3][c].
-// Any bijection between the contraction index and (instruction, g) that A and B share gives the
-// same product, which the kernels use to read operands 16 bytes per lane and, in the attention
-// kernels, to feed a D tile straight back in as a B operand.
+// Every product runs on the fp32 matrix cores (operand layout in f32_frag.h).
 #include "f32.h"
 
 #include <algorithm>
 
-#include "mfma.h"
+#include "f32_frag.h"
+#include "gelu.h"
 
 namespace tfm {
 
 namespace {
-
-__device__ __forceinline__ f32x4 mfma32(float a, float b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float4 ld4(const float* p) {
-  return *reinterpret_cast<const float4*>(p);
-}
-__device__ __forceinline__ float4 ld4(const bf16* p) {
-  const uint2 u = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-}
-__device__ __forceinline__ void st4(float* p, const float4& v) {
-  *reinterpret_cast<float4*>(p) = v;
-}
-__device__ __forceinline__ void st4(bf16* p, const float4& v) {
-  *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16),
-                                            (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16));
-}
-__device__ __forceinline__ float4 zf4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 
 // Native cell of active cell p (p < 2^26, so 32-bit division).
 __device__ __forceinline__ int64_t native32(const Geo& g, int64_t p) {
@@ -278,14 +251,6 @@ __global__ __launch_bounds__(256) void k_f32_ln_bwd(Geo g, const T* __restrict__
 // consecutive k of its row at once; LDS rows of 36 floats keep those 16-byte reads apart.  A
 // transposed weight is staged as it lies ([k][n], rows of 68 floats) and read one float a lane.
 constexpr int LK = 32, LSR = 36, LST = 68;
-
-__device__ __forceinline__ float gelu_exact(float x) {
-  return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_exact_grad(float x) {
-  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-  return cdf + x * 0.39894228040143268f * expf(-0.5f * x * x);
-}
 
 template <class T, int AM, bool WT, int EPI>
 __global__ __launch_bounds__(256) void k_f32_linear(F32LinArgs<T> a) {

@@ -1,4 +1,4 @@
-// Attention of the float32 mode (declarations and operand layout in f32.h and f32.hip): float32
+// Attention of the float32 mode (declarations in f32.h, operand layout in f32_frag.h): float32
 // products on v_mfma_f32_16x16x4_f32, softmax in float32.
 //
 // A wave owns 16 queries (or, for the key and value gradients, 16 keys).  It computes score
@@ -12,31 +12,12 @@
 #include <math.h>
 
 #include "f32.h"
-#include "mfma.h"
+#include "f32_frag.h"
 
 namespace tfm {
 
 namespace {
 
-__device__ __forceinline__ f32x4 mfma32(float a, float b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ float4 ld4(const float* p) {
-  return *reinterpret_cast<const float4*>(p);
-}
-__device__ __forceinline__ float4 ld4(const bf16* p) {
-  const uint2 u = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-}
-__device__ __forceinline__ void st4(float* p, const f32x4& v) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-__device__ __forceinline__ void st4(bf16* p, const f32x4& v) {
-  *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                            (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
-}
-__device__ __forceinline__ float4 zf4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 __device__ __forceinline__ float el(const float4& v, int j) {
   return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }

@@ -1,4 +1,5 @@
-// Exact-erf GELU and its derivative on the VALU, shared by the MFMA kernels.
+// Exact-erf GELU and its derivative on the VALU: gelu_f for the bfloat16 kernels, gelu_exact (the
+// library's erff) for float32 arithmetic.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -29,6 +30,14 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
   float e;
   const float cdf = norm_cdf(x, &e);
   return fmaf(x * 0.39894228040143268f, e, cdf);
+}
+
+__device__ __forceinline__ float gelu_exact(float x) {
+  return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
+}
+__device__ __forceinline__ float gelu_exact_grad(float x) {
+  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  return cdf + x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
 }  // namespace tfm

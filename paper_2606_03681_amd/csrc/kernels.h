@@ -10,8 +10,8 @@ namespace tfm {
 // arguments (stream-ordered, no host synchronisation, host memory free to reuse at return).
 hipError_t launch_upload(const int32_t* host, int64_t count, int32_t* dst, hipStream_t s);
 
-// partial[z][j] = sum over rows m of chunk z of A[m*lda+j] (* B[m*ldb+j] if B non-null)
-template <class T>
-hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B, int64_t ldb,
-                         int64_t chunk, float* partial, hipStream_t s);
+// partial[z][j] = sum over rows m of chunk z of A[m * lda + j]
+hipError_t launch_colsum(int64_t M, int Nj, const float* A, int64_t lda, int64_t chunk,
+                         float* partial, hipStream_t s);
+
 }  // namespace tfm

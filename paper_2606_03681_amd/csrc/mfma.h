@@ -73,9 +73,6 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
   return *reinterpret_cast<uint32_t*>(&r);
 }
 
-// One bf16 from a float (round to nearest even) through the hardware convert.
-__device__ __forceinline__ uint16_t to_bf16(float a) { return (uint16_t)(pack2(a, 0.f) & 0xffffu); }
-
 // 2^x on the transcendental unit (v_exp_f32), without the library's range handling; the
 // callers pass arguments <= 0 whose results below the float range may flush to 0.
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }

@@ -1,4 +1,4 @@
-// Small kernels shared by every path: uploads through kernel arguments and column sums.
+// Small kernels: uploads through kernel arguments, column sums of the decoder's bias gradients.
 #include "kernels.h"
 
 namespace tfm {
@@ -27,39 +27,24 @@ hipError_t launch_upload(const int32_t* host, int64_t count, int32_t* dst, hipSt
 }
 
 // ============================================================================ column sums
-template <class T>
-__global__ void k_colsum(int64_t M, int Nj, const T* __restrict__ A, int64_t lda,
-                         const T* __restrict__ B, int64_t ldb, int64_t chunk,
-                         float* __restrict__ part) {
+__global__ void k_colsum(int64_t M, int Nj, const float* __restrict__ A, int64_t lda,
+                         int64_t chunk, float* __restrict__ part) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= Nj) return;
   int64_t mb = (int64_t)blockIdx.y * chunk;
   int64_t me = (mb + chunk < M) ? mb + chunk : M;
   float acc = 0.f;
-  for (int64_t m = mb; m < me; ++m) {
-    float v = ld(A + m * lda + j);
-    if (B) v *= ld(B + m * ldb + j);
-    acc += v;
-  }
+  for (int64_t m = mb; m < me; ++m) acc += A[m * lda + j];
   part[(int64_t)blockIdx.y * Nj + j] = acc;
 }
 
-template <class T>
-hipError_t launch_colsum(int64_t M, int Nj, const T* A, int64_t lda, const T* B, int64_t ldb,
-                         int64_t chunk, float* partial, hipStream_t s) {
+hipError_t launch_colsum(int64_t M, int Nj, const float* A, int64_t lda, int64_t chunk,
+                         float* partial, hipStream_t s) {
   int64_t Z = (M + chunk - 1) / chunk;
   if (Z < 1) Z = 1;
   dim3 grid((unsigned)((Nj + 255) / 256), (unsigned)Z);
-  k_colsum<T><<<grid, 256, 0, s>>>(M, Nj, A, lda, B, ldb, chunk, partial);
+  k_colsum<<<grid, 256, 0, s>>>(M, Nj, A, lda, chunk, partial);
   return hipGetLastError();
 }
-
-// ============================================================================ instantiations
-#define INST(T)                                                                               \
-  template hipError_t launch_colsum<T>(int64_t, int, const T*, int64_t, const T*, int64_t,   \
-                                       int64_t, float*, hipStream_t);
-
-INST(float)
-INST(bf16)
 
 }  // namespace tfm
