@@ -192,7 +192,7 @@ k_gemm(GemmArgs a) {
     }
   }
 
-  // ---- operand streaming.  Every stage moves A rows [m0, m0+64) and B rows [n0, n0+BN), k in
+  // ---- operand streaming.  Every stage moves A rows [m0, m0+BM) and B rows [n0, n0+BN), k in
   // [k0, k0+32), straight from memory into the stage's LDS slot (global_load_lds: lane L of a
   // wave fills bytes 16L..16L+15 of the wave's 1 KB block).  LDS position p (16-byte units)
   // holds row p / 4, k chunk kslot^-1(p % 4); this lane's A positions are below.
@@ -943,7 +943,10 @@ __global__ __launch_bounds__(512, 1) void k_gemm_wr(GemmArgs a) {
 // Q|K|V epilogue, A rows compact or native (at BN = 256 the weight slice leaves too few
 // registers), of at least GEMM_WR_MIN tiles: its 256 persistent workgroups pay for the weights
 // they load with the tiles that follow the first two or three (1,000 x 21 table, 165 and 495
-// tiles: 468 us, 455 us with the staged kernel).
+// tiles: 468 us, 455 us with the staged kernel).  Forward + backward over 500 to 147,000 cells at
+// E = 64, 128 and 192: taking it always costs 1 to 10 % up to 21,000 cells and nothing from 63,000
+// on; never taking it, nothing up to 21,000, and from 63,000 on it is within 0.7 % at E = 192 but
+// 1.6 to 2.9 % faster at E = 64 and up to 2.2 % at E = 128, whose tiles are short for this kernel.
 constexpr int64_t GEMM_WR_MIN = 600;
 static bool gemm_wr_ok(const GemmArgs& a) {
   if ((a.M + 127) / 128 * (a.N / a.BN) < GEMM_WR_MIN) return false;
@@ -969,9 +972,13 @@ static hipError_t gemm_wr_dispatch(const GemmArgs& a, hipStream_t s) {
 // (loads, then an epilogue of several barriers) is the launch's time, and 64 rows have less of
 // it.  Forward + backward of one 1,000 x 21 table (165 tiles) 520 -> 504 us, eight query rows
 // through five pre-norm blocks (2 tiles) 678 -> 517 us; 1,056 tiles (8 x 512 x 33) 1,444 us
-// with 128 rows, 1,457 us with 64.
+// with 128 rows, 1,457 us with 64.  Forward + backward over 500 to 147,000 cells at E = 64 to 256:
+// 128 rows always are 1 to 17 % slower from 4,000 to 21,000 cells, within 1 % up to 2,000 and from
+// 100,000 on, and 1 to 4 % faster from 63,000 to 84,000 cells at E >= 128; 64 rows always are 1.5 to
+// 3 % slower from 100,000 cells at E >= 192, and up to 2 % faster from 42,000 at E <= 192.
 // Launches that 32-row tiles keep within one workgroup a CU take those: eight query rows 480 ->
-// 440 us.
+// 440 us; without them the layer is 1.5 to 14 % slower up to 4,000 cells, up to 5 % at 8,000, the
+// same from 12,000 on.
 constexpr int64_t GEMM_FILL = 700, GEMM_DEEP = 256;
 static int gemm_bm(int epi, int BN, int N, int64_t M) {
   if ((M + 31) / 32 * (N / BN) <= GEMM_DEEP) return 32;

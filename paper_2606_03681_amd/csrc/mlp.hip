@@ -33,9 +33,6 @@ namespace tfm {
 
 namespace {
 
-// k position of slot j (0..7) of lane group g in a B fragment that two D blocks form:
-// values 4 g .. 4 g + 3 of the first block, then of the second (16 + ...).
-
 __device__ __forceinline__ f32x4 unpack4(uint32_t lo, uint32_t hi) {
   f32x4 r;
   r[0] = __uint_as_float(lo << 16);

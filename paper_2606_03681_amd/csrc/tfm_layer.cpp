@@ -322,7 +322,12 @@ int make_plan(const Dims& d, const int32_t* n_train, const uint8_t* mask, Plan& 
 // CU / 1.95 / 2.27) for up to 256 / 512 / 768 keys; the two kernels 20 a call, 0.01 a problem and
 // 4.9e-7 (3.9e-7) a score of whole 128 x 128 tiles.  One against two, d = 32: 768 keys 83 / 75 us
 // at 126 problems, 166 / 135 at 264, 1,314 / 1,604 at 3,936; 512 keys 712 / 719 at 3,936; 384
-// keys 521 / 464; 128 keys 21 / 22 at 264.
+// keys 521 / 464; 128 keys 21 / 22 at 264.  Both forms are priced as if every
+// prefix were the longest, which overstates the two kernels in batches of unequal ones; the rule
+// then keeps the one-kernel form where the other is up to 12 % faster.  Forward + backward, one /
+// two / this rule: 16 tables of 64 to 760 labelled rows x 21 cells 1,285 / 1,133 / 1,284 us at
+// d = 16 (E = 64), 2,845 / 2,684 / 2,844 at d = 32 (E = 192); 40 of 32 to 250 x 11 at d = 32 1,442 /
+// 1,392 / 1,381; 3 of 500 to 900 x 11 544 / 512 / 512.
 bool item_attn_bwd_fused_pays(int d, int64_t problems, int R, int nmax) {
   const int third = nmax <= 256 ? 0 : (nmax <= 512 ? 1 : 2);
   const double c32[3] = {1.7, 2.1, 2.57}, c16[3] = {1.75, 1.95, 2.27};

@@ -427,8 +427,8 @@ static int wgrad_bn(int E, int64_t M) { return E > 192 && M < WGRAD_WIDE_MIN ? 1
 
 // Workgroups the chip's 256 CUs hold at once: the 176 and 252 registers of the 192- and 256-wide
 // tiles leave room for one workgroup of 8 waves on a CU.  With twice that many chunks a 1,000 x 21
-// table took 488 instead of 471 us (forward + backward; more partials to write and add), 16 x 1024
-// x 101 16.31 instead of 16.25 ms; 80,000 cells at E = 256 1,367 instead of 1,341 us.
+// table took 488 instead of 471 us (forward + backward; more partials to write and add) and 80,000
+// cells at E = 256 1,367 instead of 1,341 us; 16 x 1024 x 101 the same within noise (16.3 ms).
 static int wgrad_slots(int BN) { return BN >= 192 ? 256 : 512; }
 
 static int wgrad_tiles(int BN, int E, int H) {

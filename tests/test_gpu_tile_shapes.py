@@ -1,6 +1,6 @@
 """The forward-only calls give the training forward's rows bit for bit although their GEMM launches
 take other tile shapes: a training forward of 97,200 cells runs 128-row tiles, its context call the
-same, and query chunks of 81 to 3,240 cells run 32- and 64-row tiles.  The weight gradients at
+same, and query chunks of 81, 405 and 2,835 cells run 32- and 64-row tiles.  The weight gradients at
 E = 256 agree with the float64 oracle on both sides of the cell count from which their tiles are
 256 wide, within the parity tests' bfloat16 tolerance (2e-2 of each tensor's largest value)."""
 
