@@ -113,7 +113,7 @@ TEST_CONFIGS = {
                               n_train=(550, 950), C=8, active=(4, 8), mask="random", E=192,
                               heads=6, H=384, layers=1, cells="normal", weights="xavier_bias"),
     # rows wider than the matrix-core feature attention takes (more than 128 cells at d = 32,
-    # more than 64 at d = 64): the bfloat16 feature attention runs on the vector kernels
+    # more than 64 at d = 64): the bfloat16 feature attention runs in float32 arithmetic
     "wide-d32-bf16": dict(name="wide-d32-bf16", dtype="bf16", B=3, R=128, n_train=(1, 128),
                           C=150, active=(100, 150), mask="random", E=64, heads=2, H=128,
                           layers=1, cells="normal", weights="xavier_bias"),
