@@ -974,16 +974,22 @@ static hipError_t gemm_wr_dispatch(const GemmArgs& a, hipStream_t s) {
 // through five pre-norm blocks (2 tiles) 678 -> 517 us; 1,056 tiles (8 x 512 x 33) 1,444 us
 // with 128 rows, 1,457 us with 64.  Forward + backward over 500 to 147,000 cells at E = 64 to 256:
 // 128 rows always are 1 to 17 % slower from 4,000 to 21,000 cells, within 1 % up to 2,000 and from
-// 100,000 on, and 1 to 4 % faster from 63,000 to 84,000 cells at E >= 128; 64 rows always are 1.5 to
-// 3 % slower from 100,000 cells at E >= 192, and up to 2 % faster from 42,000 at E <= 192.
+// 100,000 on, and 1 to 2.4 % faster near 84,000 at E >= 128; 64 rows always are 1.5 to 3 % slower
+// from 100,000 cells at E >= 192, and up to 2 % faster from 42,000 at E <= 192.
 // Launches that 32-row tiles keep within one workgroup a CU take those: eight query rows 480 ->
 // 440 us; without them the layer is 1.5 to 14 % slower up to 4,000 cells, up to 5 % at 8,000, the
 // same from 12,000 on.
 constexpr int64_t GEMM_FILL = 700, GEMM_DEEP = 256;
+// Single-column launches at E >= 192 whose 128-row tiles all run at once (two on a CU) while 64-row
+// ones would leave a second, nearly empty round after the first 768 take 128 rows: 54,000 to 60,000
+// cells, forward 316 -> 303 us (E = 192, H = 768) and 393 -> 375 us (E = 256, H = 768, pre-norm).
+constexpr int64_t GEMM_ONCE_64 = 768, GEMM_ONCE_128 = 512;
 static int gemm_bm(int epi, int BN, int N, int64_t M) {
   if ((M + 31) / 32 * (N / BN) <= GEMM_DEEP) return 32;
   if (BN > 192 && (epi == EPI_LN_BWD || epi == EPI_RMS_BWD)) return GEMM_BM;
-  return (M + 127) / 128 * (N / BN) < GEMM_FILL ? GEMM_BM : 128;
+  const int64_t t128 = (M + 127) / 128 * (N / BN);
+  if (N == BN && BN >= 192 && t128 <= GEMM_ONCE_128 && gemm_row_tiles(M) > GEMM_ONCE_64) return 128;
+  return t128 < GEMM_FILL ? GEMM_BM : 128;
 }
 
 // Row tiles (partial rows of LN_BWD / RMS_BWD) of any M <= Mmax.
